@@ -7,35 +7,43 @@
 // the knot minimising BIC = T ln(RSS / T) + df ln T (df = nonzero coefficients) is kept.
 //
 // Everything the path needs is in one FP64 matrix: the centred cross-products C of the
-// m (p + 1) lag-embedded columns, shared by all m regressions.  One workgroup follows one
-// variable's path on it.  Its state lives in a region of global memory of its own:
-//   Gi   inverse of the (unsigned) Gram of the active columns, updated by bordering when a
-//        column joins and by the Schur complement when one leaves (O(|A|^2) each).  The
-//        rank-one parts of up to kPruneDefer borderings are kept as a thin factor and applied
-//        together, so a joining column costs one read of Gi (to form G_A^{-1} b) and Gi is
-//        rewritten once per kPruneDefer joins (and before a column leaves);
-//   q    G_A^{-1} s, bordered along with Gi (recomputed from Gi after a column leaves);
-//   c    correlations z~_j^T r with the current residual, updated by c -= gamma a;
+// m (p + 1) lag-embedded columns, shared by all m regressions (lag 0 in the causal order, so a
+// design's columns are two runs of consecutive columns of C).  One workgroup follows one
+// variable's path on it.  Its state:
+//   Li   the inverse of the Cholesky factor of the active columns' Gram (lower triangular,
+//        G_A^{-1} = Li^T Li), in a region of global memory of its own.  A joining column appends
+//        one row and leaves the others as they are; a leaving one rotates the rows below it;
+//   q    G_A^{-1} s, bordered along with Li (recomputed from Li after a column leaves);
+//   c    correlations z~_j^T r of the inactive columns with the current residual, updated by
+//        c -= gamma a; an active column's is s_j C after every step (the equiangular property);
 //   beta the scaled coefficients, best the coefficients of the best knot so far.
-// The correlation of an active column is set to s_j C after every step (the equiangular
-// property), and the residual sum of squares follows from the correlations:
-//   RSS = y^T y - sum_{j in A} beta_j (c0_j + c_j).
+// The residual sum of squares follows from the step: the direction u has |u| = 1 and
+// u^T r = C / A_A, so RSS falls by gamma (2 C / A_A - gamma).
 // Numerical rules, shared with the FP64 reference: a step must exceed 1e-12 of the full step
 // C / A_A; a column whose Schur complement against the active ones is <= 1e-12 of its squared
 // norm is excluded; the path ends once C <= 1e-12 C_0, at the least-squares fit, or after the
 // step limit (8 d by default).  Ties go to the lowest design column.
+//
+// What bounds it: memory.  A step with |A| of d columns active reads Li once (|A|^2 / 2
+// doubles, private to the variable: 3.3 GB of active matrices at m = 400, p = 2, far over the
+// caches) and min(|A|, d - |A|) rows of C (shared, 11.5 MB: served by L2 and the Infinity Cache).
+// Measured at m = 400, p = 2, n = 10^4, complete paths: 191 ms a call, 1.4 TB read; 601 ms with the
+// inverse of the active Gram itself kept and updated (1.25 |A|^2 doubles a step, written too).
+// Clocks of the longest path (1199 columns): 71 ms in the products with C, 89 ms in those with
+// Li, 23 ms in the rest; together the workgroups move ~9 TB/s through the caches.
 #include "prune.hpp"
 #include "gram.hpp"
+#include "order_dev.hpp"
 #include "profile.hpp"
 #include "var_fit.hpp"
+
 
 namespace vl {
 namespace {
 
 constexpr int kPT = 512;            // threads per variable
-constexpr int kU = 8;               // independent loads in flight per thread (row updates)
-constexpr int kUD = 16;             // independent loads in flight per thread (dot products)
 constexpr int kPW = kPT / kWave;
+constexpr int kPanel = 1024;        // inactive columns per pass when the state is in memory
 constexpr double kGammaRel = 1e-12;
 constexpr double kCollinearRel = 1e-12;
 constexpr double kStopRel = 1e-12;
@@ -44,7 +52,7 @@ constexpr int kNone = 0x7fffffff;
 struct PruneArgs {
   const double* C;
   int64_t ldc, m, T, cap;
-  int p;
+  int p, dmax;
   const int32_t* order;
   const double* B0;
   const double* Bl;
@@ -55,87 +63,96 @@ struct PruneArgs {
   int32_t* st;
 };
 
-// sum_k M[k ld + r] v[k] over k < n (a row of a column-major matrix times a vector), with kU
-// loads in flight; a fixed summation order, so repeated calls give the same bits.
-__device__ inline double col_dot(const double* __restrict__ M, int64_t ld, int r,
-                                 const double* __restrict__ v, int n) {
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  int k = 0;
-  for (; k + kUD <= n; k += kUD) {
-    double x[kUD];
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) x[u] = M[(int64_t)(k + u) * ld + r];
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) s[u & 3] += x[u] * v[k + u];
-  }
-  for (; k < n; ++k) s[0] += M[(int64_t)k * ld + r] * v[k];
-  return (s[0] + s[1]) + (s[2] + s[3]);
+// Sum over the wave, the same bits in every lane (DPP and permlane butterflies).
+__device__ inline double wave_allsum_d(double v) {
+  v += dpp_f64<kDppRowMirror>(v);
+  v += dpp_f64<kDppHalfMirror>(v);
+  v += dpp_f64<kDppQuadXor2>(v);
+  v += dpp_f64<kDppQuadXor1>(v);
+  v += partner16_f64(v);
+  v += partner32_f64(v);
+  return v;
 }
 
-// sum_r Cj[col[r] ld] w[r] over r < n (a gathered row of the covariance times a vector)
-__device__ inline double gather_dot(const double* __restrict__ Cj, int64_t ld,
-                                    const int* __restrict__ col, const double* __restrict__ w,
-                                    int n) {
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  int r = 0;
-  for (; r + kUD <= n; r += kUD) {
-    double x[kUD];
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) x[u] = Cj[(int64_t)col[r + u] * ld];
-#pragma unroll
-    for (int u = 0; u < kUD; ++u) s[u & 3] += x[u] * w[r + u];
-  }
-  for (; r < n; ++r) s[0] += Cj[(int64_t)col[r] * ld] * w[r];
-  return (s[0] + s[1]) + (s[2] + s[3]);
-}
-
-// Row x of a column-major matrix: M[y ld + x] += a f[y] for y < n, kU loads in flight.
-__device__ inline void row_axpy(double* __restrict__ M, int64_t ld, int x, double a,
-                                const double* __restrict__ f, int n) {
-  int y = 0;
-  for (; y + kU <= n; y += kU) {
-    double v[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) v[u] = M[(int64_t)(y + u) * ld + x];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) M[(int64_t)(y + u) * ld + x] = v[u] + a * f[y + u];
-  }
-  for (; y < n; ++y) M[(int64_t)y * ld + x] += a * f[y];
-}
-
-// Workgroup sum, the same bits in every thread (lane 0 of each wave, waves in a fixed order).
-__device__ inline double wg_sum(double v, double* red) {
-  v = wave_sum_d(v);
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = v;
-  __syncthreads();
-  double s = red[0];
-#pragma unroll
-  for (int w = 1; w < kPW; ++w) s += red[w];
-  return s;
-}
-
-__device__ inline void take_min(double& g, int& j, double g2, int j2) {
-  if (g2 < g || (g2 == g && j2 < j)) {
-    g = g2;
-    j = j2;
-  }
-}
-
-// Workgroup (value, index) minimum, lowest index on ties; exact, so the same in every thread.
-__device__ inline void wg_argmin(double& g, int& j, double* rg, int* rj) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) take_min(g, j, __shfl_xor(g, s, kWave), __shfl_xor(j, s, kWave));
+// Workgroup sums of two values, the same bits in every thread (waves in a fixed order).
+__device__ inline void wg_sum2(double& a, double& b, double* red) {
+  a = wave_allsum_d(a);
+  b = wave_allsum_d(b);
   __syncthreads();
   if ((threadIdx.x & (kWave - 1)) == 0) {
-    rg[threadIdx.x / kWave] = g;
-    rj[threadIdx.x / kWave] = j;
+    red[threadIdx.x / kWave] = a;
+    red[kPW + threadIdx.x / kWave] = b;
   }
   __syncthreads();
-  g = rg[0];
-  j = rj[0];
+  a = red[0];
+  b = red[kPW];
 #pragma unroll
-  for (int w = 1; w < kPW; ++w) take_min(g, j, rg[w], rj[w]);
+  for (int w = 1; w < kPW; ++w) {
+    a += red[w];
+    b += red[kPW + w];
+  }
+}
+
+__device__ inline double wg_sum(double v, double* red) {
+  double z = 0.0;
+  wg_sum2(v, z, red);
+  return v;
+}
+
+// A candidate step: its length, the design column that breaks ties, the slot it is held in.
+struct Cand {
+  double g = INFINITY;
+  int j = kNone, slot = kNone;
+  __device__ inline void take(double g2, int j2, int s2) {
+    if (g2 < g || (g2 == g && j2 < j)) {
+      g = g2;
+      j = j2;
+      slot = s2;
+    }
+  }
+};
+
+// Smallest candidate of the wave, the lowest design column on ties, in every lane.
+__device__ inline void wave_min_cand(Cand& x) {
+  const double g = wave_min_quiet(x.g);
+  const int j = wave_min_i32(x.g == g ? x.j : kNone);
+  const int s = wave_min_i32(x.g == g && x.j == j ? x.slot : kNone);
+  x.g = g;
+  x.j = j;
+  x.slot = s;
+}
+
+// Workgroup minima of two candidates, exact, so the same in every thread.
+__device__ inline void wg_min2(Cand& x, Cand& y, double* rg, int* rj) {
+  wave_min_cand(x);
+  wave_min_cand(y);
+  __syncthreads();
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    const int w = threadIdx.x / kWave;
+    rg[w] = x.g;
+    rg[kPW + w] = y.g;
+    rj[w] = x.j;
+    rj[kPW + w] = x.slot;
+    rj[2 * kPW + w] = y.j;
+    rj[3 * kPW + w] = y.slot;
+  }
+  __syncthreads();
+  x = Cand{rg[0], rj[0], rj[kPW]};
+  y = Cand{rg[kPW], rj[2 * kPW], rj[3 * kPW]};
+#pragma unroll
+  for (int w = 1; w < kPW; ++w) {
+    x.take(rg[w], rj[w], rj[kPW + w]);
+    y.take(rg[kPW + w], rj[2 * kPW + w], rj[3 * kPW + w]);
+  }
+}
+
+// The lane index, opaque to the optimiser: what is derived from it is then formed where it is
+// used.  Otherwise the row offsets below are hoisted out of the path's loop, held in registers
+// across all of it, and spilled (129 registers at NC = 20).
+__device__ __forceinline__ int fresh_lane() {
+  int lane = threadIdx.x & (kWave - 1);
+  asm volatile("" : "+v"(lane));
+  return lane;
 }
 
 // Values every thread of the workgroup holds alike (read back from LDS after a reduction),
@@ -147,65 +164,157 @@ __device__ inline int64_t uni64(int64_t v) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Workgroup sums of kPruneDefer values at once, the same bits in every thread.
-__device__ inline void wg_sum_vec(double (&v)[kPruneDefer], double* red) {
+// ------------------------------------------------------------------------------------------
+// Li, packed by blocks of 64 rows: block k holds rows 64 k .. 64 k + 63, each 64 (k + 1)
+// doubles long (its entries, then zeros), so a wave reads a row as k + 1 aligned 512-byte
+// pieces and the whole matrix is read in memory order.
+// ------------------------------------------------------------------------------------------
+__device__ inline int64_t li_row(int r) {
+  const int64_t k = r >> 6;
+  return 2048 * k * (k + 1) + (int64_t)(r & 63) * 64 * (k + 1);
+}
+
+// Rows of block k - 1 (k = K or K - 1 pieces a row) against x: the wave's rows 64 (k - 1) + w +
+// 8 i, two at a time.  Each row stays in registers between its dot product y_r = Li_r x and its
+// share of g += Li_r^T y_r, so Li is read once; ysq sums y_r^2.
+template <int K, int NC>
+__device__ __forceinline__ void li_block(const double* __restrict__ Li, int k, int n, int w,
+                                         const double (&x)[NC], double (&g)[NC], double& ysq) {
+  const double* B = Li + 2048 * (int64_t)(k - 1) * k + fresh_lane();
+  const bool odd = k < K;
+#pragma unroll 1
+  for (int i = w; i < 64; i += 2 * kPW) {
+    const int r = 64 * (k - 1) + i;
+    if (r >= n) break;
+    const bool two = r + kPW < n;
+    const double* p0 = B + i * 64 * k;
+    const double* p1 = two ? p0 + kPW * 64 * k : p0;
+    double a0[K], a1[K];
 #pragma unroll
-  for (int q = 0; q < kPruneDefer; ++q) v[q] = wave_sum_d(v[q]);
-  __syncthreads();
-  if ((threadIdx.x & (kWave - 1)) == 0) {
+    for (int c = 0; c < K - 1; ++c) a0[c] = p0[64 * c];
 #pragma unroll
-    for (int q = 0; q < kPruneDefer; ++q) red[q * kPW + threadIdx.x / kWave] = v[q];
-  }
-  __syncthreads();
+    for (int c = 0; c < K - 1; ++c) a1[c] = p1[64 * c];
+    a0[K - 1] = a1[K - 1] = 0.0;
+    if (!odd) {
+      a0[K - 1] = p0[64 * (K - 1)];
+      a1[K - 1] = p1[64 * (K - 1)];
+    }
+    double s0 = 0.0, s1 = 0.0;
 #pragma unroll
-  for (int q = 0; q < kPruneDefer; ++q) {
-    double s = red[q * kPW];
-    for (int w = 1; w < kPW; ++w) s += red[q * kPW + w];
-    v[q] = s;
+    for (int c = 0; c < K; ++c) {
+      s0 = fma(a0[c], x[c], s0);
+      s1 = fma(a1[c], x[c], s1);
+    }
+    s0 = wave_allsum_d(s0);
+    s1 = two ? wave_allsum_d(s1) : 0.0;
+    ysq = fma(s0, s0, ysq);
+    ysq = fma(s1, s1, ysq);
+#pragma unroll
+    for (int c = 0; c < K; ++c) g[c] = fma(a1[c], s1, fma(a0[c], s0, g[c]));
   }
 }
 
-constexpr int kFC = 256;  // rows of the deferred factor staged in LDS per flush chunk
+// Every block of rows; one instance per two piece counts keeps the loop's code (it runs through
+// all of them each step) well inside the instruction cache.
+template <int K, int NC>
+__device__ __forceinline__ void li_blocks(const double* __restrict__ Li, int n, int w,
+                                          const double (&x)[NC], double (&g)[NC], double& ysq) {
+  const int nb = (n + 63) >> 6;
+#pragma unroll 1
+  for (int k = K - 1; k <= K && k <= nb; ++k) li_block<K, NC>(Li, k, n, w, x, g, ysq);
+  if constexpr (K < NC) {
+    if (K < nb) li_blocks<K + 2, NC>(Li, n, w, x, g, ysq);
+  }
+}
 
-// Gi(x, y) += sum_q U_q[x] w_q U_q[y] for x, y < n: the deferred rank-one terms applied in one
-// read and one write of Gi.  us: kPruneDefer x kFC doubles of LDS.
-__device__ inline void flush_deferred(double* __restrict__ Gi, int64_t dA,
-                                      const double* __restrict__ U, int64_t ldu,
-                                      const double* __restrict__ w, int nU, int n,
-                                      double* __restrict__ us) {
-  for (int y0 = 0; y0 < n; y0 += kFC) {
-    const int ny = min(kFC, n - y0);
-    __syncthreads();
-    for (int e = threadIdx.x; e < kPruneDefer * kFC; e += kPT) {
-      const int q = e / kFC, yy = e % kFC;
-      us[e] = q < nU && yy < ny ? U[(int64_t)q * ldu + y0 + yy] * w[q] : 0.0;
+// out = G_A^{-1} x = Li^T (Li x) over n active slots; returns |Li x|^2 (every thread alike).
+// NC > 0: rows in registers, one read of Li (n <= 64 NC; x in LDS, zeros up to
+// the next multiple of 64).  NC = 0: any n, Li read twice (the
+// row sums through y, a scratch vector of n).  Ends with a barrier; x, out may not alias.
+template <int NC>
+__device__ inline double apply_inverse(const double* __restrict__ Li, int n, const double* x,
+                                       double* out, double* y, double* part, double* red) {
+  const int t = threadIdx.x, lane = fresh_lane(), w = uni(t / kWave);
+  double ysq = 0.0, z = 0.0;
+  if constexpr (NC > 0) {
+    double xr[NC], g[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      xr[c] = 64 * c < n ? x[64 * c + lane] : 0.0;
+      g[c] = 0.0;
+    }
+    static_assert(NC % 2 == 0, "two piece counts an instance");
+    li_blocks<2, NC>(Li, n, w, xr, g, ysq);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int e = 64 * c + lane;
+      if (e < n) part[w * n + e] = g[c];
+    }
+    ysq = lane == 0 ? ysq : 0.0;
+    wg_sum2(ysq, z, red);
+    for (int r = t; r < n; r += kPT) {
+      double s = part[r];
+#pragma unroll
+      for (int q = 1; q < kPW; ++q) s += part[q * n + r];
+      out[r] = s;
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < n; x += kPT) {
-      double ux[kPruneDefer];
-#pragma unroll
-      for (int q = 0; q < kPruneDefer; ++q) ux[q] = q < nU ? U[(int64_t)q * ldu + x] : 0.0;
-      constexpr int kF = 4;  // rows of Gi in flight per group (register budget)
-      int yy = 0;
-      for (; yy + kF <= ny; yy += kF) {
-        double v[kF];
-#pragma unroll
-        for (int u = 0; u < kF; ++u) v[u] = Gi[(int64_t)(y0 + yy + u) * dA + x];
-#pragma unroll
-        for (int u = 0; u < kF; ++u) {
-          double sum = 0.0;
-#pragma unroll
-          for (int q = 0; q < kPruneDefer; ++q) sum += ux[q] * us[q * kFC + yy + u];
-          Gi[(int64_t)(y0 + yy + u) * dA + x] = v[u] + sum;
-        }
-      }
-      for (; yy < ny; ++yy) {
-        double sum = 0.0;
-#pragma unroll
-        for (int q = 0; q < kPruneDefer; ++q) sum += ux[q] * us[q * kFC + yy];
-        Gi[(int64_t)(y0 + yy) * dA + x] += sum;
-      }
+  } else {
+    for (int r = w; r < n; r += kPW) {
+      const double* p = Li + li_row(r);
+      double s = 0.0;
+      for (int e = lane; e <= r; e += kWave) s = fma(p[e], x[e], s);
+      s = wave_allsum_d(s);
+      ysq = fma(s, s, ysq);
+      if (lane == 0) y[r] = s;
     }
+    ysq = lane == 0 ? ysq : 0.0;
+    wg_sum2(ysq, z, red);
+    for (int e0 = 64 * w; e0 < n; e0 += kPT) {
+      double s = 0.0;
+      for (int r = e0; r < n; ++r) s = fma(Li[li_row(r) + e0 + lane], y[r], s);
+      if (e0 + lane < n) out[e0 + lane] = s;
+    }
+    __syncthreads();
+  }
+  return ysq;
+}
+
+// Removes active slot r0 of n from Li.  G_A^{-1} = sum of the rows' outer products; rotating row
+// r0 into every row below it moves all of column r0 into that one row, whose outer product is
+// then the Schur complement's term, and is dropped.  cs, sn, v, tmp: vectors of n.  Ends with a
+// barrier.
+__device__ inline void li_remove(double* __restrict__ Li, int n, int r0, double* cs, double* sn,
+                                 double* v, double* tmp) {
+  const int t = threadIdx.x;
+  // the rotations follow from column r0 alone
+  for (int k = r0 + t; k < n; k += kPT) sn[k] = Li[li_row(k) + r0];
+  for (int e = t; e < n; e += kPT) v[e] = e <= r0 ? Li[li_row(r0) + e] : 0.0;
+  __syncthreads();
+  if (t == 0) {
+    double h = sn[r0];
+    for (int k = r0 + 1; k < n; ++k) {
+      const double b = sn[k], h2 = sqrt(fma(h, h, b * b));
+      cs[k] = h / h2;
+      sn[k] = b / h2;
+      h = h2;
+    }
+  }
+  __syncthreads();
+  // row k against the carried row v, written to the place of row k - 1 with column r0 left out
+  // once every thread has read its entries of both
+  for (int k = r0 + 1; k < n; ++k) {
+    const double* src = Li + li_row(k);
+    double* dst = Li + li_row(k - 1);
+    const double ck = cs[k], sk = sn[k];
+    for (int e = t; e <= k; e += kPT) {
+      const double b = src[e];
+      tmp[e] = fma(ck, b, -sk * v[e]);
+      v[e] = fma(sk, b, ck * v[e]);
+    }
+    __syncthreads();
+    for (int e = t; e <= k; e += kPT)
+      if (e != r0) dst[e < r0 ? e : e - 1] = tmp[e];
   }
   __syncthreads();
 }
@@ -226,15 +335,113 @@ __global__ __launch_bounds__(256) void prune_check_order_kernel(const int32_t* _
     if (seen[e] != 1) raise_status(st, VL_ERR_INVALID_ARG);
 }
 
+// part[w np + e] = sum over the wave's eighth of the n active slots of C[col_r][ic_e] b_r, for
+// np inactive columns ic: every wave has the same work whatever the split of active and inactive
+// columns.  The slots' columns and weights go to scalar registers; 2 RU loads are in flight per
+// lane (a row of C is read as coalesced pieces where the inactive columns are consecutive).
+template <int RU>
+__device__ inline void inactive_dots(const double* __restrict__ C, int64_t ldc, int n,
+                                     const int* col, const double* b, int np, const int* ic,
+                                     double* part) {
+  const int lane = fresh_lane(), w = uni(threadIdx.x / kWave);
+  const int r0 = n * w / kPW, r1 = n * (w + 1) / kPW;
+  for (int e0 = 0; e0 < np; e0 += 2 * kWave) {
+    const int ea = e0 + lane, eb = ea + kWave;
+    const int oa = ic[min(ea, np - 1)], ob = ic[min(eb, np - 1)];
+    double sa[2] = {0.0, 0.0}, sb[2] = {0.0, 0.0};
+    for (int rb = r0; rb < r1; rb += kWave) {
+      const int rl = min(rb + lane, r1 - 1);
+      const int cl = col[rl];
+      const double bl = rb + lane < r1 ? b[rl] : 0.0;
+      const int lo = __double2loint(bl), hi = __double2hiint(bl);
+      const int nb = min(kWave, r1 - rb);
+#pragma unroll 1
+      for (int u0 = 0; u0 < nb; u0 += RU) {        // lanes past the end: weight 0
+        double xa[RU], xb[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+          const double* row = C + (int64_t)__builtin_amdgcn_readlane(cl, u0 + u) * ldc;
+          xa[u] = row[oa];
+          xb[u] = row[ob];
+        }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+          const double wu = __hiloint2double(__builtin_amdgcn_readlane(hi, u0 + u),
+                                             __builtin_amdgcn_readlane(lo, u0 + u));
+          sa[u & 1] = fma(xa[u], wu, sa[u & 1]);
+          sb[u & 1] = fma(xb[u], wu, sb[u & 1]);
+        }
+      }
+    }
+    if (ea < np) part[w * np + ea] = sa[0] + sa[1];
+    if (eb < np) part[w * np + eb] = sb[0] + sb[1];
+  }
+}
+
+// y[e] = sum_j C[ic_e][col_j] x_j over all d design columns (x in LDS: zero outside the active ones and
+// up to the next multiple of 64) for
+// np inactive columns ic; col_j = j, plus gap from pos on.  The other form of the same products, for more active columns than
+// inactive ones.  A step then reads min(|A|, d - |A|) rows of C whole; by active rows alone the
+// late steps read whole cache lines for a few scattered columns each (the longest path at
+// m = 400, p = 2: 152 ms in these products by active rows alone, 71 ms with both forms).
+template <int K>  // d <= 64 K
+__device__ __forceinline__ void inactive_rows_k(const double* __restrict__ C, int64_t ldc, int d,
+                                                int pos, int gap, const double* x, int np,
+                                                const int* ic, double* y) {
+  const int lane = fresh_lane(), w = uni(threadIdx.x / kWave);
+  double xr[K];
+  uint32_t k[K];
+#pragma unroll
+  for (int c = 0; c < K; ++c) {
+    const int j = min(64 * c + lane, d - 1);
+    k[c] = (uint32_t)(j + (j >= pos ? gap : 0));
+    xr[c] = 64 * c < d ? x[64 * c + lane] : 0.0;
+  }
+#pragma unroll 1
+  for (int e = w; e < np; e += 2 * kPW) {
+    const bool two = e + kPW < np;
+    const double* p0 = C + (int64_t)uni(ic[e]) * ldc;
+    const double* p1 = C + (int64_t)uni(ic[two ? e + kPW : e]) * ldc;
+    double a0[K], a1[K];
+#pragma unroll
+    for (int c = 0; c < K; ++c) a0[c] = p0[k[c]];
+#pragma unroll
+    for (int c = 0; c < K; ++c) a1[c] = p1[k[c]];
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int c = 0; c < K; ++c) {
+      s0 = fma(a0[c], xr[c], s0);
+      s1 = fma(a1[c], xr[c], s1);
+    }
+    s0 = wave_allsum_d(s0);
+    s1 = wave_allsum_d(s1);
+    if (lane == 0) {
+      y[e] = s0;
+      if (two) y[e + kPW] = s1;
+    }
+  }
+}
+
+template <int K, int NC>
+__device__ __forceinline__ void inactive_rows(const double* __restrict__ C, int64_t ldc, int d,
+                                              int pos, int gap, const double* x, int np,
+                                              const int* ic, double* y) {
+  if (d <= 64 * K)
+    inactive_rows_k<K>(C, ldc, d, pos, gap, x, np, ic, y);
+  else if constexpr (K < NC)
+    inactive_rows<K + 2, NC>(C, ldc, d, pos, gap, x, np, ic, y);
+}
+
+// One workgroup per variable.  Active slots sit at the front of the state vectors, inactive
+// columns (in design order until one leaves the active set) at their end, [ib, d).
+//   NC > 0: the state vectors in LDS, designs of at most 64 NC columns;
+//   NC = 0: any size, the state vectors in the region.
+template <int NC>
 __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
-  __shared__ double red[kPW];
-  __shared__ double rg[kPW];
-  __shared__ int rj[kPW];
-  __shared__ int slot;
-  __shared__ double redv[kPruneDefer * kPW];
-  __shared__ double wq[kPruneDefer];  // weights 1 / delta of the deferred terms
-  __shared__ double us[kPruneDefer * kFC];
-  const int t = threadIdx.x;
+  extern __shared__ double dyn[];
+  __shared__ double red[2 * kPW], rg[2 * kPW];
+  __shared__ int rj[4 * kPW], cnt[kPW];
+  const int t = threadIdx.x, lane = t & (kWave - 1), wv = uni(t / kWave);
   const int64_t m = a.m, mp = m * a.p, ldc = a.ldc;
   const int64_t pos = m - 1 - (int64_t)blockIdx.x;  // the longest designs start first
   const int i = min(max(a.order[pos], 0), (int)m - 1);
@@ -243,281 +450,309 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
   double off = 0.0;
   for (int64_t k = t; k < pos; k += kPT) off += (double)prune_region_doubles(k + mp, a.cap);
   const int64_t base = uni64((int64_t)wg_sum(off, red));
-  const int64_t d = pos + mp;
-  const int64_t dA = prune_active_cap(d, a.cap);
-  double* Gi = a.regions + base;
-  double* sc = Gi + dA * dA;
-  double* c0 = sc + d;
-  double* c = c0 + d;
-  double* av = c + d;
-  double* beta = av + d;
-  double* best = beta + d;
-  double* sv = best + d;  // sign of each active slot
-  double* qv = sv + d;    // G_A^{-1} s of the active slots
-  double* dd = qv + d;    // direction of each active slot
-  double* bv = dd + d;    // scaled direction, then the bordering column
-  double* gn = bv + d;    // G_A^{-1} times the bordering column
-  double* U = gn + d;     // deferred rank-one terms of Gi, kPruneDefer columns of d
-  int* idx = reinterpret_cast<int*>(U + (int64_t)kPruneDefer * d);  // column of C per column
-  int* state = idx + d;                       // 0 inactive, 1 active, 2 excluded
-  int* act = state + d;                       // design column of each active slot
-  int* ac = act + d;                          // its column of C
+  const int d = (int)(pos + mp);
+  double* Li = a.regions + base;
+  double* best = Li + prune_li_doubles(prune_active_cap(d, a.cap));
+  // state vectors: scale; beta | correlation; q | Z~^T u; sign; two scratch vectors; column of C;
+  // design column
+  const int D = NC > 0 ? (int)round_up(a.dmax, 64) : d;
+  double* vec;
+  if constexpr (NC > 0) vec = dyn;
+  else vec = best + d;
+  double* sc = vec;
+  double* bc = sc + D;
+  double* qa = bc + D;
+  double* sv = qa + D;
+  double* bv = sv + D;
+  double* gn = bv + D;
+  double *part, *more;                 // wave partials; scratch vectors of li_remove and NC = 0
+  int* col;
+  if constexpr (NC > 0) {
+    part = gn + D;
+    more = part;
+    col = reinterpret_cast<int*>(part + kPW * D);
+  } else {
+    part = dyn;
+    more = gn + D;
+    col = reinterpret_cast<int*>(more + 5 * D);
+  }
+  int* des = col + D;
+  const int panel = NC > 0 ? D : kPanel;
 
   // design columns: lag-0 predecessors in order, then (tau, k) for tau = 1..p, k = 0..m-1
-  double g0 = INFINITY, nkeep = 0.0;
-  int j0 = kNone;
-  for (int64_t j = t; j < d; j += kPT) {
-    int cj;
+  auto design = [&](int j, int& cj, double& s) {
     double bj;
     if (j < pos) {
-      const int v = min(max(a.order[j], 0), (int)m - 1);
-      cj = v;
-      bj = a.B0[(int64_t)i * m + v];
+      cj = j;
+      bj = a.B0[(int64_t)i * m + min(max(a.order[j], 0), (int)m - 1)];
     } else {
-      const int64_t jj = j - pos, tau = jj / m + 1, k = jj % m;
-      cj = (int)(m * tau + k);
-      bj = a.Bl[(tau - 1) * m * m + (int64_t)i * m + k];
+      const int64_t jj = j - pos;
+      cj = (int)(m + jj);
+      bj = a.Bl[jj / m * m * m + (int64_t)i * m + jj % m];
     }
-    const double s = fabs(bj);
-    const double gjj = s * s * a.C[(int64_t)cj * ldc + cj];
-    const double cj0 = s * a.C[(int64_t)cj * ldc + i];
-    idx[j] = cj;
-    sc[j] = s;
-    c0[j] = cj0;
-    c[j] = cj0;
-    beta[j] = 0.0;
+    s = fabs(bj);
+  };
+  double nkeep = 0.0, nok = 0.0;
+  for (int j = t; j < d; j += kPT) {
+    int cj;
+    double s;
+    design(j, cj, s);
     best[j] = 0.0;
-    const bool ok = s > 0.0 && gjj > 0.0;
-    state[j] = ok ? 0 : 2;
     nkeep += s > 0.0 ? 1.0 : 0.0;
-    if (ok) take_min(g0, j0, -fabs(cj0), (int)j);
+    nok += s > 0.0 && s * s * a.C[(int64_t)cj * ldc + cj] > 0.0 ? 1.0 : 0.0;
   }
-  const int64_t n_keep = uni((int)wg_sum(nkeep, red));
-  wg_argmin(g0, j0, rg, rj);
-  j0 = uni(j0);
-  const double C0 = j0 == kNone ? 0.0 : -g0;
-  const double T = (double)a.T, lnT = log(T);
-  const double yy = a.C[(int64_t)i * ldc + i];
-  double best_bic = T * log(yy / T);
-  int best_knot = 0, best_df = 0, steps = 0, nA = 0;
-  const int64_t cap = a.cap > 0 ? a.cap : 8 * n_keep;
-  double Cc = C0;
-  if (C0 > 0.0) {
+  wg_sum2(nkeep, nok, red);
+  int nA = 0, ib = d - uni((int)nok);
+  Cand first, none;
+  for (int j0 = 0, at = ib; j0 < d; j0 += kPT) {    // the usable columns, in design order
+    const int j = j0 + t;
+    int cj = 0;
+    double s = 0.0;
+    bool ok = false;
+    if (j < d) {
+      design(j, cj, s);
+      ok = s > 0.0 && s * s * a.C[(int64_t)cj * ldc + cj] > 0.0;
+    }
+    const unsigned long long mk = __ballot(ok);
+    if (lane == 0) cnt[wv] = __builtin_popcountll(mk);
     __syncthreads();
+    int x = at + __builtin_popcountll(mk & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int w = 0; w < kPW; ++w) {
+      x += w < wv ? cnt[w] : 0;
+      at += cnt[w];
+    }
+    if (ok) {
+      const double c = s * a.C[(int64_t)cj * ldc + pos];
+      sc[x] = s;
+      bc[x] = c;
+      col[x] = cj;
+      des[x] = j;
+      first.take(-fabs(c), j, x);
+    }
+    __syncthreads();
+  }
+  wg_min2(first, none, rg, rj);
+  const double C0 = first.j == kNone ? 0.0 : -first.g;
+  const double T = (double)a.T, lnT = log(T);
+  const double yy = a.C[pos * ldc + pos];
+  double best_bic = T * log(yy / T), rss = yy, Cc = C0;
+  int best_knot = 0, best_df = 0, steps = 0;
+  const int64_t cap = a.cap > 0 ? a.cap : 8 * (int64_t)uni((int)nkeep);
+
+  // inactive slot e leaves the list: the ones before it move up by one.  Every thread must be
+  // done with slot e before the call; ends with a barrier.
+  auto drop_inactive = [&](int e) {
+    for (int hi = e - 1; hi >= ib; hi -= kPT) {
+      const int x = hi - t;
+      double v0 = 0.0, v1 = 0.0;
+      int w0 = 0, w1 = 0;
+      if (x >= ib) {
+        v0 = sc[x];
+        v1 = bc[x];
+        w0 = col[x];
+        w1 = des[x];
+      }
+      __syncthreads();
+      if (x >= ib) {
+        sc[x + 1] = v0;
+        bc[x + 1] = v1;
+        col[x + 1] = w0;
+        des[x + 1] = w1;
+      }
+    }
+    ++ib;
+    __syncthreads();
+  };
+
+  if (C0 > 0.0) {
+    const int e = uni(first.slot), c1 = col[e], j1 = des[e];
+    const double s1 = sc[e], sg = bc[e] >= 0.0 ? 1.0 : -1.0;
+    const double g1 = s1 * s1 * a.C[(int64_t)c1 * ldc + c1];
+    __syncthreads();
+    drop_inactive(e);
+    if (t < kWave) Li[t] = t == 0 ? 1.0 / sqrt(g1) : 0.0;
     if (t == 0) {
-      const int cj = idx[j0];
-      Gi[0] = 1.0 / (sc[j0] * sc[j0] * a.C[(int64_t)cj * ldc + cj]);
-      act[0] = j0;
-      ac[0] = cj;
-      sv[0] = c[j0] >= 0.0 ? 1.0 : -1.0;
-      qv[0] = sv[0] * Gi[0];
-      state[j0] = 1;
+      sc[0] = s1;
+      bc[0] = 0.0;
+      qa[0] = sg / g1;
+      sv[0] = sg;
+      col[0] = c1;
+      des[0] = j1;
     }
     nA = 1;
     __syncthreads();
   }
 
-  // The inverse of the active Gram is Gi + sum_{q < nU} U_q wq[q] U_q^T: the rank-one parts of
-  // the last nU borderings are kept as columns of U (zero in the rows of slots added after
-  // them) and applied to Gi every kPruneDefer borderings, or before a column leaves.
-  int nU = 0;
   while (nA > 0 && steps < cap) {
-    // A_A = (s^T q)^(-1/2), direction dd = A_A q
-    double part = 0.0;
-    for (int r = t; r < nA; r += kPT) part += sv[r] * qv[r];
-    const double AA = 1.0 / sqrt(wg_sum(part, red));
-    for (int r = t; r < nA; r += kPT) {
-      const double w = AA * qv[r];
-      dd[r] = w;
-      bv[r] = sc[act[r]] * w;
-    }
+    // A_A = (s^T q)^(-1/2), direction A_A q
+    double sq = 0.0;
+    for (int r = t; r < nA; r += kPT) sq += sv[r] * qa[r];
+    const double AA = 1.0 / sqrt(wg_sum(sq, red));
+    for (int r = t; r < nA; r += kPT) bv[r] = sc[r] * (AA * qa[r]);
     __syncthreads();
-    // a = Z~^T u for the inactive columns, and the first of them to reach the active
-    // correlation (gamma^)
+    // a = Z~^T u for the inactive columns, the first of them to reach the active correlation
+    // (gamma^), and the first active coefficient to change sign (gamma~)
     const double full = Cc / AA, tol = kGammaRel * full;
-    double gh = INFINITY;
-    int jh = kNone;
-    for (int64_t j = t; j < d; j += kPT) {
-      if (state[j] != 0) continue;
-      const double aj = sc[j] * gather_dot(a.C + idx[j], ldc, ac, bv, nA), cj = c[j];
-      av[j] = aj;
-      double den = AA - aj;
-      if (den != 0.0) {
-        const double g = (Cc - cj) / den;
-        if (isfinite(g) && g > tol) take_min(gh, jh, g, (int)j);
+    Cand hat, til;
+    const int nI = d - ib;
+    for (int p0 = 0; p0 < nI; p0 += panel) {
+      const int np = min(panel, nI - p0);
+      if (p0 > 0) __syncthreads();
+      bool rows = false;
+      if constexpr (NC > 0) {
+        rows = nA > nI;
+        if (rows) {
+          for (int j = t; j < 64 * ((d + 63) / 64); j += kPT) gn[j] = 0.0;
+          __syncthreads();
+          for (int r = t; r < nA; r += kPT) gn[des[r]] = bv[r];
+          __syncthreads();
+          inactive_rows<2, NC>(a.C, ldc, d, (int)pos, (int)(m - pos), gn, np, col + ib, part);
+        }
       }
-      den = AA + aj;
-      if (den != 0.0) {
-        const double g = (Cc + cj) / den;
-        if (isfinite(g) && g > tol) take_min(gh, jh, g, (int)j);
+      if (!rows)
+        inactive_dots<16>(a.C, ldc, nA, col, bv, np, col + ib + p0,
+                                                     part);
+      __syncthreads();
+      for (int e = t; e < np; e += kPT) {
+        double s = part[e];
+        if (!rows) {
+#pragma unroll
+          for (int q = 1; q < kPW; ++q) s += part[q * np + e];
+        }
+        const int x = ib + p0 + e;
+        const double aj = sc[x] * s, cj = bc[x];
+        const int j = des[x];
+        qa[x] = aj;
+        double den = AA - aj;
+        if (den != 0.0) {
+          const double g = (Cc - cj) / den;
+          if (isfinite(g) && g > tol) hat.take(g, j, x);
+        }
+        den = AA + aj;
+        if (den != 0.0) {
+          const double g = (Cc + cj) / den;
+          if (isfinite(g) && g > tol) hat.take(g, j, x);
+        }
       }
     }
-    wg_argmin(gh, jh, rg, rj);
-    jh = uni(jh);
-    // first active coefficient to change sign (gamma~)
-    double gt = INFINITY;
-    int lt = kNone;
     for (int r = t; r < nA; r += kPT) {
-      const int l = act[r];
-      if (beta[l] != 0.0 && dd[r] != 0.0) {
-        const double g = -beta[l] / dd[r];
-        if (g > tol) take_min(gt, lt, g, l);
+      const double dd = AA * qa[r];
+      if (bc[r] != 0.0 && dd != 0.0) {
+        const double g = -bc[r] / dd;
+        if (g > tol) til.take(g, des[r], r);
       }
     }
-    wg_argmin(gt, lt, rg, rj);
-    lt = uni(lt);
-    if (jh == kNone) gh = full;
-    int event;
-    double gamma;
-    if (gt < gh) {
-      event = -1;
-      gamma = gt;
-    } else if (jh != kNone) {
-      event = 1;
-      gamma = gh;
-    } else {
-      event = 0;
-      gamma = full;
+    wg_min2(hat, til, rg, rj);
+    const bool any = uni(hat.j) != kNone;
+    const double gh = any ? hat.g : full;
+    const int event = uni(til.g < gh ? -1 : any ? 1 : 0);
+    const double gamma = event < 0 ? til.g : gh;
+    const int r0 = event < 0 ? uni(til.slot) : -1;   // the leaving slot
+    // move along the direction; df = nonzero coefficients of the columns that stay
+    int nz = 0;
+    for (int rb = 0; rb < nA; rb += kPT) {
+      const int r = rb + t;
+      bool on = false;
+      if (r < nA) {
+        const double b = bc[r] + gamma * (AA * qa[r]);
+        bc[r] = b;
+        on = b != 0.0 && r != r0;
+      }
+      nz += __builtin_popcountll(__ballot(on));
     }
-    event = uni(event);
-    // move along the direction
-    for (int r = t; r < nA; r += kPT) beta[act[r]] += gamma * dd[r];
-    for (int64_t j = t; j < d; j += kPT)
-      if (state[j] == 0) c[j] -= gamma * av[j];
+    for (int x = ib + t; x < d; x += kPT) bc[x] -= gamma * qa[x];
+    rss -= gamma * (2.0 * full - gamma);
     Cc -= gamma * AA;
-    for (int r = t; r < nA; r += kPT) c[act[r]] = sv[r] * Cc;
+    if (lane == 0) cnt[wv] = nz;
     __syncthreads();
+    int df = 0;
+#pragma unroll
+    for (int w = 0; w < kPW; ++w) df += cnt[w];
 
-    if (event == -1) {
-      if (nU > 0) {
-        flush_deferred(Gi, dA, U, d, wq, nU, nA, us);
-        nU = 0;
-      }
-      // slot of the leaving column; swap it with the last slot, then take the Schur complement
-      for (int r = t; r < nA; r += kPT)
-        if (act[r] == lt) slot = r;
+    if (event < 0) {
+      const double s0 = sc[r0], g0 = sv[r0] * Cc;
+      const int c0 = col[r0], j0 = des[r0];
       __syncthreads();
-      const int r0 = uni(slot), L = nA - 1;
-      if (r0 != L) {
-        for (int x = t; x < nA; x += kPT) {  // rows
-          const double u = Gi[(int64_t)x * dA + r0];
-          Gi[(int64_t)x * dA + r0] = Gi[(int64_t)x * dA + L];
-          Gi[(int64_t)x * dA + L] = u;
+      li_remove(Li, nA, r0, more, more + D, more + 2 * D, more + 3 * D);
+      for (int lo = r0 + 1; lo < nA; lo += kPT) {
+        const int x = lo + t;
+        double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+        int w0 = 0, w1 = 0;
+        if (x < nA) {
+          v0 = sc[x];
+          v1 = bc[x];
+          v2 = sv[x];
+          w0 = col[x];
+          w1 = des[x];
         }
         __syncthreads();
-        for (int x = t; x < nA; x += kPT) {  // columns
-          const double u = Gi[(int64_t)r0 * dA + x];
-          Gi[(int64_t)r0 * dA + x] = Gi[(int64_t)L * dA + x];
-          Gi[(int64_t)L * dA + x] = u;
+        if (x < nA) {
+          sc[x - 1] = v0;
+          bc[x - 1] = v1;
+          sv[x - 1] = v2;
+          col[x - 1] = w0;
+          des[x - 1] = w1;
         }
         __syncthreads();
-        if (t == 0) {
-          const int ta = act[r0], tc = ac[r0];
-          const double ts = sv[r0];
-          act[r0] = act[L];
-          ac[r0] = ac[L];
-          sv[r0] = sv[L];
-          act[L] = ta;
-          ac[L] = tc;
-          sv[L] = ts;
-        }
       }
-      __syncthreads();
-      // row L of the inverse over the pivot, then Gi(x, y) -= Gi(x, L) Gi(L, y) / Gi(L, L)
-      const double piv = Gi[(int64_t)L * dA + L];
-      for (int y = t; y < L; y += kPT) dd[y] = Gi[(int64_t)y * dA + L] / piv;
-      __syncthreads();
-      for (int x = t; x < L; x += kPT) row_axpy(Gi, dA, x, -Gi[(int64_t)L * dA + x], dd, L);
+      --nA;
+      --ib;
       if (t == 0) {
-        beta[lt] = 0.0;
-        state[lt] = 0;
+        sc[ib] = s0;
+        bc[ib] = g0;
+        col[ib] = c0;
+        des[ib] = j0;
       }
-      nA = L;
+      for (int r = t; r < (NC > 0 ? 64 * ((nA + 63) / 64) : nA); r += kPT)
+        bv[r] = r < nA ? sv[r] : 0.0;
       __syncthreads();
-      for (int r = t; r < nA; r += kPT) qv[r] = col_dot(Gi, dA, r, sv, nA);
+      apply_inverse<NC>(Li, nA, bv, qa, more + 4 * (NC > 0 ? 0 : D), part, red);
+    } else if (event > 0) {
+      // border the factor with the joining column (or exclude it when collinear)
+      const int e = uni(hat.slot), ck = col[e], jk = des[e];
+      const double sk = sc[e], sgn = bc[e] >= 0.0 ? 1.0 : -1.0;
+      const double* Ck = a.C + (int64_t)ck * ldc;     // C is symmetric
+      const double gkk = sk * sk * Ck[ck];
+      for (int r = t; r < (NC > 0 ? 64 * ((nA + 63) / 64) : nA); r += kPT)
+        bv[r] = r < nA ? sc[r] * sk * Ck[col[r]] : 0.0;
       __syncthreads();
-    } else if (event == 1) {
-      // border the inverse with the joining column k (or exclude it when collinear)
-      const int k = jh, ck = idx[k];
-      const double sk = sc[k];
-      for (int r = t; r < nA; r += kPT) bv[r] = sc[act[r]] * sk * a.C[(int64_t)ac[r] * ldc + ck];
-      __syncthreads();
-      // g = G_A^{-1} b = Gi b + sum_q U_q wq[q] (U_q^T b): one read of Gi
-      double tv[kPruneDefer];
-#pragma unroll
-      for (int q = 0; q < kPruneDefer; ++q) tv[q] = 0.0;
-      for (int r = t; r < nA; r += kPT) {
-        const double br = bv[r];
-#pragma unroll
-        for (int q = 0; q < kPruneDefer; ++q)
-          if (q < nU) tv[q] += U[(int64_t)q * d + r] * br;
-      }
-      wg_sum_vec(tv, redv);
-#pragma unroll
-      for (int q = 0; q < kPruneDefer; ++q) tv[q] = q < nU ? tv[q] * wq[q] : 0.0;
-      double bg = 0.0;
-      for (int r = t; r < nA; r += kPT) {
-        double g = col_dot(Gi, dA, r, bv, nA);
-#pragma unroll
-        for (int q = 0; q < kPruneDefer; ++q)
-          if (q < nU) g += U[(int64_t)q * d + r] * tv[q];
-        gn[r] = g;
-        bg += bv[r] * g;
-      }
-      const double gkk = sk * sk * a.C[(int64_t)ck * ldc + ck];
-      const double delta = gkk - wg_sum(bg, red);
+      const double delta =
+          gkk - apply_inverse<NC>(Li, nA, bv, gn, more + 4 * (NC > 0 ? 0 : D), part, red);
       if (delta <= kCollinearRel * gkk) {
-        if (t == 0) state[k] = 2;
+        drop_inactive(e);
       } else {
-        // border: G'^{-1} = [[Gi + g g^T / delta, -g / delta], [-g^T / delta, 1 / delta]]
-        // (the g g^T / delta term deferred); q' = [q + g (g^T s - s_k) / delta,
-        // (s_k - g^T s) / delta]
-        const double rd = 1.0 / delta;
-        const double sk1 = c[k] >= 0.0 ? 1.0 : -1.0;
+        // g = G_A^{-1} b: the new row of Li is [-g, 1] / sqrt(delta), and
+        // q' = [q + g (g^T s - s_k) / delta, (s_k - g^T s) / delta]
+        const double rd = 1.0 / delta, rs = 1.0 / sqrt(delta);
         double gp = 0.0;
         for (int x = t; x < nA; x += kPT) gp += gn[x] * sv[x];
         const double gs = wg_sum(gp, red);
-        for (int x = t; x < nA; x += kPT) {
-          Gi[(int64_t)nA * dA + x] = -gn[x] * rd;
-          Gi[(int64_t)x * dA + nA] = -gn[x] * rd;
-          qv[x] += gn[x] * ((gs - sk1) * rd);
-          U[(int64_t)nU * d + x] = gn[x];
-        }
+        double* row = Li + li_row(nA);
+        for (int x = t; x < 64 * (nA / 64 + 1); x += kPT)
+          row[x] = x < nA ? -gn[x] * rs : (x == nA ? rs : 0.0);
+        for (int x = t; x < nA; x += kPT) qa[x] += gn[x] * ((gs - sgn) * rd);
+        drop_inactive(e);
         if (t == 0) {
-          Gi[(int64_t)nA * dA + nA] = rd;
-          act[nA] = k;
-          ac[nA] = ck;
-          sv[nA] = sk1;
-          qv[nA] = (sk1 - gs) * rd;
-          state[k] = 1;
-          for (int q = 0; q <= nU; ++q) U[(int64_t)q * d + nA] = 0.0;
-          wq[nU] = rd;
+          sc[nA] = sk;
+          bc[nA] = 0.0;
+          qa[nA] = (sgn - gs) * rd;
+          sv[nA] = sgn;
+          col[nA] = ck;
+          des[nA] = jk;
         }
-        ++nU;
         ++nA;
-      }
-      __syncthreads();
-      if (nU == kPruneDefer) {
-        flush_deferred(Gi, dA, U, d, wq, nU, nA, us);
-        nU = 0;
+        __syncthreads();
       }
     }
     ++steps;
-    // the knot: RSS from the correlations, df = nonzero coefficients
-    double rp = 0.0, nz = 0.0;
-    for (int r = t; r < nA; r += kPT) {
-      const int l = act[r];
-      rp += beta[l] * (c0[l] + c[l]);
-      nz += beta[l] != 0.0 ? 1.0 : 0.0;
-    }
-    const double rss = yy - wg_sum(rp, red);
-    const int df = (int)wg_sum(nz, red);
     const double bic = T * log(rss / T) + (double)df * lnT;
     if (bic < best_bic) {
       best_bic = bic;
       best_knot = steps;
       best_df = df;
-      for (int64_t j = t; j < d; j += kPT) best[j] = beta[j];
+      for (int r = t; r < nA; r += kPT) best[des[r]] = bc[r];
+      for (int x = ib + t; x < d; x += kPT) best[des[x]] = 0.0;
     }
     __syncthreads();
     if (event == 0 || Cc <= kStopRel * C0) break;
@@ -527,13 +762,16 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
   double* rowB0 = a.B0o + (int64_t)i * m;
   for (int64_t v = t; v < m; v += kPT) rowB0[v] = 0.0;
   __syncthreads();
-  for (int64_t j = t; j < d; j += kPT) {
-    const double v = best[j] * sc[j];
+  for (int j = t; j < d; j += kPT) {
+    int cj;
+    double s;
+    design(j, cj, s);
+    const double v = best[j] * s;
     if (j < pos) {
-      rowB0[idx[j]] = v;
+      rowB0[min(max(a.order[j], 0), (int)m - 1)] = v;
     } else {
-      const int64_t jj = j - pos, tau = jj / m + 1, k = jj % m;
-      a.Blo[(tau - 1) * m * m + (int64_t)i * m + k] = v;
+      const int64_t jj = j - pos;
+      a.Blo[jj / m * m * m + (int64_t)i * m + jj % m] = v;
     }
   }
   if (a.info && t == 0) {
@@ -541,6 +779,25 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
     a.info[3 * i + 1] = best_knot;
     a.info[3 * i + 2] = best_df;
   }
+}
+
+// LDS of the state vectors of a design of d columns: six FP64 vectors, the wave partials and two
+// int32 vectors; the budget is a CU's 160 KiB
+// less the kernel's static arrays.
+constexpr size_t kPruneLds = 156 * 1024;
+size_t prune_lds_bytes(int64_t d) {
+  return (size_t)round_up(d, 64) * ((6 + kPW) * sizeof(double) + 2 * sizeof(int));
+}
+
+template <int NC>
+int launch_prune(const PruneArgs& a, hipStream_t stream) {
+  const size_t lds = NC > 0 ? prune_lds_bytes(a.dmax) : (size_t)kPW * kPanel * sizeof(double);
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&prune_lars_kernel<NC>),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+    return VL_ERR_HIP;
+  prune_lars_kernel<NC><<<(unsigned)a.m, kPT, lds, stream>>>(a);
+  VL_LAUNCH_CHECK();
+  return VL_OK;
 }
 
 }  // namespace
@@ -565,7 +822,7 @@ int run_prune(int64_t n, int64_t m, int p, const PruneWs& w, const float* X, int
               double* B0_out, double* Blag_out, int32_t* info, int32_t* st, hipStream_t stream) {
   ProfileScope ps("prune", stream);
   const int64_t nc = m * (p + 1);
-  int rc = lag_covariance(n, m, p, X, ldx, w.colmap, w.mu, w.C, w.scratch, st, stream);
+  int rc = lag_covariance(n, m, p, X, ldx, order, w.colmap, w.mu, w.C, w.scratch, st, stream);
   if (rc) return rc;
   prune_check_order_kernel<<<1, 256, 0, stream>>>(order, m, st);
   VL_LAUNCH_CHECK();
@@ -584,9 +841,16 @@ int run_prune(int64_t n, int64_t m, int p, const PruneWs& w, const float* X, int
   a.Blo = Blag_out;
   a.info = info;
   a.st = st;
-  prune_lars_kernel<<<(unsigned)m, kPT, 0, stream>>>(a);
-  VL_LAUNCH_CHECK();
-  return VL_OK;
+  // Rows of Li and C in registers and the state in LDS while both hold the longest design, by
+  // register need; beyond that the general form.
+  const int64_t d = m - 1 + m * p;
+  a.dmax = (int)d;
+  if (prune_lds_bytes(d) <= kPruneLds) {
+    if (d <= 64 * 6) return launch_prune<6>(a, stream);
+    if (d <= 64 * 10) return launch_prune<10>(a, stream);
+    if (d <= 64 * 20) return launch_prune<20>(a, stream);
+  }
+  return launch_prune<0>(a, stream);
 }
 
 }  // namespace vl

@@ -16,15 +16,17 @@ struct PruneWs {
 __host__ __device__ inline int64_t prune_active_cap(int64_t d, int64_t cap) {
   return cap > 0 && cap + 1 < d ? cap + 1 : d;
 }
-// Rank-one updates of the inverse of the active Gram kept aside and applied together.
-constexpr int kPruneDefer = 8;
+// Doubles of the packed lower-triangular inverse factor of n active columns (blocks of 64 rows,
+// padded to whole 64-wide pieces).
+__host__ __device__ inline int64_t prune_li_doubles(int64_t n) {
+  const int64_t k = ceil_div(n, 64);
+  return 2048 * k * (k + 1);
+}
 
-// Doubles of the region of a variable with d design columns: the inverse of the active Gram
-// (capacity^2), eleven FP64 vectors of d, the kPruneDefer deferred columns of d and four int32
-// vectors of d.
+// Doubles of the region of a variable with d design columns: the inverse factor, the best knot's
+// coefficients, and (designs too long for LDS) eleven FP64 vectors and two int32 vectors of d.
 __host__ __device__ inline int64_t prune_region_doubles(int64_t d, int64_t cap) {
-  const int64_t a = prune_active_cap(d, cap);
-  return round_up(a * a + (13 + kPruneDefer) * d, 32);
+  return round_up(prune_li_doubles(prune_active_cap(d, cap)) + 13 * d, 32);
 }
 
 size_t prune_ws_bytes(int64_t n, int64_t m, int p, int64_t cap, void* base, PruneWs* out);

@@ -31,11 +31,15 @@ namespace vl {
 constexpr int kBf16RefineSteps = 3;
 
 
-// colmap[tau*m + i] = (p - tau) * ldx + i  for tau = 0..p  (tau = 0 is Y, tau >= 1 is Z)
-__global__ void lag_colmap_kernel(int64_t m, int p, int64_t ldx, int64_t* __restrict__ colmap) {
+// colmap[tau*m + i] = (p - tau) * ldx + i  for tau = 0..p  (tau = 0 is Y, tau >= 1 is Z); with an
+// order, lag 0 holds the variables in that order (clamped: a caller's check reports bad entries)
+__global__ void lag_colmap_kernel(int64_t m, int p, int64_t ldx, int64_t* __restrict__ colmap,
+                                  const int32_t* __restrict__ order = nullptr) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= m * (p + 1)) return;
-  const int64_t tau = c / m, i = c % m;
+  const int64_t tau = c / m;
+  int64_t i = c % m;
+  if (order && tau == 0) i = min(max(order[i], 0), (int)m - 1);
   colmap[c] = (p - tau) * ldx + i;
 }
 
@@ -374,10 +378,11 @@ size_t lag_cov_scratch_doubles(int64_t n, int64_t m, int p) {
   return s1 > s2 ? s1 : s2;
 }
 
-int lag_covariance(int64_t n, int64_t m, int p, const float* X, int64_t ldx, int64_t* colmap,
-                   double* mu, double* C, double* scratch, int32_t* st, hipStream_t stream) {
+int lag_covariance(int64_t n, int64_t m, int p, const float* X, int64_t ldx,
+                   const int32_t* order, int64_t* colmap, double* mu, double* C, double* scratch,
+                   int32_t* st, hipStream_t stream) {
   const int64_t nc = m * (p + 1), n_eff = n - p;
-  lag_colmap_kernel<<<(unsigned)ceil_div(nc, 256), 256, 0, stream>>>(m, p, ldx, colmap);
+  lag_colmap_kernel<<<(unsigned)ceil_div(nc, 256), 256, 0, stream>>>(m, p, ldx, colmap, order);
   VL_LAUNCH_CHECK();
   int rc = colmeans(X, ldx, colmap, nc, n_eff, mu, scratch, st, stream);
   if (rc) return rc;

@@ -222,3 +222,40 @@ def test_prune_largest_design_step_limit(api):
     want = P.prune(X32.astype(np.float64), p, order, B0, Bl, max_steps=10,
                    positions=[0, m - 1])
     _compare(got, want)
+
+
+# Designs whose active sets cross the 64-wide pieces of the inverse factor (d = 64, 65, 127, 128,
+# 129), the register classes (d <= 384, 640, 1280) and the general form beyond them.
+EDGES = [(64, 1, 900, 0, [0, 1, 63]), (65, 1, 900, 0, [62, 63, 64]), (193, 1, 1200, 0, [191, 192]),
+         (330, 1, 1500, 40, [0, 310, 329]), (645, 1, 1700, 40, [0, 635, 636, 644])]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=lambda c: f"m{c[0]}_p{c[1]}_steps{c[3]}")
+def test_prune_design_sizes_at_the_edges(api, case):
+    m, p, n, cap, positions = case
+    print(f"prune edges m={m} p={p} n={n} steps {cap}", flush=True)
+    inst = synth.make_custom(m, n, p, "laplace", 7, edge_prob=4.0 / m, w_lo=0.1, w_hi=0.5)
+    X64 = inst.X32.astype(np.float64)
+    M, _, E = O.fit_var(X64, p)
+    order = inst.perm
+    B0, Bl = O.estimate_B(E, order, M)
+    want = P.prune(X64, p, order, B0, Bl, max_steps=cap, positions=positions)
+    _compare(_run(api, inst.X32, p, order, B0, Bl, cap), want)
+
+
+def test_prune_long_path_with_leaving_columns(api):
+    """Columns leaving an active set of more than 64 (the rotations of the inverse factor then
+    cross its blocks of rows)."""
+    inst = synth.make_custom(70, 320, 1, "laplace", 3, edge_prob=0.5, w_lo=0.3, w_hi=0.6)
+    X64 = inst.X32.astype(np.float64)
+    M, _, E = O.fit_var(X64, 1)
+    B0, Bl = O.estimate_B(E, inst.perm, M)
+    want = P.prune(X64, 1, inst.perm, B0, Bl, positions=[67, 68, 69])
+    wide = 0
+    for oi in want["info"]:
+        active = 1
+        for e, _ in oi["events"]:
+            wide += e == -1 and active > 64
+            active += e
+    assert wide >= 5
+    _compare(_run(api, inst.X32, 1, inst.perm, B0, Bl), want)
