@@ -59,6 +59,28 @@ def test_var_simulate_matches_oracle(api, case):
     print(f"  max rel err {err:.1e}", flush=True)
 
 
+# Sizes at the edges of the recursion kernels' tiles (16 variables a task, 64 a group, one or two
+# tasks a wave, past them the kernels without row broadcasts) and of the 8-step blocks of draws.
+@pytest.mark.parametrize("case", [(1, 1, 9), (16, 1, 8), (17, 2, 7), (64, 1, 17), (65, 1, 16),
+                                  (100, 2, 50), (128, 2, 15), (160, 1, 33), (161, 1, 12),
+                                  (33, 5, 40), (10, 12, 25), (5, 17, 24)],
+                         ids=lambda c: f"m{c[0]}_p{c[1]}_T{c[2]}")
+def test_var_simulate_tile_edges(api, case):
+    m, p, T = case
+    print(f"simulate edges m={m} p={p} T={T}", flush=True)
+    rng = np.random.default_rng(100 * m + p)
+    M = rng.normal(0.0, 0.5 / np.sqrt(m * p), (p, m, m))
+    c = rng.normal(0.0, 0.3, m)
+    X0 = rng.normal(0.0, 1.0, (p, m)).astype(np.float32)
+    E32 = rng.laplace(0.0, 1.0, (40, m)).astype(np.float32)
+    idx = rng.integers(0, 40, size=(3, T)).astype(np.int32)
+    got = api.var_simulate(_dev(M), _dev(c), _dev(X0), _dev(E32), _dev(idx)).cpu().numpy()
+    for r in range(3):
+        ref = EN.simulate_var(M, c, X0.astype(np.float64), E32.astype(np.float64), idx[r])
+        assert np.array_equal(got[r][:p], X0)
+        assert np.abs(got[r] - ref).max() / np.abs(ref).max() <= 1e-5, r
+
+
 def test_var_simulate_identity_draws_full_size(api):
     """m = 400, n = 10000, p = 2: drawing the GPU fit's residuals in their own order
     regenerates the series (a property that holds at any size)."""
