@@ -85,12 +85,70 @@ __device__ inline int64_t uni(int64_t v) {
 }
 template <class T>
 __device__ inline T* uni(T* p) {
-  return reinterpret_cast<T*>(uni(reinterpret_cast<int64_t>(p)));
+  typedef __attribute__((address_space(1))) T* global_ptr;
+  return (T*)(global_ptr)(uintptr_t)uni((int64_t)(uintptr_t)p);
+}
+
+// A block's copy of a problem's descriptor: every field in scalar registers, and every pointer
+// known to be to global memory.  A pointer read from memory is generic to the compiler, which
+// then uses flat loads and stores (they wait for LDS and memory alike: the FP64 Gram
+// tiles took 6.0 ms that way at 256 problems, 1.8 ms with global loads).  Fields a
+// kernel does not use cost nothing.
+__device__ __forceinline__ BInst block_inst(const BInst* __restrict__ p) {
+  BInst r;
+  r.X = uni(p->X);
+  r.n = uni(p->n);
+  r.m = uni(p->m);
+  r.ldx = uni(p->ldx);
+  r.n_eff = uni(p->n_eff);
+  r.dz = uni(p->dz);
+  r.nc = uni(p->nc);
+  r.p = (int)uni(p->p);
+  r.fp32 = (int)uni(p->fp32);
+  r.M = uni(p->M);
+  r.intercept = uni(p->intercept);
+  r.E = uni(p->E);
+  r.lde = uni(p->lde);
+  r.S = uni(p->S);
+  r.order = uni(p->order);
+  r.margin = uni(p->margin);
+  r.B0 = uni(p->B0);
+  r.Blag = uni(p->Blag);
+  r.nt = (int)uni(p->nt);
+  r.nchunk = (int)uni(p->nchunk);
+  r.chunk_len = (int)uni(p->chunk_len);
+  r.pad = 0;
+  r.m_pad = uni(p->m_pad);
+  r.tiles = uni(p->tiles);
+  r.n_pad = uni(p->n_pad);
+  r.items = uni(p->items);
+  r.colmap = uni(p->colmap);
+  r.mu = uni(p->mu);
+  r.G = uni(p->G);
+  r.Coef = uni(p->Coef);
+  r.L = uni(p->L);
+  r.Tmp = uni(p->Tmp);
+  r.chol = uni(p->chol);
+  r.CoefF = uni(p->CoefF);
+  r.emu = uni(p->emu);
+  r.cov = uni(p->cov);
+  r.momx = uni(p->momx);
+  r.Hx = uni(p->Hx);
+  r.Hr = uni(p->Hr);
+  r.Xs = uni(p->Xs);
+  r.coef = uni(p->coef);
+  r.partU = uni(p->partU);
+  r.partB = uni(p->partB);
+  r.clist = uni(p->clist);
+  r.P = uni(p->P);
+  r.Linv = uni(p->Linv);
+  r.bchol = uni(p->bchol);
+  return r;
 }
 
 __device__ inline int bat_locate(const BTables& T, int map, int64_t blk, int64_t& local) {
-  const int b = T.bmap[map][blk];
-  local = blk - T.first[map][b];
+  const int b = __builtin_amdgcn_readfirstlane(T.bmap[map][blk]);
+  local = uni(blk - T.first[map][b]);
   return b;
 }
 
@@ -105,7 +163,7 @@ __global__ void bat_reset_kernel(int32_t* st, int count) {
 __global__ __launch_bounds__(256) void bat_colmeans_kernel(BTables T, int which, int32_t* st0) {
   int64_t lb;
   const int b = bat_locate(T, which ? kMapColE : kMapColVar, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   __shared__ double red[4][64];
   const int cc = threadIdx.x & 63, rg = threadIdx.x >> 6;
   const float* A = which ? d.E : d.X;
@@ -156,7 +214,7 @@ __device__ inline void lower_tile(int64_t k, int64_t& ti, int64_t& tj) {
 }
 
 template <bool kFp64>
-__device__ inline void bat_gram_tile(const float* A, int64_t lda, const int64_t* mapA,
+__device__ __forceinline__ void bat_gram_tile(const float* A, int64_t lda, const int64_t* mapA,
                                      const double* muA, int64_t M, const float* B, int64_t ldb,
                                      const int64_t* mapB, const double* muB, int64_t N,
                                      int64_t i0, int64_t j0, int64_t K, double* C, int64_t ldc,
@@ -171,31 +229,33 @@ __device__ inline void bat_gram_tile(const float* A, int64_t lda, const int64_t*
 }
 
 template <bool kFp64>
-__global__ __launch_bounds__(256) void bat_gram_kernel(BTables T, int which) {
+__global__ __launch_bounds__(256, kFp64 ? 2 : 4) void bat_gram_kernel(BTables T, int which) {
   int64_t lb;
   const int b = bat_locate(T, which ? kMapGramCov : kMapGramVar, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
+  const int64_t m = d.m, n_eff = d.n_eff;
   if (which == 0) {
-    const int64_t tz = ceil_div(d.dz, kGT), tm = ceil_div(d.m, kGT);
-    const int64_t* mapZ = d.colmap + d.m;
-    const double* muZ = d.mu + d.m;
+    const int64_t dz = d.dz, ldx = d.ldx;
+    const float* X = d.X;
+    const int64_t* map = d.colmap;
+    const double* mu = d.mu;
+    const int64_t tz = ceil_div(dz, kGT), tm = ceil_div(m, kGT);
     const int64_t tri = tz * (tz + 1) / 2;
-    if (lb < tri) {
-      int64_t ti, tj;
-      lower_tile(lb, ti, tj);
-      bat_gram_tile<kFp64>(d.X, d.ldx, mapZ, muZ, d.dz, d.X, d.ldx, mapZ, muZ, d.dz, ti * kGT,
-                           tj * kGT, d.n_eff, d.G, d.dz, 1.0, false);
-    } else {
-      const int64_t l2 = lb - tri;
-      bat_gram_tile<kFp64>(d.X, d.ldx, mapZ, muZ, d.dz, d.X, d.ldx, d.colmap, d.mu, d.m,
-                           (l2 / tm) * kGT, (l2 % tm) * kGT, d.n_eff, d.Tmp, d.m, 1.0, false);
-    }
+    const bool g = lb < tri;                       // a tile of G, else of R
+    int64_t ti, tj;
+    lower_tile(lb, ti, tj);
+    const int64_t i0 = (g ? ti : (lb - tri) / tm) * kGT, j0 = (g ? tj : (lb - tri) % tm) * kGT;
+    bat_gram_tile<kFp64>(X, ldx, map + m, mu + m, dz, X, ldx, g ? map + m : map,
+                         g ? mu + m : mu, g ? dz : m, uni(i0), uni(j0), n_eff,
+                         g ? d.G : d.Tmp, g ? dz : m, 1.0, false);
   } else {
     int64_t ti, tj;
     lower_tile(lb, ti, tj);
-    bat_gram_tile<kFp64>(d.E, d.lde, nullptr, d.emu, d.m, d.E, d.lde, nullptr, d.emu, d.m,
-                         ti * kGT, tj * kGT, d.n_eff, d.cov, d.m, 1.0 / (double)d.n_eff,
-                         ti != tj);
+    const float* E = d.E;
+    const int64_t lde = d.lde;
+    const double* mu = d.emu;
+    bat_gram_tile<kFp64>(E, lde, nullptr, mu, m, E, lde, nullptr, mu, m, uni(ti * kGT),
+                         uni(tj * kGT), n_eff, d.cov, m, 1.0 / (double)n_eff, ti != tj);
   }
 }
 
@@ -224,7 +284,7 @@ __device__ inline CholArgs bat_chol_args(const BInst& d, int which, int32_t* st)
 // One workgroup per problem: L^{-1} set to the identity and the first diagonal block factored.
 __global__ __launch_bounds__(256) void bat_chol_prologue_kernel(const BInst* __restrict__ I,
                                                                 int which, int32_t* st0) {
-  const CholArgs a = bat_chol_args(I[blockIdx.x], which, st0 + blockIdx.x);
+  const CholArgs a = bat_chol_args(block_inst(I + blockIdx.x), which, st0 + blockIdx.x);
   for (int64_t e = threadIdx.x; e < a.n * a.n; e += 256) chol_linv_init(a, e);
   chol_prologue_block(a);
 }
@@ -234,7 +294,7 @@ __global__ __launch_bounds__(256) void bat_chol_step_kernel(BTables T, int which
                                                             int32_t* st0) {
   int64_t lb;
   const int b = bat_locate(T, (which ? kMapBChol0 : kMapVarChol0) + k, blockIdx.x, lb);
-  const CholArgs a = bat_chol_args(T.inst[b], which, st0 + b);
+  const CholArgs a = bat_chol_args(block_inst(T.inst + b), which, st0 + b);
   chol_step_item(a, k, lb);
 }
 
@@ -242,7 +302,7 @@ __global__ __launch_bounds__(256) void bat_chol_step_kernel(BTables T, int which
 __global__ __launch_bounds__(256) void bat_back_kernel(BTables T) {
   int64_t lb;
   const int b = bat_locate(T, kMapVarBack, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   const int64_t tn = ceil_div(d.m, (int64_t)32);
   gemm_f64_block(d.dz, d.m, d.dz, 1.0, d.L, d.dz, 1, d.Tmp, d.m, 0, 0.0, d.Coef, d.m, 0, 2,
                  (lb / tn) * 32, (lb % tn) * 32);
@@ -250,7 +310,7 @@ __global__ __launch_bounds__(256) void bat_back_kernel(BTables T) {
 
 // One workgroup per problem: lag matrices, intercept and (FP32 mode) the FP32 coefficients.
 __global__ __launch_bounds__(256) void bat_var_post_kernel(const BInst* __restrict__ I) {
-  const BInst& d = I[blockIdx.x];
+  const BInst d = block_inst(I + blockIdx.x);
   const int64_t m = d.m, dz = d.dz;
   const int tid = threadIdx.x;
   for (int64_t e = tid; e < (int64_t)d.p * m * m; e += 256) {
@@ -270,7 +330,7 @@ template <bool kFp64>
 __global__ __launch_bounds__(256) void bat_var_residual_kernel(BTables T) {
   int64_t lb;
   const int b = bat_locate(T, kMapResid, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   const int64_t tm = ceil_div(d.m, 64);
   const int64_t t0 = (lb / tm) * 64, j0 = (lb % tm) * 64;
   if (kFp64)
@@ -284,7 +344,7 @@ __global__ __launch_bounds__(256) void bat_var_residual_kernel(BTables T) {
 __global__ __launch_bounds__(256) void bat_standardize_kernel(BTables T, int32_t* st0) {
   int64_t lb;
   const int b = bat_locate(T, kMapStd, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   const int64_t gx = ceil_div(d.n_pad, 64);
   standardize_tile(d.E, d.lde, d.n_eff, d.m, d.emu, d.cov, d.Xs, d.n_pad, d.m_pad, st0 + b,
                    (lb % gx) * 64, (lb / gx) * 64, d.clist, d.tiles + 1, lb,
@@ -295,7 +355,7 @@ __global__ __launch_bounds__(256) void bat_standardize_kernel(BTables T, int32_t
 __global__ __launch_bounds__(256) void bat_prep_kernel(BTables T, int32_t* st0) {
   int64_t lb;
   const int b = bat_locate(T, kMapPrep, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   if (lb < d.m)
     hx_block<256>(d.Xs, d.n_pad, d.n_eff, d.Hx, d.momx, lb);
   else
@@ -310,19 +370,18 @@ __global__ __launch_bounds__(256) void bat_moments_kernel(BTables T, int64_t tot
   if (g >= total) return;
   int64_t lb;
   const int b = bat_locate(T, kMapMom, g, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t item = uni(lb) * 4 + wave;
-  if (item >= uni(d.items)) return;
-  pairwise_moments_item(uni(d.Xs), uni(d.n_pad), uni(d.coef), uni(d.m_pad), uni(d.m),
-                        (int)uni(d.nt), uni(d.tiles), (int)uni(d.chunk_len), item,
-                        uni(d.partU), uni(d.partB));
+  const int64_t item = lb * 4 + wave;
+  if (item >= d.items) return;
+  pairwise_moments_item(d.Xs, d.n_pad, d.coef, d.m_pad, d.m, d.nt, d.tiles, d.chunk_len, item,
+                        d.partU, d.partB);
 }
 
 // The listed near-collinear tiles of problem blockIdx.x, recomputed after the moment kernel
 // (one workgroup per problem, grid-stride over its list).
 __global__ __launch_bounds__(256) void bat_collinear_kernel(const BInst* __restrict__ I) {
-  const BInst& d = I[blockIdx.x];
+  const BInst d = block_inst(I + blockIdx.x);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t total = (int64_t)d.clist[d.tiles] * d.nchunk;
   for (int64_t w = wave; w < total; w += 4) {
@@ -337,7 +396,7 @@ __global__ __launch_bounds__(256) void bat_collinear_kernel(const BInst* __restr
 __global__ __launch_bounds__(256) void bat_combine_kernel(BTables T) {
   int64_t lb;
   const int b = bat_locate(T, kMapComb, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   const int64_t m = d.m, e = lb * 256 + threadIdx.x;
   if (e >= m * m) return;
   const int64_t i = e / m, j = e % m;
@@ -359,7 +418,7 @@ __global__ __launch_bounds__(256) void bat_combine_kernel(BTables T) {
 // (with the permutation check).
 __global__ __launch_bounds__(256) void bat_order_kernel(const BInst* __restrict__ I,
                                                         int32_t* st0) {
-  const BInst& d = I[blockIdx.x];
+  const BInst d = block_inst(I + blockIdx.x);
   int32_t* st = st0 + blockIdx.x;
   const int64_t m = d.m;
   const int tid = threadIdx.x;
@@ -386,7 +445,7 @@ __global__ __launch_bounds__(256) void bat_order_kernel(const BInst* __restrict_
 
 // One workgroup per problem: B0[K_a][K_b] = -Linv[a][b] / Linv[a][a] for b < a, else 0.
 __global__ __launch_bounds__(256) void bat_b0_kernel(const BInst* __restrict__ I) {
-  const BInst& d = I[blockIdx.x];
+  const BInst d = block_inst(I + blockIdx.x);
   const int64_t m = d.m;
   const int32_t* K = d.order;
   for (int64_t e = threadIdx.x; e < m * m; e += 256) {
@@ -401,7 +460,7 @@ __global__ __launch_bounds__(256) void bat_b0_kernel(const BInst* __restrict__ I
 __global__ __launch_bounds__(256) void bat_blag_kernel(BTables T) {
   int64_t lb;
   const int b = bat_locate(T, kMapBlag, blockIdx.x, lb);
-  const BInst& d = T.inst[b];
+  const BInst d = block_inst(T.inst + b);
   const int64_t m = d.m, tm = ceil_div(m, (int64_t)32);
   const int64_t tau = lb / (tm * tm), rem = lb % (tm * tm);
   const double* Mt = d.M + tau * m * m;

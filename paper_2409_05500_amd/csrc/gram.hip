@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void gram_tn_bf16_kernel(
                  P + (int64_t)blockIdx.z * M * N, N, 1.0);
 }
 
-__global__ __launch_bounds__(256) void gram_tn_f64_kernel(
+__global__ __launch_bounds__(256, 2) void gram_tn_f64_kernel(
     const float* __restrict__ A, int64_t lda, const int64_t* __restrict__ mapA,
     const double* __restrict__ muA, int64_t M, const float* __restrict__ B, int64_t ldb,
     const int64_t* __restrict__ mapB, const double* __restrict__ muB, int64_t N, int64_t K,
@@ -223,7 +223,9 @@ __global__ __launch_bounds__(256) void gram_tn_f64_kernel(
 }
 
 // C[i][j] = sum_t (A(t,i) - muA[i]) B64[t][j] with an FP64 right operand (not centred): the
-// refinement residual Zc^T E64.  Same tiling as gram_tn_f64_kernel.
+// refinement residual Zc^T E64.  64 x 64 tiles of 4 waves of 32 x 32, 32 samples per LDS stage.
+constexpr int kGK64 = 32;
+
 __global__ __launch_bounds__(256) void gram_tn_f64b_kernel(
     const float* __restrict__ A, int64_t lda, const int64_t* __restrict__ mapA,
     const double* __restrict__ muA, int64_t M, const double* __restrict__ B, int64_t ldb,
@@ -342,8 +344,9 @@ int gram_tn(const float* A, int64_t lda, const int64_t* mapA, const double* muA,
             const float* B, int64_t ldb, const int64_t* mapB, const double* muB, int64_t N,
             int64_t K, GramMode mode, double scale, double* C, int64_t ldc, double* scratch,
             hipStream_t stream, bool sym) {
-  const int splits = gram_splits(M, N, K);
+  int splits = mode == GramMode::kFp64 ? gram_splits_f64(M, N, K) : gram_splits(M, N, K);
   const int64_t kchunk = round_up(ceil_div(K, splits), kGK);
+  if (mode == GramMode::kFp64) splits = (int)ceil_div(K, kchunk);   // no empty splits
   const int64_t tm = ceil_div(M, kGT), tn = ceil_div(N, kGT);
   dim3 grid(sym ? (unsigned)(tm * (tm + 1) / 2) : (unsigned)tn, sym ? 1u : (unsigned)tm,
             (unsigned)splits);

@@ -35,6 +35,24 @@ inline int gram_splits(int64_t M, int64_t N, int64_t K) {
   return (int)(s < 1 ? 1 : s);
 }
 
+// Split-K factor of the FP64 Grams.  Two workgroups fit a CU (registers), so 512 run at once: the
+// largest count that fills one round, or two where one would leave over a fifth of it idle; one
+// workgroup more costs a round of its own.  Down to 128 samples a split (two groups of loads
+// per wave).  More splits than gram_splits() only while the partials stay within 8 MB, so that no
+// workspace grows at sizes where it counts.
+inline int gram_splits_f64(int64_t M, int64_t N, int64_t K) {
+  const int64_t old = gram_splits(M, N, K);
+  const int64_t tm = ceil_div(M, 64);
+  const int64_t tiles = M == N ? tm * (tm + 1) / 2 : tm * ceil_div(N, 64);
+  int64_t s = 512 / tiles;
+  if (tiles * s < 410) s = 1024 / tiles;
+  const int64_t smax = K / 128, few = (8 << 20) / (8 * M * N);
+  s = s < 64 ? s : 64;
+  s = s < smax ? s : smax;
+  if (s > old) s = few > old ? (s < few ? s : few) : old;
+  return (int)(s < 1 ? 1 : s);
+}
+
 // Arithmetic of gram_tn():
 //   kFp32        FP32 MFMA, FP32 accumulation over the whole split;
 //   kFp32Flush64 FP32 MFMA partial sums over 128-sample blocks accumulated in FP64;

@@ -187,102 +187,152 @@ __device__ inline void gram_tile_bf16(
 }
 
 // ------------------------------------------------------------------------------------------
-// FP64 variant: same tiling, v_mfma_f64_16x16x4f64.  FP32 inputs are widened when read from
-// LDS, so every product is exact and the sum is FP64 throughout.  Wave tile 32 x 32 = 2 x 2
-// blocks of 16 x 16; 16 samples per LDS stage.
+// FP64 variant: a 64 x 64 tile by v_mfma_f64_16x16x4f64.  FP32 inputs are widened and centred in
+// FP64, so every product is exact and the sum is FP64 throughout.
+// What bounds it: the FP64 matrix rate, ~60 TFLOP/s sustained, to which every vector operation
+// beside a product adds its own issue time (the FP64 matrix and vector units are one).  Hence
+// each of the four waves forms the whole tile over a quarter of the samples, straight from
+// global memory in the operands' own layout (four rows of 16 consecutive values a load): 16
+// products for 8 loads, 8 conversions and 8 subtractions, no LDS and no barrier in the loop, the
+// same work for every wave whatever part of an edge tile is live, and a chain a quarter as long.
+// A step's values are loaded again for the next group as soon as they are converted (16 samples,
+// 64 products, ahead), without a condition: behind a branch the compiler cannot count the
+// loads and waits for all.  The quarters are added through LDS in wave
+// order at the end.  Two waves per SIMD (128 accumulator registers).
+// Measured against the former form (raw values staged in LDS, widened, centred and masked at each
+// use): 1000 x 1000 over 49999 samples (lower tiles) 1.43 -> 0.93 ms (60 TFLOP/s of the tiles),
+// 400 x 2000 over 9996 0.46 -> 0.35 ms, 10 x 10 over 999 22.6 -> 6.3 us; both Grams of the 256
+// uneven problems (m 20-200, n 500-8000) 2.67 -> 1.77 ms, of 181 windows of 50 x 2000 0.38 -> 0.23.
 // ------------------------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGK64 = 32;
+constexpr int kGS64 = 16;    // samples per group of loads
 
-__device__ inline void gram_tile_f64(
+__device__ __forceinline__ void gram_tile_f64(
     const float* __restrict__ A, int64_t lda, const int64_t* __restrict__ mapA,
     const double* __restrict__ muA, int64_t M, const float* __restrict__ B, int64_t ldb,
     const int64_t* __restrict__ mapB, const double* __restrict__ muB, int64_t N, int64_t i0,
     int64_t j0, int64_t kb, int64_t ke, double* __restrict__ out, int64_t ldo, double scale,
     bool mirror = false) {
-  __shared__ float As[kGK64 * kGLd];
-  __shared__ float Bs[kGK64 * kGLd];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cc = tid & 63, rg = tid >> 6;
-  const int64_t ia = i0 + cc, jb = j0 + cc;
-  const bool va = ia < M, vb = jb < N;
-  const float* pa = A + (va ? (mapA ? mapA[ia] : ia) : 0);
-  const float* pb = B + (vb ? (mapB ? mapB[jb] : jb) : 0);
-  const int wi = wave >> 1, wj = wave & 1;
-  // 16 x 16 blocks wholly in the padding (edge tiles) are skipped (wave-uniform tests)
-  const bool live_a[2] = {i0 + wi * 32 < M, i0 + wi * 32 + 16 < M};
-  const bool live_b[2] = {j0 + wj * 32 < N, j0 + wj * 32 + 16 < N};
-  // the means are subtracted after widening (in FP64), per operand column of this lane
-  double mua[2], mub[2];
+  __shared__ double part[4][8][4][64];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // live 16-wide blocks of the tile; columns past the edge read column 0 (their products land in
+  // rows and columns that are not written)
+  const int na = (int)(M - i0 < 64 ? (M - i0 + 15) / 16 : 4);
+  const int nb = (int)(N - j0 < 64 ? (N - j0 + 15) / 16 : 4);
+  const float *pa[4], *pb[4];
+  double ma[4], mb[4];
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const int64_t ii = i0 + wi * 32 + q * 16 + (lane & 15);
-    const int64_t jj = j0 + wj * 32 + q * 16 + (lane & 15);
-    mua[q] = ii < M ? muA[ii] : 0.0;
-    mub[q] = jj < N ? muB[jj] : 0.0;
+  for (int q = 0; q < 4; ++q) {
+    const int64_t ia = i0 + 16 * q + li, jb = j0 + 16 * q + li;
+    pa[q] = A + (ia < M ? (mapA ? mapA[ia] : ia) : 0);
+    pb[q] = B + (jb < N ? (mapB ? mapB[jb] : jb) : 0);
+    ma[q] = ia < M ? muA[ia] : 0.0;
+    mb[q] = jb < N ? muB[jb] : 0.0;
   }
-  f64x4 acc[2][2];
+  f64x4 acc[4][4];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  float ra[kGK64 / 4], rb[kGK64 / 4];
-  auto load = [&](int64_t k0) {
+    for (int b = 0; b < 4; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // this wave's samples: whole groups, but for the last wave that has any
+  const int64_t K = ke - kb, len = K > 0 ? round_up(ceil_div(K, (int64_t)4), kGS64) : 0;
+  const int64_t k0w = kb + wave * len, k1w = k0w + len < ke ? k0w + len : ke;
+  const int64_t ng = k1w > k0w ? (k1w - k0w) / kGS64 : 0;
+  constexpr int kSteps = kGS64 / 4;
+  float xa[kSteps][4], xb[kSteps][4];
+  auto products = [&](const double (&av)[4], const double (&bv)[4]) {
 #pragma unroll
-    for (int r = 0; r < kGK64 / 4; ++r) {
-      const int64_t t = k0 + rg + 4 * r;
-      const bool in = t < ke;
-      // a plain conditional load (no arithmetic on the value here, so no wait per load)
-      ra[r] = (va && in) ? pa[t * lda] : 0.f;
-      rb[r] = (vb && in) ? pb[t * ldb] : 0.f;
-    }
-  };
-  load(kb);
-  for (int64_t k0 = kb; k0 < ke; k0 += kGK64) {
-    // raw values; rows past the end of the split are zeroed again after centring below
+    for (int a = 0; a < 4; ++a)
+      if (a < na) {
 #pragma unroll
-    for (int r = 0; r < kGK64 / 4; ++r) {
-      As[(rg + 4 * r) * kGLd + cc] = ra[r];
-      Bs[(rg + 4 * r) * kGLd + cc] = rb[r];
-    }
-    __syncthreads();
-    if (k0 + kGK64 < ke) load(k0 + kGK64);
-#pragma unroll
-    for (int kk = 0; kk < kGK64; kk += 4) {
-      if (!(live_a[0] && live_b[0])) break;
-      const bool in = k0 + kk + (lane >> 4) < ke;
-      double av[2], bv[2];
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const double ra = (double)As[(kk + (lane >> 4)) * kGLd + wi * 32 + q * 16 + (lane & 15)];
-        const double rb = (double)Bs[(kk + (lane >> 4)) * kGLd + wj * 32 + q * 16 + (lane & 15)];
-        av[q] = in ? ra - mua[q] : 0.0;
-        bv[q] = in ? rb - mub[q] : 0.0;
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          if (live_a[a] && live_b[b])
+        for (int b = 0; b < 4; ++b)
+          if (b < nb)
             acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
+      }
+  };
+  if (ng > 0) {
+    const float *qa[4], *qb[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      qa[q] = pa[q] + lk * lda;
+      qb[q] = pb[q] + lk * ldb;
     }
-    __syncthreads();
+    auto load = [&](int64_t t, int s) {              // t wave-uniform
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        xa[s][q] = qa[q][t * lda];
+        xb[s][q] = qb[q][t * ldb];
+      }
+    };
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      load(k0w + 4 * s, s);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    const int64_t last = k0w + (ng - 1) * kGS64;
+    for (int64_t k0 = k0w; k0 <= last; k0 += kGS64) {
+      const int64_t kn = k0 < last ? k0 + kGS64 : last;    // (past the end: the last group again)
+#pragma unroll
+      for (int s = 0; s < kSteps; ++s) {
+        double av[4], bv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          av[q] = (double)xa[s][q] - ma[q];
+          bv[q] = (double)xb[s][q] - mb[q];
+          asm volatile("" : "+v"(av[q]), "+v"(bv[q]));   // formed here, not at each product
+        }
+        load(kn + 4 * s, s);
+        __builtin_amdgcn_sched_barrier(0);               // (loads stay in this order)
+        products(av, bv);
+      }
+    }
   }
-  // D layout of 16x16x4 f64: lane l, reg r -> row l/16 + 4 r, column l%16
+  for (int64_t t0 = k0w + ng * kGS64; t0 < k1w; t0 += 4) {   // the rest: clamped and masked
+    const int64_t t = t0 + lk, tc = t < k1w ? t : k1w - 1;
+    double av[4], bv[4];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int q = 0; q < 4; ++q) {
+      xa[0][q] = pa[q][tc * lda];
+      xb[0][q] = pb[q][tc * ldb];
+    }
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int q = 0; q < 4; ++q) {
+      av[q] = t < k1w ? (double)xa[0][q] - ma[q] : 0.0;
+      bv[q] = t < k1w ? (double)xb[0][q] - mb[q] : 0.0;
+    }
+    products(av, bv);
+  }
+  // D layout of 16x16x4 f64: lane l, reg r -> row l/16 + 4 r, column l%16.  Two block rows at a
+  // time: every wave leaves its sums in LDS, then adds up and writes two of the eight blocks.
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (2 * h >= na) break;
+    if (h > 0) __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][4 * a + b][r][lane] = acc[2 * h + a][b][r];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int blk = 2 * wave + u, a = 2 * h + (blk >> 2), b = blk & 3;
+      if (a >= na || b >= nb) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int64_t i = i0 + wi * 32 + a * 16 + (lane >> 4) + 4 * r;
-        const int64_t j = j0 + wj * 32 + b * 16 + (lane & 15);
+        const double v = ((part[0][blk][r][lane] + part[1][blk][r][lane]) +
+                          part[2][blk][r][lane]) + part[3][blk][r][lane];
+        const int64_t i = i0 + a * 16 + lk + 4 * r, j = j0 + b * 16 + li;
         if (i < M && j < N) {
-          out[i * ldo + j] = scale * acc[a][b][r];
-          if (mirror) out[j * ldo + i] = scale * acc[a][b][r];
+          out[i * ldo + j] = scale * v;
+          if (mirror) out[j * ldo + i] = scale * v;
         }
       }
+    }
+  }
 }
 
 }  // namespace vl

@@ -168,7 +168,8 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out) {
 
 size_t scratch_doubles(const PairwisePlan& p) {
   size_t a = (size_t)colmean_splits(p.n_eff) * p.m;
-  size_t b = (size_t)gram_splits(p.m, p.m, p.n_eff) * p.m * p.m;
+  size_t b = (size_t)std::max(gram_splits(p.m, p.m, p.n_eff),
+                              gram_splits_f64(p.m, p.m, p.n_eff)) * p.m * p.m;
   if (p.sliced) {
     a *= 3;     // column ranges for the slice exponents
     b = std::max(b, (size_t)slice_gram_splits(p.m, p.m, p.n_eff, true) * p.m * p.m);

@@ -25,6 +25,8 @@
 #include "var_dev.hpp"
 #include "profile.hpp"
 
+#include <algorithm>
+
 namespace vl {
 
 // Refinement steps after the BF16 Gram solve (contraction ~cond(G) 2^-8 per step).
@@ -212,7 +214,8 @@ size_t var_ws_bytes(const VarPlan& v, void* base, VarWs* out) {
   w.F = c.take<double>(v.m * nc);
   w.mu0 = c.take<double>(nc);
   size_t s1 = (size_t)colmean_splits(v.n_eff) * nc * (v.sliced ? 3 : 1);
-  size_t s2 = (size_t)gram_splits(v.m, nc, v.n_eff) * v.m * nc;      // lag products
+  size_t s2 = (size_t)std::max(gram_splits(v.m, nc, v.n_eff),
+                               gram_splits_f64(v.m, nc, v.n_eff)) * v.m * nc;  // lag products
   size_t s3 = (size_t)gram_splits(v.dz, v.m, v.n_eff) * v.dz * v.m;   // R, refinement Gram
   size_t s4 = (size_t)gram_splits(v.dz, v.dz, v.n_eff) * v.dz * v.dz; // direct G
   size_t s = s1 > s2 ? s1 : s2;
@@ -374,7 +377,7 @@ static int var_normal_equations(const VarPlan& v, const VarWs& w, const float* X
 size_t lag_cov_scratch_doubles(int64_t n, int64_t m, int p) {
   const int64_t nc = m * (p + 1), n_eff = n - p;
   const size_t s1 = (size_t)colmean_splits(n_eff) * nc;
-  const size_t s2 = (size_t)gram_splits(nc, nc, n_eff) * nc * nc;
+  const size_t s2 = (size_t)gram_splits_f64(nc, nc, n_eff) * nc * nc;
   return s1 > s2 ? s1 : s2;
 }
 
