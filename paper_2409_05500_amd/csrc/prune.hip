@@ -27,7 +27,7 @@
 // What bounds it: memory.  A step with |A| of d columns active reads Li once (|A|^2 / 2
 // doubles, private to the variable: 3.3 GB of active matrices at m = 400, p = 2, far over the
 // caches) and min(|A|, d - |A|) rows of C (shared, 11.5 MB: served by L2 and the Infinity Cache).
-// Measured at m = 400, p = 2, n = 10^4, complete paths: 191 ms a call, 1.4 TB read; 601 ms with the
+// Measured at m = 400, p = 2, n = 10^4, complete paths: 174 ms a call, 1.4 TB read; 601 ms with the
 // inverse of the active Gram itself kept and updated (1.25 |A|^2 doubles a step, written too).
 // Clocks of the longest path (1199 columns): 71 ms in the products with C, 89 ms in those with
 // Li, 23 ms in the rest; together the workgroups move ~9 TB/s through the caches.
@@ -232,7 +232,7 @@ __device__ __forceinline__ void li_blocks(const double* __restrict__ Li, int n, 
 // the next multiple of 64).  NC = 0: any n, Li read twice (the
 // row sums through y, a scratch vector of n).  Ends with a barrier; x, out may not alias.
 template <int NC>
-__device__ inline double apply_inverse(const double* __restrict__ Li, int n, const double* x,
+__device__ __forceinline__ double apply_inverse(const double* __restrict__ Li, int n, const double* x,
                                        double* out, double* y, double* part, double* red) {
   const int t = threadIdx.x, lane = fresh_lane(), w = uni(t / kWave);
   double ysq = 0.0, z = 0.0;
@@ -284,7 +284,7 @@ __device__ inline double apply_inverse(const double* __restrict__ Li, int n, con
 // r0 into every row below it moves all of column r0 into that one row, whose outer product is
 // then the Schur complement's term, and is dropped.  cs, sn, v, tmp: vectors of n.  Ends with a
 // barrier.
-__device__ inline void li_remove(double* __restrict__ Li, int n, int r0, double* cs, double* sn,
+__device__ __forceinline__ void li_remove(double* __restrict__ Li, int n, int r0, double* cs, double* sn,
                                  double* v, double* tmp) {
   const int t = threadIdx.x;
   // the rotations follow from column r0 alone
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(256) void prune_check_order_kernel(const int32_t* _
 // columns.  The slots' columns and weights go to scalar registers; 2 RU loads are in flight per
 // lane (a row of C is read as coalesced pieces where the inactive columns are consecutive).
 template <int RU>
-__device__ inline void inactive_dots(const double* __restrict__ C, int64_t ldc, int n,
+__device__ __forceinline__ void inactive_dots(const double* __restrict__ C, int64_t ldc, int n,
                                      const int* col, const double* b, int np, const int* ic,
                                      double* part) {
   const int lane = fresh_lane(), w = uni(threadIdx.x / kWave);
