@@ -31,6 +31,16 @@ int gemm_f64(int64_t M, int64_t N, int64_t K, double alpha, const double* A, int
   return VL_OK;
 }
 
+// blockIdx.y: the matrix of a batch (strides of A and of the scratch; right-hand sides and inverses
+// are single-matrix only)
+__device__ inline CholArgs chol_of_batch(CholArgs a, int64_t strideA, int64_t strideW) {
+  const int64_t z = blockIdx.y;
+  a.A += z * strideA;
+  a.diag0 += z * strideW;
+  a.Yb += z * strideW;
+  return a;
+}
+
 __global__ __launch_bounds__(256) void chol_prologue_kernel(CholArgs a) {
   if (blockIdx.x > 0) {
     chol_linv_init(a, (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x);
@@ -41,6 +51,18 @@ __global__ __launch_bounds__(256) void chol_prologue_kernel(CholArgs a) {
 
 __global__ __launch_bounds__(256) void chol_step_kernel(CholArgs a, int64_t k) {
   chol_step_item(a, k, blockIdx.x);
+}
+
+__global__ __launch_bounds__(256) void chol_batch_prologue_kernel(CholArgs a, int64_t strideA,
+                                                                  int64_t strideW) {
+  const CholArgs b = chol_of_batch(a, strideA, strideW);
+  chol_prologue_block(b);
+}
+
+__global__ __launch_bounds__(256) void chol_batch_step_kernel(CholArgs a, int64_t k,
+                                                              int64_t strideA, int64_t strideW) {
+  const CholArgs b = chol_of_batch(a, strideA, strideW);
+  chol_step_item(b, k, blockIdx.x);
 }
 
 size_t chol_ws_doubles(int64_t n) { return (size_t)chol_ws_doubles_dev(n); }
@@ -69,6 +91,33 @@ int chol_solve_lower(double* A, int64_t n, int64_t lda, double* R, int64_t nrhs,
     const int64_t items = step_items(nb, k, cr, Linv != nullptr).total();
     if (items == 0) continue;
     chol_step_kernel<<<(unsigned)items, 256, 0, stream>>>(a, k);
+    VL_LAUNCH_CHECK();
+  }
+  return VL_OK;
+}
+
+int chol_batch(double* A, int64_t strideA, int64_t n, double* ws, int64_t strideW, int count,
+               int32_t* st, hipStream_t stream) {
+  const int64_t nb = ceil_div(n, (int64_t)kNb);
+  CholArgs a;
+  a.A = A;
+  a.n = n;
+  a.lda = n;
+  a.R = nullptr;
+  a.nrhs = 0;
+  a.ldr = 0;
+  a.Li = nullptr;
+  a.ldli = 0;
+  a.diag0 = ws;
+  a.Yb = ws + n;
+  a.st = st;
+  chol_batch_prologue_kernel<<<dim3(1, (unsigned)count), 256, 0, stream>>>(a, strideA, strideW);
+  VL_LAUNCH_CHECK();
+  for (int64_t k = 0; k < nb; ++k) {
+    const int64_t items = step_items(nb, k, 0, false).total();
+    if (items == 0) continue;
+    chol_batch_step_kernel<<<dim3((unsigned)items, (unsigned)count), 256, 0, stream>>>(
+        a, k, strideA, strideW);
     VL_LAUNCH_CHECK();
   }
   return VL_OK;

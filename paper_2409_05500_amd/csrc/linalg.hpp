@@ -23,4 +23,14 @@ size_t chol_ws_doubles(int64_t n);
 int chol_solve_lower(double* A, int64_t n, int64_t lda, double* R, int64_t nrhs, int64_t ldr,
                      double* Linv, int64_t ldli, double* ws, int32_t* st, hipStream_t stream);
 
+// The factorisation alone of `count` matrices A + z strideA (n x n, ld n), one launch per panel
+// for all of them; matrix z's scratch is ws + z strideW (chol_ws_doubles(n) each).
+int chol_batch(double* A, int64_t strideA, int64_t n, double* ws, int64_t strideW, int count,
+               int32_t* st, hipStream_t stream);
+
+// Diagonal entry i of L^{-1} in that scratch (n the matrix's size).
+__host__ __device__ inline const double* chol_inv_diag(const double* ws, int64_t n, int64_t i) {
+  return ws + n + (i >> 6) * 64 * 64 + (i & 63) * 65;
+}
+
 }  // namespace vl

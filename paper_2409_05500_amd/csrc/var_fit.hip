@@ -20,6 +20,7 @@
 //          design is too ill-conditioned for a BF16 Gram) raises VL_ERR_SINGULAR.
 #include "gram.hpp"
 #include "linalg.hpp"
+#include "chol_dev.hpp"
 #include "var_fit.hpp"
 #include "sliced.hpp"
 #include "var_dev.hpp"
@@ -465,19 +466,43 @@ int run_var(const VarPlan& v, const VarWs& w, const float* X, int64_t ldx, int p
 //   T Sigma_p = Yc^T Yc - R_p^T G_p^{-1} R_p = Yc^T Yc - sum_{tau <= p} W_tau^T W_tau,
 // and ln det Sigma_p = -2 sum_i ln (L_p^{-1})_ii - m ln T from the factor of T Sigma_p.
 // ------------------------------------------------------------------------------------------
-__global__ void lag_copy_kernel(const double* __restrict__ a, double* __restrict__ b, int64_t n) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) b[e] = a[e];
+// A_p = W_p^T W_p for every p at once (blockIdx.z = p - 1; the lower triangles).
+__global__ __launch_bounds__(256) void lag_products_kernel(const double* __restrict__ W, int64_t m,
+                                                           double* __restrict__ A) {
+  const int64_t off = (int64_t)blockIdx.z * m * m;
+  gemm_f64_block(m, m, m, 1.0, W + off, m, 1, W + off, m, 0, 0.0, A + off, m, 1, 0,
+                 (int64_t)blockIdx.y * 32, (int64_t)blockIdx.x * 32);
 }
 
-__global__ __launch_bounds__(256) void lag_scores_kernel(const double* __restrict__ Li, int64_t m,
-                                                         int p, double T,
+// A_p <- T Sigma_p = Yc^T Yc - sum_{tau <= p} W_tau^T W_tau, in lag order; Yc^T Yc is the lag
+// product F_0 of the normal equations (its lower triangle).
+__global__ void lag_sigma_kernel(const double* __restrict__ F, int64_t ldf, int64_t m, int pmax,
+                                 double* __restrict__ A) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= m * m) return;
+  const int64_t i = e / m, j = e % m;
+  if (j > i) return;
+  double s = F[i * ldf + j];
+  for (int p = 0; p < pmax; ++p) {
+    double* Ap = A + (int64_t)p * m * m;
+    s -= Ap[e];
+    Ap[e] = s;
+    Ap[j * m + i] = s;      // (the factorisation loads whole diagonal tiles)
+  }
+}
+
+// One workgroup per lag order: ln det Sigma_p from the diagonal of the factor's inverse, then the
+// criteria.
+__global__ __launch_bounds__(256) void lag_scores_kernel(const double* __restrict__ chol,
+                                                         int64_t strideW, int64_t m, double T,
                                                          double* __restrict__ logdet,
                                                          double* __restrict__ aic,
                                                          double* __restrict__ bic) {
   __shared__ double part[4];
+  const int p = (int)blockIdx.x + 1;
+  const double* ws = chol + (int64_t)blockIdx.x * strideW;
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < m; i += 256) s += log(Li[i * m + i]);
+  for (int64_t i = threadIdx.x; i < m; i += 256) s += log(*chol_inv_diag(ws, m, i));
   s = wave_sum_d(s);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
   __syncthreads();
@@ -510,20 +535,10 @@ size_t lag_ws_bytes(const VarPlan& v, void* base, LagWs* out) {
   char* vbase = c.take<char>(vb);
   if (base) var_ws_bytes(v, vbase, &w.var);
   const int64_t m = v.m;
-  w.Syy = c.take<double>(m * m);
-  w.A = c.take<double>(m * m);
-  w.Li = c.take<double>(m * m);
-  w.chol = c.take<double>(chol_ws_doubles(m));
+  w.A = c.take<double>(v.p * m * m);
+  w.chol = c.take<double>(v.p * chol_ws_doubles(m));
   if (out) *out = w;
   return c.used;
-}
-
-__global__ void lag_syy_kernel(const double* __restrict__ F, int64_t m, int64_t ldf,
-                               double* __restrict__ Syy) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= m * m) return;
-  const int64_t i = e / m, j = e % m;
-  Syy[e] = i >= j ? F[i * ldf + j] : F[j * ldf + i];
 }
 
 int run_lag_select(const VarPlan& v, const LagWs& w, const float* X, int64_t ldx, double* logdet,
@@ -538,23 +553,22 @@ int run_lag_select(const VarPlan& v, const LagWs& w, const float* X, int64_t ldx
     if (rc) return rc;
   }
   ProfileScope ps("lag_scores", stream);
-  // T Sigma_0 = Yc^T Yc: the lag product F_0 of the normal equations (lag-0 columns centred by
-  // their own means), its lower triangle mirrored
-  lag_syy_kernel<<<(unsigned)ceil_div(m * m, 256), 256, 0, stream>>>(vw.F, m, m * (v.p + 1),
-                                                                     w.Syy);
+  // every p at once: the p_max products, the running differences, one factorisation launch per
+  // panel for all of them (the diagonal of the inverse factor is all that ln det needs).  One p
+  // after another, each with the whole inverse, the four factorisations at m = 400 were 32 short
+  // launches: the call took 1.52 ms, 1.10 so (m = 10, p_max = 5: 0.23 and 0.12).
+  const int64_t wsd = (int64_t)chol_ws_doubles(m);
+  const unsigned t32 = (unsigned)ceil_div(m, (int64_t)32);
+  lag_products_kernel<<<dim3(t32, t32, (unsigned)v.p), 256, 0, stream>>>(vw.Tmp, m, w.A);
   VL_LAUNCH_CHECK();
-  const double T = (double)n_eff;
-  for (int p = 1; p <= v.p; ++p) {
-    const double* Wp = vw.Tmp + (int64_t)(p - 1) * m * m;
-    rc = gemm_f64(m, m, m, -1.0, Wp, m, true, Wp, m, false, 1.0, w.Syy, m, false, stream);
-    if (rc) return rc;
-    lag_copy_kernel<<<(unsigned)ceil_div(m * m, 256), 256, 0, stream>>>(w.Syy, w.A, m * m);
-    VL_LAUNCH_CHECK();
-    rc = chol_solve_lower(w.A, m, m, nullptr, 0, 0, w.Li, m, w.chol, st, stream);
-    if (rc) return rc;
-    lag_scores_kernel<<<1, 256, 0, stream>>>(w.Li, m, p, T, logdet, aic, bic);
-    VL_LAUNCH_CHECK();
-  }
+  lag_sigma_kernel<<<(unsigned)ceil_div(m * m, 256), 256, 0, stream>>>(vw.F, m * (v.p + 1), m, v.p,
+                                                                       w.A);
+  VL_LAUNCH_CHECK();
+  rc = chol_batch(w.A, m * m, m, w.chol, wsd, v.p, st, stream);
+  if (rc) return rc;
+  lag_scores_kernel<<<(unsigned)v.p, 256, 0, stream>>>(w.chol, wsd, m, (double)n_eff, logdet, aic,
+                                                       bic);
+  VL_LAUNCH_CHECK();
   lag_best_kernel<<<1, 64, 0, stream>>>(aic, bic, v.p, best);
   VL_LAUNCH_CHECK();
   return VL_OK;

@@ -36,10 +36,8 @@ struct VarWs {
 // Lag-order selection workspace: the VAR workspace of the p_max plan, then m x m buffers.
 struct LagWs {
   VarWs var;
-  double* Syy = nullptr;    // T Sigma_p, updated in place from p = 0
-  double* A = nullptr;      // copy factored for the log-determinant
-  double* Li = nullptr;     // its L^{-1}
-  double* chol = nullptr;   // factorisation scratch (m)
+  double* A = nullptr;      // T Sigma_p for every p (p_max m x m), factored in place
+  double* chol = nullptr;   // their factorisation scratch
 };
 
 VarPlan plan_var(int64_t n, int64_t m, int p, bool sliced = false);

@@ -71,3 +71,13 @@ def test_select_lag_recovers_the_generating_order(api):
     inst = synth.make_custom(6, 8000, 2, "laplace", 8, edge_prob=0.2, w_lo=0.1, w_hi=0.4)
     _, _, _, (pa, pb) = api.select_lag(torch.from_numpy(inst.X32).cuda(), 4)
     assert pb == 2 and pa >= 2
+
+
+@pytest.mark.parametrize("case", [(63, 1), (64, 3), (128, 2), (129, 1), (2, 9)],
+                         ids=lambda c: f"m{c[0]}_pmax{c[1]}")
+def test_select_lag_panel_edges(api, case):
+    """Sizes at the edges of the factorisation's 64-wide panels, all lag orders factored together."""
+    m, p_max = case
+    print(f"lag selection edges m={m} p_max={p_max}", flush=True)
+    X = np.random.default_rng(m).laplace(0.0, 1.0, (m * p_max * 4 + 200, m)).astype(np.float32)
+    _check(api, X, p_max)
