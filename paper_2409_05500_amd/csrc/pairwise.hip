@@ -95,17 +95,26 @@ __global__ __launch_bounds__(256) void pairwise_collinear_kernel(
   }
 }
 
-template <class TP>
-__global__ void combine_hr_kernel(const TP* __restrict__ partU, const TP* __restrict__ partB,
-                                  int nc, int64_t m, int64_t n_eff, double* __restrict__ Hr,
-                                  double* __restrict__ mom) {
-  combine_hr_elem(partU, partB, nc, m, n_eff, Hr, mom,
-                  (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+// The items' rows, one wave each (see use_rows()); no remap: a handful of items.
+__global__ __launch_bounds__(256) void pairwise_rows_kernel(
+    const float* __restrict__ Xs, int64_t n_pad, const float2* __restrict__ coef, int64_t m_pad,
+    int64_t m, int nt, int64_t tiles, int chunk_len, int64_t items, float* __restrict__ partU,
+    float* __restrict__ partB) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t item = blockIdx.x;
+  if (item >= items) return;
+  pairwise_moments_row(Xs, n_pad, coef, m_pad, m, nt, tiles, chunk_len, item, wave, partU, partB);
 }
 
-__global__ void score_kernel(const double* __restrict__ Hx, const double* __restrict__ Hr,
-                             int64_t m, double* __restrict__ S) {
-  score_elem(Hx, Hr, m, S, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+// blockIdx.x: the upper-triangular blocks of combine_score_block, row by row.
+template <class TP>
+__global__ __launch_bounds__(kCS * kCS) void combine_score_kernel(
+    const TP* __restrict__ partU, const TP* __restrict__ partB, int nc, int64_t m, int64_t n_eff,
+    const double* __restrict__ Hx, double* __restrict__ Hr, double* __restrict__ mom,
+    double* __restrict__ S, int nb) {
+  int bi, bj;
+  tile_coords(blockIdx.x, nb, bi, bj);
+  combine_score_block(partU, partB, nc, m, n_eff, Hx, Hr, mom, S, bi, bj);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -187,6 +196,15 @@ int standardize_to(const float* E, int64_t lde, int64_t n_eff, int64_t m, const 
   return VL_OK;
 }
 
+// Whether a plan's items run as four one-row waves each.  The 1024 SIMDs issue at their limit from
+// one wave on, so a plan of x = items / 1024 waves a SIMD takes ceil(x) item times, in rows
+// ceil(4 x) / 4 of them, each up to 15% longer for its loads
+// (measured: x = 0.01, m = 10, n = 1000 20.0 -> 11.3 us with the launch; 0.44 15.8 -> 10.5; 1.2
+// 21.0 -> 15.8; 1.85 and 2.86 even; 16.5 161 -> 171).
+static bool use_rows(int64_t items) {
+  return 1.15 * (double)ceil_div(4 * items, (int64_t)1024) < 4.0 * (double)ceil_div(items, (int64_t)1024);
+}
+
 // Stages 4-5 with FP32 (plain sums) or FP64 (compensated sums) partials.
 template <class TP>
 static int launch_moments(const PairwisePlan& p, const PairwiseWs& w, const float* E,
@@ -195,8 +213,16 @@ static int launch_moments(const PairwisePlan& p, const PairwiseWs& w, const floa
   const int64_t m = p.m, n_eff = p.n_eff;
   {
     ProfileScope ps("pairwise_moments", stream);
-    pairwise_moments_kernel<TP><<<(unsigned)p.blocks, 256, 0, stream>>>(
-        w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB);
+    bool rows = false;
+    if constexpr (std::is_same<TP, float>::value) {
+      rows = use_rows(p.items);
+      if (rows)
+        pairwise_rows_kernel<<<(unsigned)p.items, 256, 0, stream>>>(
+            w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB);
+    }
+    if (!rows)
+      pairwise_moments_kernel<TP><<<(unsigned)p.blocks, 256, 0, stream>>>(
+          w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB);
     VL_LAUNCH_CHECK();
   }
   {
@@ -209,10 +235,9 @@ static int launch_moments(const PairwisePlan& p, const PairwiseWs& w, const floa
   }
   {
     ProfileScope ps("pairwise_combine", stream);
-    combine_hr_kernel<TP><<<(unsigned)ceil_div(m * m, 256), 256, 0, stream>>>(
-        partU, partB, p.nc, m, n_eff, Hr, mom);
-    VL_LAUNCH_CHECK();
-    score_kernel<<<(unsigned)ceil_div(m * m, 256), 256, 0, stream>>>(Hx, Hr, m, S);
+    const int64_t nb = ceil_div(m, (int64_t)kCS);
+    combine_score_kernel<TP><<<(unsigned)(nb * (nb + 1) / 2), kCS * kCS, 0, stream>>>(
+        partU, partB, p.nc, m, n_eff, Hx, Hr, mom, S, (int)nb);
     VL_LAUNCH_CHECK();
   }
   return VL_OK;

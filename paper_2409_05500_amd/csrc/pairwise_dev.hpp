@@ -409,6 +409,97 @@ __device__ __attribute__((always_inline)) inline void pairwise_moments_item(
   }
 }
 
+// One row of a work item: variable i0 + row against the tile's kT columns, both directions.  The
+// samples of a lane, the order of its sums, the flushes and the lane pairing of the reduction are
+// the whole item's, so the partials are the same bits; a plan with few items then has four times
+// the waves, each a quarter as long.
+__device__ __attribute__((always_inline)) inline void pairwise_moments_row(
+    const float* __restrict__ Xs, int64_t n_pad, const float2* __restrict__ coef, int64_t m_pad,
+    int64_t m, int nt, int64_t tiles, int chunk_len, int64_t item, int row,
+    float* __restrict__ partU, float* __restrict__ partB) {
+  const int lane = threadIdx.x & 63;
+  const int64_t chunk = item / tiles;
+  const int64_t tile = item - chunk * tiles;
+  int bi, bj;
+  tile_coords(tile, nt, bi, bj);
+  const int64_t i = (int64_t)bi * kT + row, j0 = (int64_t)bj * kT;
+  if (i >= m) return;
+  float ca[kT], cb[kT];
+#pragma unroll
+  for (int jj = 0; jj < kT; ++jj) {
+    typedef const __attribute__((address_space(4))) float* const_f32p;
+    const const_f32p cp = (const_f32p)(uintptr_t)coef;
+    const int64_t ci = 2 * (i * m_pad + j0 + jj);
+    ca[jj] = cp[ci];
+    cb[jj] = cp[ci + 1];
+  }
+  float U[2][kT], P[2][kT], B[2][kT];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int jj = 0; jj < kT; ++jj) {
+      U[d][jj] = 0.f;
+      P[d][jj] = 1.f;
+      B[d][jj] = 0.f;
+    }
+  const uint32_t tb = (uint32_t)(chunk * chunk_len) + 2u * (uint32_t)lane;
+  const float* xi_r = Xs + i * n_pad;
+  const float* xj_r[kT];
+#pragma unroll
+  for (int k = 0; k < kT; ++k) xj_r[k] = Xs + (j0 + k) * n_pad;
+  const float cln2 = (float)(kWScale * kLn2);
+  const int steps = chunk_len / 128;
+  int since_flush = 0;
+  for (int s = 0; s < steps; ++s) {
+    const uint32_t o = tb + 128u * (uint32_t)s;
+    const float2 xi = *reinterpret_cast<const float2*>(xi_r + o);
+    float2 xj[kT];
+#pragma unroll
+    for (int k = 0; k < kT; ++k) xj[k] = *reinterpret_cast<const float2*>(xj_r[k] + o);
+#pragma unroll
+    for (int jj = 0; jj < kT; ++jj) {
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float xv = e ? xi.y : xi.x;
+        const float yv = e ? xj[jj].y : xj[jj].x;
+        const float w0 = fmaf(xv, ca[jj], -(yv * cb[jj]));
+        const float w1 = fmaf(yv, ca[jj], -(xv * cb[jj]));
+        moment_step(w0, U[0][jj], P[0][jj], B[0][jj]);
+        moment_step(w1, U[1][jj], P[1][jj], B[1][jj]);
+      }
+    }
+    since_flush += 2;
+    if (since_flush == 64 || s == steps - 1) {
+      const float cnt = (float)since_flush;
+#pragma unroll
+      for (int d = 0; d < 2; ++d)
+#pragma unroll
+        for (int jj = 0; jj < kT; ++jj) {
+          U[d][jj] = fmaf(__builtin_amdgcn_logf(P[d][jj]) - cnt, cln2, U[d][jj]);
+          P[d][jj] = 1.f;
+        }
+      since_flush = 0;
+    }
+  }
+  // value index v = kind*8 + d*4 + jj; lanes 4 v .. 4 v + 3 hold its sum
+  float v[16];
+#pragma unroll
+  for (int d = 0; d < 2; ++d)
+#pragma unroll
+    for (int jj = 0; jj < kT; ++jj) {
+      v[d * 4 + jj] = U[d][jj];
+      v[8 + d * 4 + jj] = B[d][jj];
+    }
+  const float sum = wave_reduce_scatter16(v);
+  const int kind = lane >> 5, d = (lane >> 4) & 1, jj = (lane >> 2) & 3;
+  const int64_t j = j0 + jj;
+  if ((lane & 3) == 0 && j < m && i != j) {
+    const int64_t r = d ? j : i, c = d ? i : j;
+    float* dst = kind ? partB : partU;
+    dst[chunk * m * m + r * m + c] = sum;
+  }
+}
+
 // The same work item with Kahan-compensated sums and FP64 partials (231 VGPRs, 2 waves per
 // SIMD).  A separate body: folding both forms into one template changed the schedule the
 // compiler chose for the plain one (6% slower).
@@ -589,6 +680,16 @@ __device__ inline void pairwise_collinear_item(
 // ------------------------------------------------------------------------------------------
 // Stage 5: FP64 combine.  Hr[i][j] from the chunk partials (fixed order), then S.
 // ------------------------------------------------------------------------------------------
+__device__ inline double combine_finish(double su, double sb, int64_t n_eff, double* mom) {
+  const double A = su / (kWScale * (double)n_eff);
+  const double B = sb / (kWScale * (double)n_eff);
+  if (mom) {
+    mom[0] = A;
+    mom[1] = B;
+  }
+  return kHGauss - kK1 * (A - kGamma) * (A - kGamma) - kK2 * B * B;
+}
+
 template <class TP>
 __device__ inline void combine_hr_elem(const TP* __restrict__ partU,
                                        const TP* __restrict__ partB, int nc, int64_t m,
@@ -606,21 +707,75 @@ __device__ inline void combine_hr_elem(const TP* __restrict__ partU,
     su += (double)partU[(int64_t)c * m * m + e];
     sb += (double)partB[(int64_t)c * m * m + e];
   }
-  const double A = su / (kWScale * (double)n_eff);
-  const double B = sb / (kWScale * (double)n_eff);
-  Hr[e] = kHGauss - kK1 * (A - kGamma) * (A - kGamma) - kK2 * B * B;
-  if (mom) {
-    mom[2 * e] = A;
-    mom[2 * e + 1] = B;
-  }
+  Hr[e] = combine_finish(su, sb, n_eff, mom ? mom + 2 * e : nullptr);
 }
 
-__device__ inline void score_elem(const double* __restrict__ Hx, const double* __restrict__ Hr,
-                                  int64_t m, double* __restrict__ S, int64_t e) {
-  if (e >= m * m) return;
-  const int64_t i = e / m, j = e % m;
-  // the same two sums in both orders -> S[j][i] == -S[i][j] bit for bit
-  S[e] = i == j ? 0.0 : (Hx[j] + Hr[i * m + j]) - (Hx[i] + Hr[j * m + i]);
+// Block bi <= bj of kCS x kCS entries and its mirror image, one entry of each a thread: Hr of both
+// (partials read along rows, four chunks of both in flight, added in chunk order), then S of
+// both, the mirrored Hr passing through LDS: the same two sums in both orders -> S[j][i] ==
+// -S[i][j] bit for bit.  kCS^2 threads.
+constexpr int kCS = 16;
+
+template <class TP>
+__device__ inline void combine_score_block(const TP* __restrict__ partU,
+                                           const TP* __restrict__ partB, int nc, int64_t m,
+                                           int64_t n_eff, const double* __restrict__ Hx,
+                                           double* __restrict__ Hr, double* __restrict__ mom,
+                                           double* __restrict__ S, int64_t bi, int64_t bj) {
+  __shared__ double h[2][kCS][kCS + 1];
+  const int tx = threadIdx.x % kCS, ty = threadIdx.x / kCS;
+  int64_t i[2], j[2], e[2];
+  bool in[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    i[q] = (q ? bj : bi) * kCS + ty;
+    j[q] = (q ? bi : bj) * kCS + tx;
+    in[q] = i[q] < m && j[q] < m;
+    e[q] = in[q] ? i[q] * m + j[q] : 0;
+  }
+  const int64_t mm = m * m;
+  double su[2] = {0.0, 0.0}, sb[2] = {0.0, 0.0};
+  int c = 0;
+  for (; c + 4 <= nc; c += 4) {
+    TP u[2][4], b[2][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        u[q][k] = partU[(int64_t)(c + k) * mm + e[q]];
+        b[q][k] = partB[(int64_t)(c + k) * mm + e[q]];
+      }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        su[q] += (double)u[q][k];
+        sb[q] += (double)b[q][k];
+      }
+  }
+  for (; c < nc; ++c)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      su[q] += (double)partU[(int64_t)c * mm + e[q]];
+      sb[q] += (double)partB[(int64_t)c * mm + e[q]];
+    }
+  double v[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const bool off = i[q] != j[q];
+    v[q] = 0.0;
+    if (in[q]) {
+      if (off) v[q] = combine_finish(su[q], sb[q], n_eff, mom ? mom + 2 * e[q] : nullptr);
+      else if (mom) mom[2 * e[q]] = mom[2 * e[q] + 1] = 0.0;
+      Hr[e[q]] = v[q];
+    }
+    h[q][ty][tx] = v[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 2; ++q)
+    if (in[q])
+      S[e[q]] = i[q] == j[q] ? 0.0 : (Hx[j[q]] + v[q]) - (Hx[i[q]] + h[1 - q][tx][ty]);
 }
 
 }  // namespace vl
