@@ -31,6 +31,8 @@ inline bool sliced(int prec) { return (prec & ~VL_PAIRWISE_COMPENSATED) == VL_PR
 
 inline bool aligned256(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 255u) == 0; }
 
+// Sets the status word, for the calls whose first raising kernel does not follow a kernel of the
+// call's own that sets it (colmeans(), run_order(): a launch of 4 us less).
 int begin(int32_t* dev_status, hipStream_t stream) {
   reset_status_kernel<<<1, 64, 0, stream>>>(dev_status);
   return hipGetLastError() == hipSuccess ? VL_OK : VL_ERR_HIP;
@@ -95,8 +97,6 @@ int varlingam_fit_var(const float* X, int64_t n, int64_t m, int64_t ldx, int p, 
   VarWs w;
   var_ws_bytes(v, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
   return run_var(v, w, X, ldx, prec, M, intercept, E, lde, dev_status, s);
 }
 
@@ -118,8 +118,6 @@ int varlingam_select_lag(const float* X, int64_t n, int64_t m, int64_t ldx, int 
   LagWs w;
   lag_ws_bytes(v, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
   return run_lag_select(v, w, X, ldx, logdet, aic, bic, best, dev_status, s);
 }
 
@@ -143,8 +141,6 @@ int pairwise_stats(const float* E, int64_t n_eff, int64_t m, int64_t lde, int pr
   PairwiseWs w;
   pairwise_ws_bytes(p, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
   return run_pairwise(p, w, E, lde, prec, Hx, Hr, S, Cov, nullptr, dev_status, s);
 }
 
@@ -165,8 +161,6 @@ int pairwise_stats_noalloc(const float* E, int64_t n_eff, int64_t m, int64_t lde
   PairwiseWs w;
   pairwise_ws_bytes(p, ws, &w);
   hipStream_t s = as_stream(stream);
-  rc = begin(dev_status, s);
-  if (rc) return rc;
   return run_pairwise(p, w, E, lde, prec, Hx, Hr, S, Cov, nullptr, dev_status, s);
 }
 
@@ -188,8 +182,10 @@ int varlingam_order_iterative(const float* E, int64_t n_eff, int64_t m, int64_t 
   IterWs w;
   iter_ws_bytes(n_eff, m, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
+  if (m < 2) {                          // (otherwise the first precompute sets the status)
+    const int rc = begin(dev_status, s);
+    if (rc) return rc;
+  }
   return run_order_iterative(E, n_eff, m, lde, prec, m, order, margin, w, dev_status, s);
 }
 
@@ -209,8 +205,10 @@ int varlingam_order_hybrid(const float* E, int64_t n_eff, int64_t m, int64_t lde
   IterWs w;
   iter_ws_bytes(n_eff, m, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
+  if (m < 2) {                          // (otherwise the first precompute sets the status)
+    const int rc = begin(dev_status, s);
+    if (rc) return rc;
+  }
   return run_order_iterative(E, n_eff, m, lde, prec, k_exact, order, margin, w, dev_status, s);
 }
 
@@ -239,10 +237,8 @@ int pairwise_stats_save(const float* E, int64_t n_eff, int64_t m, int64_t lde, i
   PairwiseWs w;
   pairwise_ws_bytes(p, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
   double* cov = saved + 2 * m * m + 2 * m;
-  rc = run_pairwise(p, w, E, lde, prec, Hx, Hr, S, cov, saved, dev_status, s);
+  int rc = run_pairwise(p, w, E, lde, prec, Hx, Hr, S, cov, saved, dev_status, s);
   if (rc) return rc;
   const size_t d = sizeof(double);
   if (hipMemcpyAsync(saved + 2 * m * m, w.momx, 2 * m * d, hipMemcpyDeviceToDevice, s) ||
@@ -283,9 +279,7 @@ int approx_order(const double* S, int64_t m, int32_t* order, double* margin, voi
   if (m < 1 || m > kMaxOrderM) return VL_ERR_SHAPE;
   if (!ws || ws_bytes < approx_order_workspace_bytes(m) || !aligned256(ws)) return VL_ERR_WORKSPACE;
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
-  return run_order(S, m, order, margin, static_cast<double*>(ws), dev_status, s);
+  return run_order(S, m, order, margin, static_cast<double*>(ws), dev_status, s, true);
 }
 
 // ----------------------------------------------------------------------------------------
@@ -358,8 +352,6 @@ int varlingam_prune(const float* X, int64_t n, int64_t m, int64_t ldx, int p,
   PruneWs w;
   prune_ws_bytes(n, m, p, max_steps, ws, &w);
   hipStream_t s = as_stream(stream);
-  int rc = begin(dev_status, s);
-  if (rc) return rc;
   return run_prune(n, m, p, w, X, ldx, order, B0, Blag, max_steps, B0_out, Blag_out, info,
                    dev_status, s);
 }

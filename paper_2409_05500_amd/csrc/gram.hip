@@ -17,8 +17,9 @@ __global__ void reset_status_kernel(int32_t* st) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Column sums over K samples, split over row blocks: part[rs * ncol + c] (FP64), plus a
-// finiteness check.  Block = 256 threads = 64 columns x 4 row lanes.
+// Column sums over K samples, split over row blocks: part[rs * ncol + c] (FP64).  Block = 256
+// threads = 64 columns x 4 row lanes.  reset (nullable): a status word set to VL_OK (the call's
+// first kernel; this one raises nothing).
 // ------------------------------------------------------------------------------------------
 // kRange: also each column's minimum and maximum over the split, at part[splits ncol + ...]
 // and part[2 splits ncol + ...] (for the slice exponents).
@@ -29,8 +30,9 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
                                                              int64_t ncol, int64_t K,
                                                              int64_t rows_per_split,
                                                              double* __restrict__ part,
-                                                             int32_t* st) {
+                                                             int32_t* __restrict__ reset) {
   __shared__ double red[4][64];
+  if (reset && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *reset = VL_OK;
   __shared__ float rmin[kRange ? 4 : 1][64], rmax[kRange ? 4 : 1][64];
   const int cc = threadIdx.x & 63, rg = threadIdx.x >> 6;
   const int64_t c = (int64_t)blockIdx.x * 64 + cc;
@@ -38,7 +40,6 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
   const int64_t r1 = r0 + rows_per_split < K ? r0 + rows_per_split : K;
   double s = 0.0;
   float mn = INFINITY, mx = -INFINITY;
-  bool bad = false;
   if (c < ncol) {
     const float* p = A + (colmap ? colmap[c] : c);
     int64_t t = r0 + rg;
@@ -48,7 +49,6 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
       for (int q = 0; q < 8; ++q) v[q] = p[(t + 4 * q) * lda];
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        bad |= !isfinite(v[q]);
         s += (double)v[q];
         if constexpr (kRange) {
           mn = fminf(mn, v[q]);
@@ -58,7 +58,6 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
     }
     for (; t < r1; t += 4) {
       const float v = p[t * lda];
-      bad |= !isfinite(v);
       s += (double)v;
       if constexpr (kRange) {
         mn = fminf(mn, v);
@@ -66,7 +65,6 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
       }
     }
   }
-  if (bad) raise_status(st, VL_ERR_NONFINITE);
   red[rg][cc] = s;
   if constexpr (kRange) {
     rmin[rg][cc] = mn;
@@ -85,21 +83,28 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(const float* __rest
   }
 }
 
-// sum_{z < splits} P[z * stride + e] in split order.  Eight loads are issued before they are
-// added (the same sum): colmean_final has a few thousand threads at most, so their latency is
-// hidden by loads in flight, not by other waves.
+// f(z, v_z) for z < splits in order, v_z = P[z * stride + e], with kF loads in flight: these sums
+// run on a few thousand threads at most, so their latency is hidden by loads in flight, not by
+// other waves.  The last, partial group is loaded whole from clamped addresses.
+template <class F>
+__device__ inline void each_split(const double* __restrict__ P, int splits, int64_t stride,
+                                  int64_t e, F f) {
+  constexpr int kF = 16;
+  for (int z = 0; z < splits; z += kF) {
+    double v[kF];
+#pragma unroll
+    for (int q = 0; q < kF; ++q) v[q] = P[(int64_t)(z + q < splits ? z + q : splits - 1) * stride + e];
+#pragma unroll
+    for (int q = 0; q < kF; ++q)
+      if (z + q < splits) f(v[q]);
+  }
+}
+
+// sum_{z < splits} P[z * stride + e] in split order.
 __device__ inline double sum_splits_at(const double* __restrict__ P, int splits, int64_t stride,
                                        int64_t e) {
   double s = 0.0;
-  int z = 0;
-  for (; z + 8 <= splits; z += 8) {
-    double v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = P[(int64_t)(z + q) * stride + e];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) s += v[q];
-  }
-  for (; z < splits; ++z) s += P[(int64_t)z * stride + e];
+  each_split(P, splits, stride, e, [&](double v) { s += v; });
   return s;
 }
 
@@ -107,10 +112,13 @@ __global__ void colmean_final_kernel(const double* __restrict__ part, int64_t nc
                                      int64_t K, double* __restrict__ mean,
                                      double* __restrict__ rep, int64_t rep_m,
                                      int64_t rep_blocks, int32_t* __restrict__ range_exp,
-                                     int64_t centre_m, int32_t* __restrict__ range_exp_own) {
+                                     int64_t centre_m, int32_t* __restrict__ range_exp_own,
+                                     int32_t* st) {
   int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= ncol) return;
   const double v = sum_splits_at(part, splits, ncol, c) / (double)K;
+  // a NaN or infinity in the column makes its sum one (finite FP32 values cannot overflow FP64)
+  if (!isfinite(v)) raise_status(st, VL_ERR_NONFINITE);
   mean[c] = v;
   if (rep && c < rep_m)
     for (int64_t h = 0; h < rep_blocks; ++h) rep[h * rep_m + c] = v;
@@ -120,46 +128,31 @@ __global__ void colmean_final_kernel(const double* __restrict__ part, int64_t nc
     const int64_t sn = (int64_t)splits * ncol, c0 = c % centre_m;
     const double mu0 = c0 == c ? v : sum_splits_at(part, splits, ncol, c0) / (double)K;
     double mn = INFINITY, mx = -INFINITY;
-    int z = 0;
-    for (; z + 8 <= splits; z += 8) {      // eight of each in flight
-      double a[8], b[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        a[q] = part[sn + (int64_t)(z + q) * ncol + c];
-        b[q] = part[2 * sn + (int64_t)(z + q) * ncol + c];
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        mn = fmin(mn, a[q]);
-        mx = fmax(mx, b[q]);
-      }
-    }
-    for (; z < splits; ++z) {
-      mn = fmin(mn, part[sn + (int64_t)z * ncol + c]);
-      mx = fmax(mx, part[2 * sn + (int64_t)z * ncol + c]);
-    }
+    each_split(part + sn, splits, ncol, c, [&](double v) { mn = fmin(mn, v); });
+    each_split(part + 2 * sn, splits, ncol, c, [&](double v) { mx = fmax(mx, v); });
     range_exp[c] = exponent_of(fmax(mx - mu0, mu0 - mn));
     if (range_exp_own) range_exp_own[c] = exponent_of(fmax(mx - v, v - mn));
   }
 }
 
 int colmeans(const float* A, int64_t lda, const int64_t* colmap, int64_t ncol, int64_t K,
-             double* mean, double* scratch, int32_t* st, hipStream_t stream, double* rep,
-             int64_t rep_m, int64_t rep_blocks, int32_t* range_exp, int64_t centre_m,
-             int32_t* range_exp_own) {
+             double* mean, double* scratch, int32_t* st, hipStream_t stream, ColmeanOptions o) {
   const int splits = colmean_splits(K);
   const int64_t rows = ceil_div(K, splits);
   dim3 grid((unsigned)ceil_div(ncol, 64), (unsigned)splits);
-  if (range_exp)
-    colsum_partial_kernel<true><<<grid, 256, 0, stream>>>(A, lda, colmap, ncol, K, rows,
-                                                          scratch, st);
-  else
-    colsum_partial_kernel<false><<<grid, 256, 0, stream>>>(A, lda, colmap, ncol, K, rows,
-                                                           scratch, st);
-  VL_LAUNCH_CHECK();
-  colmean_final_kernel<<<(unsigned)ceil_div(ncol, 256), 256, 0, stream>>>(
-      scratch, ncol, splits, K, mean, rep, rep_m, rep_blocks, range_exp,
-      centre_m > 0 ? centre_m : ncol, range_exp_own);
+  int32_t* reset = o.reset ? st : nullptr;
+  if (!o.have_sums) {
+    if (o.range_exp)
+      colsum_partial_kernel<true><<<grid, 256, 0, stream>>>(A, lda, colmap, ncol, K, rows,
+                                                            scratch, reset);
+    else
+      colsum_partial_kernel<false><<<grid, 256, 0, stream>>>(A, lda, colmap, ncol, K, rows,
+                                                             scratch, reset);
+    VL_LAUNCH_CHECK();
+  }
+  colmean_final_kernel<<<(unsigned)ceil_div(ncol, 64), 64, 0, stream>>>(
+      scratch, ncol, splits, K, mean, o.rep, o.rep_m, o.rep_blocks, o.range_exp,
+      o.centre_m > 0 ? o.centre_m : ncol, o.range_exp_own, st);
   VL_LAUNCH_CHECK();
   return VL_OK;
 }

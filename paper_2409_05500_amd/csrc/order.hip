@@ -121,19 +121,23 @@ template <int R, int kThreads>
 __global__ __launch_bounds__(kThreads) void order_wave_kernel(const double* __restrict__ S, int64_t m,
                                                           int32_t* __restrict__ order,
                                                           double* __restrict__ margin,
-                                                          int32_t* st) {
+                                                          int32_t* st, int reset) {
+  if (reset) {                       // one workgroup: the status word before anything raises
+    if (threadIdx.x == 0) *st = VL_OK;
+    __syncthreads();
+  }
   order_wave_block<R, kThreads>(S, m, order, margin, st);
 }
 
 int run_order(const double* S, int64_t m, int32_t* order, double* margin, double* M0,
-              int32_t* st, hipStream_t stream) {
+              int32_t* st, hipStream_t stream, bool reset) {
   ProfileScope ps("order", stream);
   // 16 waves form M0 quickly; with more variables per lane the block is cut to 8 or 4 waves
   // so that the one sequential wave may hold them all in registers
 #define VL_ORDER_WAVE(R) \
   order_wave_kernel<R, (R <= 8 ? 1024 : (R <= 16 ? 512 : 256))> \
       <<<1, (R <= 8 ? 1024 : (R <= 16 ? 512 : 256)), 0, stream>>>( \
-      S, m, order, margin, st)
+      S, m, order, margin, st, reset ? 1 : 0)
   if (m <= 64) VL_ORDER_WAVE(1);
   else if (m <= 128) VL_ORDER_WAVE(2);
   else if (m <= 256) VL_ORDER_WAVE(4);
@@ -142,6 +146,10 @@ int run_order(const double* S, int64_t m, int32_t* order, double* margin, double
   else if (m <= 2048) VL_ORDER_WAVE(32);
   else if (m <= 4096) VL_ORDER_WAVE(64);
   else {
+    if (reset) {
+      reset_status_kernel<<<1, 64, 0, stream>>>(st);
+      VL_LAUNCH_CHECK();
+    }
     order_init_kernel<<<(unsigned)ceil_div(m, 4), 256, 0, stream>>>(S, m, M0, st);
     VL_LAUNCH_CHECK();
     order_kernel<1024, 16><<<1, 1024, 0, stream>>>(S, m, M0, order, margin);

@@ -245,13 +245,16 @@ static int launch_moments(const PairwisePlan& p, const PairwiseWs& w, const floa
 
 int run_pairwise(const PairwisePlan& p, const PairwiseWs& w, const float* E, int64_t lde,
                  int prec, double* Hx, double* Hr, double* S, double* Cov, double* mom,
-                 int32_t* st, hipStream_t stream) {
+                 int32_t* st, hipStream_t stream, PairwiseStart start) {
   const int64_t m = p.m, n_eff = p.n_eff;
   double* cov = Cov ? Cov : w.cov;
   {
     ProfileScope ps("pairwise_cov", stream);
-    int rc = colmeans(E, lde, nullptr, m, n_eff, w.mu, w.scratch, st, stream, nullptr, 0, 0,
-                      p.sliced ? w.ex : nullptr);
+    ColmeanOptions o;
+    o.reset = start != PairwiseStart::kContinue;
+    o.have_sums = start == PairwiseStart::kContinue;
+    if (p.sliced) o.range_exp = w.ex;
+    int rc = colmeans(E, lde, nullptr, m, n_eff, w.mu, w.scratch, st, stream, o);
     if (rc) return rc;
     if (p.sliced) {
       // the covariance from int8 slices of E's centred columns

@@ -45,11 +45,15 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out);
 int standardize_to(const float* E, int64_t lde, int64_t n_eff, int64_t m, const double* mu,
                    const double* cov, float* Xs, int64_t n_pad, int64_t m_pad, int32_t* st,
                    hipStream_t stream, int32_t* zero = nullptr, int64_t nzero = 0);
+// kFirst: the call's first kernels (the status word is set to VL_OK); kContinue: a step of a call
+// under way, with the splits' column sums of E already in the workspace's scratch.
+enum class PairwiseStart { kFirst, kContinue };
+
 // mom (nullable): 2 m^2 doubles, (A, B) per ordered pair, for tests and the backward pass.
 // prec: the covariance's arithmetic (VL_PREC_FP32 or another precision, possibly with the
 // VL_PAIRWISE_COMPENSATED bit, which the plan also carries).
 int run_pairwise(const PairwisePlan& p, const PairwiseWs& w, const float* E, int64_t lde,
                  int prec, double* Hx, double* Hr, double* S, double* Cov, double* mom,
-                 int32_t* st, hipStream_t stream);
+                 int32_t* st, hipStream_t stream, PairwiseStart start = PairwiseStart::kFirst);
 
 }  // namespace vl

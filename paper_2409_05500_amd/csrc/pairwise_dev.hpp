@@ -29,11 +29,20 @@ __device__ inline void standardize_tile(
     mui = mu[i];
     inv = var > 0.0 ? 1.0 / sqrt(var) : 0.0;
   }
-  for (int r = ty; r < 64; r += 4) {
-    const int64_t t = t0 + r;
-    float v = 0.f;
-    if (i < m && t < n_eff) v = (float)(((double)E[t * lde + i] - mui) * inv);
-    tile[r][tx] = v;
+  // every load of the tile in flight at once (clamped addresses; a load under the bounds test
+  // would be waited for in turn)
+  float ev[16];
+  const float* Ei = E + (i < m ? i : m - 1);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int64_t t = t0 + ty + 4 * q;
+    ev[q] = Ei[(t < n_eff ? t : n_eff - 1) * lde];
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = ty + 4 * q;
+    const float v = (float)(((double)ev[q] - mui) * inv);
+    tile[r][tx] = i < m && t0 + r < n_eff ? v : 0.f;
   }
   __syncthreads();
   for (int r = ty; r < 64; r += 4) {
@@ -66,7 +75,17 @@ __device__ inline void hx_block(const float* __restrict__ Xs, int64_t n_pad, int
 #pragma unroll
     for (int q = 0; q < 8; ++q) term(u[q]);
   }
-  for (; t < n_eff; t += NT) term(x[t]);
+  if (t < n_eff) {                           // the last few, in flight together as well
+    float u[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int64_t tq = t + q * NT;
+      u[q] = x[tq < n_eff ? tq : n_eff - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (t + q * NT < n_eff) term(u[q]);
+  }
   sa = wave_sum_d(sa);
   sb = wave_sum_d(sb);
   if ((threadIdx.x & 63) == 0) {

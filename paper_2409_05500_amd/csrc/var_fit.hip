@@ -333,9 +333,19 @@ static int var_normal_equations(const VarPlan& v, const VarWs& w, const float* X
     // MIXED also needs the lag-0 means once per lag block (mu0), written by the same pass
     // (sliced: with each lag-embedded column's range exponent about its lag-0 mean)
     const bool fp64 = gmode == GramMode::kFp64 && !v.sliced;
-    rc = colmeans(X, ldx, w.colmap, nc, n_eff, w.mu, w.scratch, st, stream,
-                  fp64 ? w.mu0 : nullptr, m, v.p + 1, v.sliced ? w.ex : nullptr, m,
-                  v.sliced ? w.ez : nullptr);
+    ColmeanOptions o;
+    o.reset = true;                     // (the column map before it raises nothing)
+    if (fp64) {
+      o.rep = w.mu0;
+      o.rep_m = m;
+      o.rep_blocks = v.p + 1;
+    }
+    if (v.sliced) {
+      o.range_exp = w.ex;
+      o.centre_m = m;
+      o.range_exp_own = w.ez;
+    }
+    rc = colmeans(X, ldx, w.colmap, nc, n_eff, w.mu, w.scratch, st, stream, o);
     if (rc) return rc;
     if (v.sliced) {
       // the same lag products F from int8 slices of the series centred by the lag-0 means
@@ -388,7 +398,9 @@ int lag_covariance(int64_t n, int64_t m, int p, const float* X, int64_t ldx,
   const int64_t nc = m * (p + 1), n_eff = n - p;
   lag_colmap_kernel<<<(unsigned)ceil_div(nc, 256), 256, 0, stream>>>(m, p, ldx, colmap, order);
   VL_LAUNCH_CHECK();
-  int rc = colmeans(X, ldx, colmap, nc, n_eff, mu, scratch, st, stream);
+  ColmeanOptions o;
+  o.reset = true;
+  int rc = colmeans(X, ldx, colmap, nc, n_eff, mu, scratch, st, stream, o);
   if (rc) return rc;
   return gram_tn(X, ldx, colmap, mu, nc, X, ldx, colmap, mu, nc, n_eff, GramMode::kFp64, 1.0, C,
                  nc, scratch, stream, true);

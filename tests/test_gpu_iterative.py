@@ -135,3 +135,33 @@ def test_hybrid_recovers_the_generating_order(api):
         viol = [(i, j) for i in range(8) for j in range(8)
                 if inst.B0[i, j] != 0 and pos[j] > pos[i]]
         assert (viol == []) == (k >= 2), (k, viol)
+
+
+@pytest.mark.parametrize("m,n", [(2, 5), (2, 131), (3, 255), (10, 256), (64, 384), (65, 515),
+                                 (66, 900), (129, 1290), (260, 700)])
+def test_iterative_steps_at_the_edges(api, m, n):
+    """Step by step against the precompute and a host refinement, at the edges of the refinement's
+    grid (64 columns by 128 rows), of its groups of rows and of the selection's column slices.
+    Both sides score (nearly) the same FP32 data: a rounding of the refined data that falls the
+    other way moves S by 1e-7 / n at most, so M (m squares of scores of order 1) by less than 1e-6;
+    a pick may differ only inside that."""
+    rng = np.random.default_rng(100 * m + n)
+    D = (rng.laplace(size=(n, m)) @ (np.eye(m) + 0.3 * rng.standard_normal((m, m)) / np.sqrt(m))
+         ).astype(np.float32)
+    order, margin = (v.cpu().numpy() for v in api.order_iterative(torch.from_numpy(D).cuda()))
+    assert sorted(order.tolist()) == list(range(m)) and np.isinf(margin[-1])
+    idx = np.arange(m)
+    steps = m - 1 if m <= 66 else 40
+    for k in range(steps):
+        _, _, S, _ = api.pairwise_stats(torch.from_numpy(np.ascontiguousarray(D)).cuda())
+        M = (np.minimum(S.cpu().numpy(), 0.0) ** 2).sum(axis=1)
+        r = np.sort(M)
+        assert abs((r[1] - r[0]) - margin[k]) <= 1e-6, k
+        c = int(np.where(idx == order[k])[0][0])
+        assert M[c] - r[0] <= 1e-6, k
+        X = D.astype(np.float64)
+        Z = (X - X.mean(axis=0)) / X.std(axis=0)
+        rho = (Z * Z[:, [c]]).mean(axis=0)
+        keep = np.arange(len(idx)) != c
+        D = (Z - rho * Z[:, [c]])[:, keep].astype(np.float32)
+        idx = idx[keep]
