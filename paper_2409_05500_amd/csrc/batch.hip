@@ -63,12 +63,12 @@ struct BInst {
   float* Xs;
   float2* coef;
   float *partU, *partB;
-  int32_t* clist;   // near-collinear tile flags, count, list (2 tiles + 1)
+  int32_t* clist;   // near-collinear tile flags
   double *P, *Linv, *bchol;
 };
 
-enum BMap { kMapColVar, kMapColE, kMapGramVar, kMapGramCov, kMapResid, kMapStd, kMapPrep,
-            kMapMom, kMapComb, kMapVarChol0, kMapBChol0 = kMapVarChol0 + kMaxCholSteps,
+enum BMap { kMapColVar, kMapColE, kMapGramVar, kMapGramCov, kMapResid, kMapStd, kMapMom,
+            kMapComb, kMapVarChol0, kMapBChol0 = kMapVarChol0 + kMaxCholSteps,
             kMapVarBack = kMapBChol0 + kMaxCholSteps, kMapBlag, kNumMaps };
 
 struct BTables {
@@ -158,46 +158,46 @@ __global__ void bat_reset_kernel(int32_t* st, int count) {
   if (i < count) st[i] = VL_OK;
 }
 
-// Column means over all n_eff rows, 64 columns per block; which = 0: the lag map of X (VAR),
-// 1: the residuals E.  Raises VL_ERR_NONFINITE.
-__global__ __launch_bounds__(256) void bat_colmeans_kernel(BTables T, int which, int32_t* st0) {
+// Column means over all n_eff rows, 64 columns by kColLanes row lanes per block, each with 16
+// loads in flight from a stepped pointer; which = 0: the lag map of X (VAR), 1: the residuals E.
+// Raises VL_ERR_NONFINITE (a NaN or infinity in a column makes its sum one).
+constexpr int kColLanes = 16;
+
+__global__ __launch_bounds__(64 * kColLanes) void bat_colmeans_kernel(BTables T, int which,
+                                                                      int32_t* st0) {
   int64_t lb;
   const int b = bat_locate(T, which ? kMapColE : kMapColVar, blockIdx.x, lb);
   const BInst d = block_inst(T.inst + b);
-  __shared__ double red[4][64];
+  __shared__ double red[kColLanes][64];
   const int cc = threadIdx.x & 63, rg = threadIdx.x >> 6;
   const float* A = which ? d.E : d.X;
   const int64_t lda = which ? d.lde : d.ldx;
   const int64_t ncol = which ? d.m : d.nc;
   const int64_t c = lb * 64 + cc;
   double s = 0.0;
-  bool bad = false;
   if (c < ncol) {
-    const float* p = A + (which ? c : d.colmap[c]);
-    const int64_t n_eff = d.n_eff;
+    const int64_t n_eff = d.n_eff, step = kColLanes * lda;
+    const float* p = A + (which ? c : d.colmap[c]) + rg * lda;
     int64_t t = rg;
-    for (; t + 28 < n_eff; t += 32) {                 // eight loads in flight per thread
-      float v[8];
+    for (; t + 15 * kColLanes < n_eff; t += 16 * kColLanes) {
+      float v[16];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = p[(t + 4 * u) * lda];
+      for (int u = 0; u < 16; ++u, p += step) v[u] = *p;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        bad |= !isfinite(v[u]);
-        s += (double)v[u];
-      }
+      for (int u = 0; u < 16; ++u) s += (double)v[u];
     }
-    for (; t < n_eff; t += 4) {
-      const float v = p[t * lda];
-      bad |= !isfinite(v);
-      s += (double)v;
-    }
+    for (; t < n_eff; t += kColLanes, p += step) s += (double)*p;
   }
-  if (bad) raise_status(st0 + b, VL_ERR_NONFINITE);
   red[rg][cc] = s;
   __syncthreads();
-  if (rg == 0 && c < ncol)
-    (which ? d.emu : d.mu)[c] =
-        (((red[0][cc] + red[1][cc]) + red[2][cc]) + red[3][cc]) / (double)d.n_eff;
+  if (rg == 0 && c < ncol) {
+    double v = red[0][cc];
+#pragma unroll
+    for (int q = 1; q < kColLanes; ++q) v += red[q][cc];
+    v /= (double)d.n_eff;
+    if (!isfinite(v)) raise_status(st0 + b, VL_ERR_NONFINITE);
+    (which ? d.emu : d.mu)[c] = v;
+  }
 }
 
 // Centred Gram tiles over all samples.  which = 0: the lower-triangle tiles of G = Zc^T Zc
@@ -308,108 +308,174 @@ __global__ __launch_bounds__(256) void bat_back_kernel(BTables T) {
                  (lb / tn) * 32, (lb % tn) * 32);
 }
 
-// One workgroup per problem: lag matrices, intercept and (FP32 mode) the FP32 coefficients.
+// kPostParts workgroups per problem: lag matrices, intercept (64 variables a workgroup, its waves
+// over a quarter of the lags each) and (FP32 mode) the FP32 coefficients.  One workgroup per
+// problem waited for one load after another (256 problems, m 20-200: 133 us, now 52).
+constexpr int kPostParts = kBatchMaxM / 64;
+
 __global__ __launch_bounds__(256) void bat_var_post_kernel(const BInst* __restrict__ I) {
   const BInst d = block_inst(I + blockIdx.x);
   const int64_t m = d.m, dz = d.dz;
-  const int tid = threadIdx.x;
-  for (int64_t e = tid; e < (int64_t)d.p * m * m; e += 256) {
-    const int64_t tau1 = e / (m * m), rem = e % (m * m), i = rem / m, k = rem % m;
-    d.M[e] = d.Coef[(tau1 * m + k) * m + i];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double* C = d.Coef;
+  double* M = d.M;
+  constexpr int kU = 4;
+  // M[tau][i][k] = Coef[tau m + k][i], a row (tau, i) per wave
+  for (int64_t r = (int64_t)blockIdx.y * 4 + wave; r < d.p * m; r += 4 * kPostParts) {
+    const int64_t tau = r / m, i = r - tau * m;
+    const double* Cr = C + tau * m * m + i;
+    double v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t k = lane + 64 * u;
+      v[u] = Cr[(k < m ? k : m - 1) * m];
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u)
+      if (lane + 64 * u < m) M[r * m + lane + 64 * u] = v[u];
   }
-  for (int64_t i = tid; i < m; i += 256) {
-    double s = 0.0;
-    for (int64_t k = 0; k < dz; ++k) s += d.Coef[k * m + i] * d.mu[m + k];
-    d.intercept[i] = d.mu[i] - s;
+  __shared__ double red[4][64];
+  const int64_t i = (int64_t)blockIdx.y * 64 + lane, ic = i < m ? i : m - 1;
+  double s = 0.0;
+  for (int64_t k0 = wave; k0 < dz; k0 += 4 * 16) {
+    double c[16], x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int64_t k = k0 + 4 * u < dz ? k0 + 4 * u : dz - 1;
+      c[u] = C[k * m + ic];
+      x[u] = d.mu[m + k];
+    }
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (k0 + 4 * u < dz) s += c[u] * x[u];
   }
+  red[wave][lane] = s;
+  __syncthreads();
+  if (wave == 0 && i < m)
+    d.intercept[i] = d.mu[i] - (((red[0][lane] + red[1][lane]) + red[2][lane]) + red[3][lane]);
   if (d.fp32)
-    for (int64_t e = tid; e < dz * m; e += 256) d.CoefF[e] = (float)d.Coef[e];
+    for (int64_t e = (int64_t)blockIdx.y * 256 + threadIdx.x; e < dz * m; e += 256 * kPostParts)
+      d.CoefF[e] = (float)C[e];
 }
 
-template <bool kFp64>
-__global__ __launch_bounds__(256) void bat_var_residual_kernel(BTables T) {
+// FP32 residual: tiles of 64 samples x 64 variables.
+__global__ __launch_bounds__(256) void bat_var_residual_f32_kernel(BTables T) {
   int64_t lb;
   const int b = bat_locate(T, kMapResid, blockIdx.x, lb);
   const BInst d = block_inst(T.inst + b);
   const int64_t tm = ceil_div(d.m, 64);
-  const int64_t t0 = (lb / tm) * 64, j0 = (lb % tm) * 64;
-  if (kFp64)
-    var_residual_tile_f64<float>(d.X, d.ldx, d.colmap, d.mu, d.m, d.p, d.n_eff, d.Coef, d.E,
-                                 d.lde, t0, j0);
-  else
-    var_residual_tile_f32(d.X, d.ldx, d.colmap, d.mu, d.m, d.p, d.n_eff, d.CoefF, d.E, d.lde, t0,
-                          j0);
+  var_residual_tile_f32(d.X, d.ldx, d.colmap, d.mu, d.m, d.p, d.n_eff, d.CoefF, d.E, d.lde,
+                        (lb / tm) * 64, (lb % tm) * 64);
 }
 
+// FP64 residual: a workgroup's four waves take 64 samples x 64 variables each, one after another
+// in the samples (kRows = 256), or a quarter of one such tile each (kRows = 64).
+template <int kRows>
+__global__ __launch_bounds__(256, 2) void bat_var_residual_kernel(BTables T) {
+  int64_t lb;
+  const int b = bat_locate(T, kMapResid, blockIdx.x, lb);
+  const BInst d = block_inst(T.inst + b);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t tm = ceil_div(d.m, 64);
+  const int64_t t0 = (lb / tm) * kRows, j0 = (lb % tm) * 64;
+  const int64_t tw = t0 + 64 * wave;
+  if constexpr (kRows == 64) {
+    var_residual_wave_f64<2, 2>(d.X, d.ldx, d.colmap, d.mu, d.m, d.p, d.n_eff, d.Coef, d.E, d.lde,
+                                t0 + 32 * (wave >> 1), j0 + 32 * (wave & 1));
+  } else if (d.m >= 16 && d.n_eff >= 64) {
+    if (tw >= d.n_eff) return;
+    const int m = (int)d.m, j = (int)j0;
+    switch (m - j >= 64 ? 4 : (m - j + 15) / 16) {
+      case 1:
+        return var_residual_wide_f64<1>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+      case 2:
+        return var_residual_wide_f64<2>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+      case 3:
+        return var_residual_wide_f64<3>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+      default:
+        return var_residual_wide_f64<4>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+    }
+  } else {
+    for (int q = 0; q < 4; ++q)
+      var_residual_wave_f64<2, 2>(d.X, d.ldx, d.colmap, d.mu, d.m, d.p, d.n_eff, d.Coef, d.E,
+                                  d.lde, tw + 32 * (q >> 1), j0 + 32 * (q & 1));
+  }
+}
+
+// A problem's standardisation tiles, then its pair coefficients, 256 entries per block.
 __global__ __launch_bounds__(256) void bat_standardize_kernel(BTables T, int32_t* st0) {
   int64_t lb;
   const int b = bat_locate(T, kMapStd, blockIdx.x, lb);
   const BInst d = block_inst(T.inst + b);
-  const int64_t gx = ceil_div(d.n_pad, 64);
-  standardize_tile(d.E, d.lde, d.n_eff, d.m, d.emu, d.cov, d.Xs, d.n_pad, d.m_pad, st0 + b,
-                   (lb % gx) * 64, (lb / gx) * 64, d.clist, d.tiles + 1, lb,
-                   gx * ceil_div(d.m_pad, 64));
-}
-
-// Blocks [0, m): Hx of variable lb; then the pair coefficients, 256 entries per block.
-__global__ __launch_bounds__(256) void bat_prep_kernel(BTables T, int32_t* st0) {
-  int64_t lb;
-  const int b = bat_locate(T, kMapPrep, blockIdx.x, lb);
-  const BInst d = block_inst(T.inst + b);
-  if (lb < d.m)
-    hx_block<256>(d.Xs, d.n_pad, d.n_eff, d.Hx, d.momx, lb);
+  const int64_t gx = ceil_div(d.n_pad, 64), nstd = gx * ceil_div(d.m_pad, 64);
+  if (lb < nstd)
+    standardize_tile(d.E, d.lde, d.n_eff, d.m, d.emu, d.cov, d.Xs, d.n_pad, d.m_pad, st0 + b,
+                     (lb % gx) * 64, (lb / gx) * 64);
   else
-    pair_coef_elem(d.cov, d.m, d.m_pad, d.coef, d.nt, d.tiles, d.clist, st0 + b,
-                   (lb - d.m) * 256 + threadIdx.x);
+    pair_coef_elem(d.cov, d.m, d.m_pad, d.coef, d.nt, d.clist, st0 + b,
+                   (lb - nstd) * 256 + threadIdx.x);
 }
 
 // The pairwise-moment items of all problems, in the table's longest-first order (no XCD
-// remap: that would hand one XCD all the long items).
+// remap: that would hand one XCD all the long items).  A problem's first blocks form its Hx, one a
+// variable.
 __global__ __launch_bounds__(256) void bat_moments_kernel(BTables T, int64_t total) {
   const int64_t g = blockIdx.x;
   if (g >= total) return;
   int64_t lb;
   const int b = bat_locate(T, kMapMom, g, lb);
   const BInst d = block_inst(T.inst + b);
+  if (lb < d.m) {
+    hx_block<256>(d.Xs, d.n_pad, d.n_eff, d.Hx, d.momx, lb);
+    return;
+  }
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t item = lb * 4 + wave;
+  const int64_t item = (lb - d.m) * 4 + wave;
   if (item >= d.items) return;
   pairwise_moments_item(d.Xs, d.n_pad, d.coef, d.m_pad, d.m, d.nt, d.tiles, d.chunk_len, item,
                         d.partU, d.partB);
 }
 
-// The listed near-collinear tiles of problem blockIdx.x, recomputed after the moment kernel
-// (one workgroup per problem, grid-stride over its list).
+// The flagged near-collinear tiles of problem blockIdx.x, recomputed after the moment kernel (one
+// workgroup per problem; every wave looks through all flags and takes every fourth item).
 __global__ __launch_bounds__(256) void bat_collinear_kernel(const BInst* __restrict__ I) {
   const BInst d = block_inst(I + blockIdx.x);
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t total = (int64_t)d.clist[d.tiles] * d.nchunk;
-  for (int64_t w = wave; w < total; w += 4) {
-    const int64_t tile = d.clist[d.tiles + 1 + w / d.nchunk], chunk = w % d.nchunk;
-    pairwise_collinear_item(d.E, d.lde, d.n_eff, d.emu, d.cov, d.m, d.nt, d.chunk_len, tile,
-                            chunk, d.partU, d.partB);
+  constexpr int kF = 8;                               // groups of 64 flags in flight
+  int count = 0;
+  for (int64_t t0 = 0; t0 < d.tiles; t0 += 64 * kF) {
+    int32_t f[kF];
+#pragma unroll
+    for (int q = 0; q < kF; ++q) {
+      const int64_t t = t0 + 64 * q + lane;
+      f[q] = d.clist[t < d.tiles ? t : d.tiles - 1];
+    }
+    for (int q = 0; q < kF; ++q) {
+      int32_t fq = f[0];
+#pragma unroll
+      for (int k = 1; k < kF; ++k) fq = q == k ? f[k] : fq;
+      uint64_t hit = __ballot(t0 + 64 * q + lane < d.tiles && fq != 0);
+      for (; hit; hit &= hit - 1) {
+        const int64_t tile = t0 + 64 * q + __ffsll((unsigned long long)hit) - 1;
+        for (int chunk = 0; chunk < d.nchunk; ++chunk)
+          if ((count++ & 3) == wave)
+            pairwise_collinear_item(d.E, d.lde, d.n_eff, d.emu, d.cov, d.m, d.nt, d.chunk_len,
+                                    tile, chunk, d.partU, d.partB);
+      }
+    }
   }
 }
 
-// Per unordered pair (one thread at i <= j): Hr of both orders, then S[i][j] and S[j][i] with
-// the single-problem formula.
-__global__ __launch_bounds__(256) void bat_combine_kernel(BTables T) {
+__global__ __launch_bounds__(kCS* kCS) void bat_combine_kernel(BTables T) {
   int64_t lb;
   const int b = bat_locate(T, kMapComb, blockIdx.x, lb);
   const BInst d = block_inst(T.inst + b);
-  const int64_t m = d.m, e = lb * 256 + threadIdx.x;
-  if (e >= m * m) return;
-  const int64_t i = e / m, j = e % m;
-  if (i > j) return;
-  combine_hr_elem(d.partU, d.partB, d.nchunk, m, d.n_eff, d.Hr, nullptr, e);
-  if (i == j) {
-    d.S[e] = 0.0;
-    return;
-  }
-  const int64_t e2 = j * m + i;
-  combine_hr_elem(d.partU, d.partB, d.nchunk, m, d.n_eff, d.Hr, nullptr, e2);
-  d.S[e] = (d.Hx[j] + d.Hr[e]) - (d.Hx[i] + d.Hr[e2]);
-  d.S[e2] = (d.Hx[i] + d.Hr[e2]) - (d.Hx[j] + d.Hr[e]);
+  int bi, bj;
+  tile_coords(lb, (int)ceil_div(d.m, (int64_t)kCS), bi, bj);
+  combine_score_block(d.partU, d.partB, d.nchunk, d.m, d.n_eff, d.Hx, d.Hr, (double*)nullptr, d.S,
+                      bi, bj);
 }
 
 // One workgroup per problem: the ordering, then B0 from the LDL^T of the order-permuted
@@ -423,36 +489,75 @@ __global__ __launch_bounds__(256) void bat_order_kernel(const BInst* __restrict_
   const int64_t m = d.m;
   const int tid = threadIdx.x;
   order_wave_block<kBatchMaxM / 64, 256>(d.S, m, d.order, d.margin, st);
-  __shared__ int seen[kBatchMaxM];
-  for (int64_t a = tid; a < m; a += 256) seen[a] = 0;
+  __shared__ int seen[kBatchMaxM], Ks[kBatchMaxM];
+  for (int64_t a = tid; a < m; a += 256) {
+    seen[a] = 0;
+    Ks[a] = d.order[a];
+  }
   __syncthreads();
-  const int32_t* K = d.order;
-  for (int64_t e = tid; e < m * m; e += 256) {
-    const int64_t a = e / m, c = e % m;
-    const int32_t ka = K[a], kc = K[c];
-    if (ka < 0 || ka >= m || kc < 0 || kc >= m) {
-      raise_status(st, VL_ERR_INVALID_ARG);
-      d.P[e] = a == c ? 1.0 : 0.0;
-      continue;
-    }
-    d.P[e] = d.cov[(int64_t)ka * m + kc];
-    if (c == 0) atomicAdd(&seen[ka], 1);
+  // the permuted covariance, four rows a wave at a time, every load of them in flight (an element
+  // a thread had the kernel at 258 us for 256 problems, now 157)
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  constexpr int kR = 4, kU = kBatchMaxM / 64;
+  const double* cov = d.cov;
+  double* P = d.P;
+  for (int64_t a0 = kR * wave; a0 < m; a0 += kR * 4) {
+    double v[kR][kU];
+    bool ok[kR][kU];
+#pragma unroll
+    for (int r = 0; r < kR; ++r)
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t a = a0 + r < m ? a0 + r : m - 1, c = lane + 64 * u < m ? lane + 64 * u : m - 1;
+        const int32_t ka = Ks[a], kc = Ks[c];
+        ok[r][u] = ka >= 0 && ka < m && kc >= 0 && kc < m;
+        v[r][u] = cov[ok[r][u] ? (int64_t)ka * m + kc : 0];
+      }
+#pragma unroll
+    for (int r = 0; r < kR; ++r)
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t a = a0 + r, c = lane + 64 * u;
+        if (a < m && c < m) {
+          P[a * m + c] = ok[r][u] ? v[r][u] : (a == c ? 1.0 : 0.0);
+          if (!ok[r][u]) raise_status(st, VL_ERR_INVALID_ARG);
+          else if (c == 0) atomicAdd(&seen[Ks[a]], 1);
+        }
+      }
   }
   __syncthreads();
   for (int64_t a = tid; a < m; a += 256)
     if (seen[a] != 1) raise_status(st, VL_ERR_INVALID_ARG);
 }
 
-// One workgroup per problem: B0[K_a][K_b] = -Linv[a][b] / Linv[a][a] for b < a, else 0.
+// B0[K_a][K_b] = -Linv[a][b] / Linv[a][a] for b < a, else 0: kB0Parts workgroups per problem, a
+// row a wave (one workgroup per problem, an element a thread: 101 us at 256 problems, now 22).
+constexpr int kB0Parts = 4;
+
 __global__ __launch_bounds__(256) void bat_b0_kernel(const BInst* __restrict__ I) {
   const BInst d = block_inst(I + blockIdx.x);
   const int64_t m = d.m;
   const int32_t* K = d.order;
-  for (int64_t e = threadIdx.x; e < m * m; e += 256) {
-    const int64_t a = e / m, c = e % m;
-    const int32_t ka = K[a], kc = K[c];
-    if (ka < 0 || ka >= m || kc < 0 || kc >= m) continue;
-    d.B0[(int64_t)ka * m + kc] = c < a ? -d.Linv[a * m + c] / d.Linv[a * m + a] : 0.0;
+  const double* L = d.Linv;
+  double* B0 = d.B0;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  constexpr int kU = kBatchMaxM / 64;
+  int32_t kc[kU];
+#pragma unroll
+  for (int u = 0; u < kU; ++u) kc[u] = K[lane + 64 * u < m ? lane + 64 * u : m - 1];
+  for (int64_t a = (int64_t)blockIdx.y * 4 + wave; a < m; a += 4 * kB0Parts) {
+    const int32_t ka = K[a];
+    const double diag = L[a * m + a];
+    double v[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) v[u] = L[a * m + (lane + 64 * u < m ? lane + 64 * u : m - 1)];
+    if (ka < 0 || ka >= m) continue;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t c = lane + 64 * u;
+      if (c < m && kc[u] >= 0 && kc[u] < m) B0[(int64_t)ka * m + kc[u]] = c < a ? -v[u] / diag : 0.0;
+    }
   }
 }
 
@@ -493,7 +598,7 @@ int bucket_of(const vl_instance& in) {
 struct InstLayout {
   size_t off = 0;                 // byte offset of this problem's slice in the workspace
   size_t cmap_off = 0;            // byte offset of its lag column map (in the table region)
-  int nt = 0, nchunk = 0, chunk_len = 0;
+  int nt = 0, nchunk = 0, chunk_len = 0, resid_rows = 64;
   int64_t m_pad = 0, tiles = 0, n_pad = 0, items = 0;
 };
 
@@ -521,7 +626,7 @@ size_t carve_inst(const vl_instance& in, const InstLayout& L, char* base, BInst*
   t.coef = c.take<float2>(L.m_pad * L.m_pad);
   t.partU = c.take<float>((size_t)L.nchunk * m * m);
   t.partB = c.take<float>((size_t)L.nchunk * m * m);
-  t.clist = c.take<int32_t>(2 * L.tiles + 1);
+  t.clist = c.take<int32_t>(L.tiles);
   t.P = c.take<double>(m * m);
   t.Linv = c.take<double>(m * m);
   t.bchol = c.take<double>(chol_ws_doubles_dev(m));
@@ -552,11 +657,11 @@ int64_t blocks_for(int map, const vl_instance& in, const InstLayout& L) {
     case kMapGramVar: return ceil_div(dz, 64) * (ceil_div(dz, 64) + 1) / 2 +
                              ceil_div(dz, 64) * ceil_div(m, 64);
     case kMapGramCov: return ceil_div(m, 64) * (ceil_div(m, 64) + 1) / 2;
-    case kMapResid: return ceil_div(m, 64) * ceil_div(n_eff, 64);
-    case kMapStd: return ceil_div(L.n_pad, 64) * ceil_div(L.m_pad, 64);
-    case kMapPrep: return m + ceil_div(L.m_pad * L.m_pad, 256);
-    case kMapMom: return ceil_div(L.items, 4);
-    case kMapComb: return ceil_div(m * m, 256);
+    case kMapResid: return ceil_div(m, 64) * ceil_div(n_eff, (int64_t)L.resid_rows);
+    case kMapStd: return ceil_div(L.n_pad, 64) * ceil_div(L.m_pad, 64) +
+                         ceil_div(coef_threads(L.nt), 256);
+    case kMapMom: return m + ceil_div(L.items, 4);
+    case kMapComb: return ceil_div(m, (int64_t)kCS) * (ceil_div(m, (int64_t)kCS) + 1) / 2;
     case kMapVarBack: return ceil_div(dz, 32) * ceil_div(m, 32);
     case kMapBlag: return (int64_t)in.p * ceil_div(m, 32) * ceil_div(m, 32);
   }
@@ -585,6 +690,7 @@ struct vl_batch {
   size_t tab_off[kNumMaps * 2] = {};  // byte offsets of the bmap / first arrays
   size_t slices_off = 0;                // end of the tables and column maps
   void* bound = nullptr;
+  int resid_rows = 64;       // samples per residual workgroup (64 or 256)
 };
 
 namespace {
@@ -593,11 +699,21 @@ namespace {
 size_t build_layout(vl_batch* B) {
   const int n = B->count;
   B->lay.resize(n);
+  // FP64 residual: tiles of one wave each from 1.5 waves for every SIMD on, else a quarter of a
+  // tile a wave (quarter / whole, in us, at 500, 1000, 2000 and 4000 tiles of problems with m
+  // 60-130: 18 / 23, 31 / 42, 52 / 46, 107 / 99).
+  int64_t tiles = 0;
+  for (const vl_instance& in : B->inst)
+    tiles += ceil_div(in.m, (int64_t)64) * ceil_div(in.n - in.p, (int64_t)64);
+  B->resid_rows = B->prec != VL_PREC_FP32 && tiles >= 3 * 512 ? 256 : 64;
   size_t used = round_up((int64_t)(n * sizeof(BInst)), 256);
   for (int k = 0; k < kNumMaps; ++k) {
     int64_t tot = 0;
     for (int b = 0; b < n; ++b) {
-      if (k == 0) B->lay[b] = layout_for(B->inst[b], B->chunk[bucket_of(B->inst[b])]);
+      if (k == 0) {
+        B->lay[b] = layout_for(B->inst[b], B->chunk[bucket_of(B->inst[b])]);
+        B->lay[b].resid_rows = B->resid_rows;
+      }
       tot += blocks_for(k, B->inst[b], B->lay[b]);
     }
     B->total[k] = tot;
@@ -734,7 +850,7 @@ int launch_fit(const vl_batch* B, void* ws, int32_t* st, hipStream_t s) {
   VL_LAUNCH_CHECK();
   {
     ProfileScope ps("batch_var", s);
-    bat_colmeans_kernel<<<(unsigned)B->total[kMapColVar], 256, 0, s>>>(T, 0, st);
+    bat_colmeans_kernel<<<(unsigned)B->total[kMapColVar], 64 * kColLanes, 0, s>>>(T, 0, st);
     VL_LAUNCH_CHECK();
     if (f64) bat_gram_kernel<true><<<(unsigned)B->total[kMapGramVar], 256, 0, s>>>(T, 0);
     else bat_gram_kernel<false><<<(unsigned)B->total[kMapGramVar], 256, 0, s>>>(T, 0);
@@ -748,22 +864,22 @@ int launch_fit(const vl_batch* B, void* ws, int32_t* st, hipStream_t s) {
     }
     bat_back_kernel<<<(unsigned)B->total[kMapVarBack], 256, 0, s>>>(T);
     VL_LAUNCH_CHECK();
-    bat_var_post_kernel<<<(unsigned)n, 256, 0, s>>>(I);
+    bat_var_post_kernel<<<dim3((unsigned)n, kPostParts), 256, 0, s>>>(I);
     VL_LAUNCH_CHECK();
-    if (f64) bat_var_residual_kernel<true><<<(unsigned)B->total[kMapResid], 256, 0, s>>>(T);
-    else bat_var_residual_kernel<false><<<(unsigned)B->total[kMapResid], 256, 0, s>>>(T);
+    const unsigned nres = (unsigned)B->total[kMapResid];
+    if (!f64) bat_var_residual_f32_kernel<<<nres, 256, 0, s>>>(T);
+    else if (B->resid_rows == 256) bat_var_residual_kernel<256><<<nres, 256, 0, s>>>(T);
+    else bat_var_residual_kernel<64><<<nres, 256, 0, s>>>(T);
     VL_LAUNCH_CHECK();
   }
   {
     ProfileScope ps("batch_pairwise", s);
-    bat_colmeans_kernel<<<(unsigned)B->total[kMapColE], 256, 0, s>>>(T, 1, st);
+    bat_colmeans_kernel<<<(unsigned)B->total[kMapColE], 64 * kColLanes, 0, s>>>(T, 1, st);
     VL_LAUNCH_CHECK();
     if (f64) bat_gram_kernel<true><<<(unsigned)B->total[kMapGramCov], 256, 0, s>>>(T, 1);
     else bat_gram_kernel<false><<<(unsigned)B->total[kMapGramCov], 256, 0, s>>>(T, 1);
     VL_LAUNCH_CHECK();
     bat_standardize_kernel<<<(unsigned)B->total[kMapStd], 256, 0, s>>>(T, st);
-    VL_LAUNCH_CHECK();
-    bat_prep_kernel<<<(unsigned)B->total[kMapPrep], 256, 0, s>>>(T, st);
     VL_LAUNCH_CHECK();
   }
   {
@@ -776,7 +892,7 @@ int launch_fit(const vl_batch* B, void* ws, int32_t* st, hipStream_t s) {
   }
   {
     ProfileScope ps("batch_order_b", s);
-    bat_combine_kernel<<<(unsigned)B->total[kMapComb], 256, 0, s>>>(T);
+    bat_combine_kernel<<<(unsigned)B->total[kMapComb], kCS * kCS, 0, s>>>(T);
     VL_LAUNCH_CHECK();
     bat_order_kernel<<<(unsigned)n, 256, 0, s>>>(I, st);
     VL_LAUNCH_CHECK();
@@ -787,7 +903,7 @@ int launch_fit(const vl_batch* B, void* ws, int32_t* st, hipStream_t s) {
       bat_chol_step_kernel<<<(unsigned)B->total[kMapBChol0 + k], 256, 0, s>>>(T, 1, k, st);
       VL_LAUNCH_CHECK();
     }
-    bat_b0_kernel<<<(unsigned)n, 256, 0, s>>>(I);
+    bat_b0_kernel<<<dim3((unsigned)n, kB0Parts), 256, 0, s>>>(I);
     VL_LAUNCH_CHECK();
     bat_blag_kernel<<<(unsigned)B->total[kMapBlag], 256, 0, s>>>(T);
     VL_LAUNCH_CHECK();

@@ -28,34 +28,26 @@ namespace vl {
 // ------------------------------------------------------------------------------------------
 // Kernels (single problem): one body call per block / thread.
 // ------------------------------------------------------------------------------------------
+// The blocks from nstd on (coef != nullptr) form the pair coefficients and the collinear flags: they
+// need the covariance only, as the standardisation does.
 __global__ __launch_bounds__(256) void standardize_transpose_kernel(
     const float* __restrict__ E, int64_t lde, int64_t n_eff, int64_t m,
     const double* __restrict__ mu, const double* __restrict__ cov, float* __restrict__ Xs,
-    int64_t n_pad, int64_t m_pad, int32_t* st, int32_t* __restrict__ zero, int64_t nzero) {
-  standardize_tile(E, lde, n_eff, m, mu, cov, Xs, n_pad, m_pad, st, (int64_t)blockIdx.x * 64,
-                   (int64_t)blockIdx.y * 64, zero, nzero,
-                   (int64_t)blockIdx.y * gridDim.x + blockIdx.x, (int64_t)gridDim.x * gridDim.y);
+    int64_t n_pad, int64_t m_pad, int32_t* st, int64_t nx, int64_t nstd,
+    float2* __restrict__ coef, int nt, int32_t* __restrict__ clist) {
+  const int64_t b = blockIdx.x;
+  if (b < nstd)
+    standardize_tile(E, lde, n_eff, m, mu, cov, Xs, n_pad, m_pad, st, (b % nx) * 64,
+                     (b / nx) * 64);
+  else
+    pair_coef_elem(cov, m, m_pad, coef, nt, clist, st, (b - nstd) * 256 + threadIdx.x);
 }
 
-// Hx takes 1024 threads per variable: one workgroup per variable is all the parallelism there
-// is (a few hundred workgroups in a fit, a handful late in the iterative search), so each works
-// its samples with 16 waves.  Measured effect is small: the iterative search at m = 400 went
-// 118.7 -> 117.4 ms, the fit's preparation stage 40.3 -> 39.8 us.
-constexpr int kHxThreads = 1024;
-
-// One launch for the two independent preparation steps: blocks [0, m) are hx_kernel's, the
-// blocks after them form the pair coefficients, one element per thread.
-__global__ __launch_bounds__(kHxThreads) void prep_kernel(
-    const float* __restrict__ Xs, int64_t n_pad, int64_t n_eff, double* __restrict__ Hx,
-    double* __restrict__ momx, const double* __restrict__ cov, int64_t m, int64_t m_pad,
-    float2* __restrict__ coef, int nt, int64_t tiles, int32_t* __restrict__ clist, int32_t* st) {
-  if ((int64_t)blockIdx.x < m) {
-    hx_block<kHxThreads>(Xs, n_pad, n_eff, Hx, momx, blockIdx.x);
-    return;
-  }
-  pair_coef_elem(cov, m, m_pad, coef, nt, tiles, clist, st,
-                 ((int64_t)blockIdx.x - m) * kHxThreads + threadIdx.x);
-}
+// Hx runs in the moments' launch, as its first blocks (one a variable; both read Xs only).  It
+// had a launch of its own with the pair coefficients: the exact search at m = 100, n = 5000 6.00
+// -> 5.55 ms, the precompute at m = 10, n = 20000 97 -> 91 us, 256 problems 10.97 -> 10.64 ms (a
+// launch of m workgroups leaves most of the chip idle for its whole length).
+static inline __host__ __device__ int64_t hx_blocks(int64_t m) { return (m + 7) / 8 * 8; }
 
 // Blocks are remapped so that XCD x (block id mod 8) processes a contiguous range of items in
 // chunk-major order, i.e. mostly one sample chunk per XCD and its L2.
@@ -64,9 +56,14 @@ template <class TP>
 __global__ __launch_bounds__(256) void pairwise_moments_kernel(
     const float* __restrict__ Xs, int64_t n_pad, const float2* __restrict__ coef, int64_t m_pad,
     int64_t m, int nt, int64_t tiles, int chunk_len, int64_t items,
-    TP* __restrict__ partU, TP* __restrict__ partB) {
-  const int64_t nb = gridDim.x;                     // a multiple of 8
-  const int64_t b = blockIdx.x;
+    TP* __restrict__ partU, TP* __restrict__ partB, int64_t n_eff, double* __restrict__ Hx,
+    double* __restrict__ momx) {
+  const int64_t nb = gridDim.x - hx_blocks(m);      // a multiple of 8
+  const int64_t b = (int64_t)blockIdx.x - hx_blocks(m);
+  if (b < 0) {
+    if (blockIdx.x < m) hx_block<256>(Xs, n_pad, n_eff, Hx, momx, blockIdx.x);
+    return;
+  }
   const int64_t lb = (b & 7) * (nb >> 3) + (b >> 3);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t item = lb * 4 + wave;
@@ -78,31 +75,49 @@ __global__ __launch_bounds__(256) void pairwise_moments_kernel(
     pairwise_moments_item(Xs, n_pad, coef, m_pad, m, nt, tiles, chunk_len, item, partU, partB);
 }
 
-// The (listed tile, chunk) items of the near-collinear micro-tiles, grid-stride over the list
-// the coefficient stage built (count = clist[tiles]); with no listed tile every wave returns
-// at once.
+// The (tile, chunk) items of the flagged micro-tiles: each wave looks through its share of all
+// items, 64 flags a time; with no flagged tile it returns after a load or two.
 template <class TP>
 __global__ __launch_bounds__(256) void pairwise_collinear_kernel(
     const float* __restrict__ E, int64_t lde, int64_t n_eff, const double* __restrict__ mu,
     const double* __restrict__ cov, int64_t m, int nt, int64_t tiles, int nc, int chunk_len,
     const int32_t* __restrict__ clist, TP* __restrict__ partU, TP* __restrict__ partB) {
+  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t total = (int64_t)clist[tiles] * nc;
-  for (int64_t w = (int64_t)blockIdx.x * 4 + wave; w < total; w += (int64_t)gridDim.x * 4) {
-    const int64_t tile = clist[tiles + 1 + w / nc], chunk = w % nc;
-    pairwise_collinear_item(E, lde, n_eff, mu, cov, m, nt, chunk_len, tile, chunk, partU,
-                            partB);
+  const int64_t total = tiles * nc, waves = (int64_t)gridDim.x * 4;
+  for (int64_t w0 = (int64_t)blockIdx.x * 4 + wave; w0 < total; w0 += 64 * waves) {
+    const int64_t wl = w0 + lane * waves;
+    uint64_t hit = __ballot(wl < total && clist[(wl < total ? wl : 0) / nc] != 0);
+    for (; hit; hit &= hit - 1) {
+      const int64_t w = w0 + (int64_t)(__ffsll((unsigned long long)hit) - 1) * waves;
+      pairwise_collinear_item(E, lde, n_eff, mu, cov, m, nt, chunk_len, w / nc, w % nc, partU,
+                              partB);
+    }
   }
 }
 
-// The items' rows, one wave each (see use_rows()); no remap: a handful of items.
+// The items' rows, one wave each (see use_rows()); no remap: a handful of items.  A flagged tile's
+// item runs as its collinear form instead, on one wave (a launch of its own for those took 3 us).
 __global__ __launch_bounds__(256) void pairwise_rows_kernel(
     const float* __restrict__ Xs, int64_t n_pad, const float2* __restrict__ coef, int64_t m_pad,
     int64_t m, int nt, int64_t tiles, int chunk_len, int64_t items, float* __restrict__ partU,
-    float* __restrict__ partB) {
+    float* __restrict__ partB, int64_t n_eff, double* __restrict__ Hx, double* __restrict__ momx,
+    const float* __restrict__ E, int64_t lde, const double* __restrict__ mu,
+    const double* __restrict__ cov, const int32_t* __restrict__ clist) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t item = blockIdx.x;
+  if (blockIdx.x < m) {
+    hx_block<256>(Xs, n_pad, n_eff, Hx, momx, blockIdx.x);
+    return;
+  }
+  const int64_t item = (int64_t)blockIdx.x - m;
   if (item >= items) return;
+  const int64_t chunk = item / tiles, tile = item - chunk * tiles;
+  if (clist[tile]) {
+    if (wave == 0)
+      pairwise_collinear_item(E, lde, n_eff, mu, cov, m, nt, chunk_len, tile, chunk, partU,
+                              partB);
+    return;
+  }
   pairwise_moments_row(Xs, n_pad, coef, m_pad, m, nt, tiles, chunk_len, item, wave, partU, partB);
 }
 
@@ -170,7 +185,7 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out) {
     w.partU = b.take<float>(np);
     w.partB = b.take<float>(np);
   }
-  w.clist = b.take<int32_t>(2 * p.tiles + 1);
+  w.clist = b.take<int32_t>(2 * p.tiles + 1);   // (tiles flags; the size is the limits')
   if (out) *out = w;
   return c.used + std::max(a.used, b.used);
 }
@@ -188,10 +203,11 @@ size_t scratch_doubles(const PairwisePlan& p) {
 
 int standardize_to(const float* E, int64_t lde, int64_t n_eff, int64_t m, const double* mu,
                    const double* cov, float* Xs, int64_t n_pad, int64_t m_pad, int32_t* st,
-                   hipStream_t stream, int32_t* zero, int64_t nzero) {
-  dim3 g((unsigned)ceil_div(n_pad, 64), (unsigned)ceil_div(m_pad, 64));
-  standardize_transpose_kernel<<<g, 256, 0, stream>>>(E, lde, n_eff, m, mu, cov, Xs, n_pad,
-                                                       m_pad, st, zero, nzero);
+                   hipStream_t stream, float2* coef, int nt, int32_t* clist) {
+  const int64_t nx = ceil_div(n_pad, (int64_t)64), nstd = nx * ceil_div(m_pad, (int64_t)64);
+  const int64_t nco = coef ? ceil_div(coef_threads(nt), (int64_t)256) : 0;
+  standardize_transpose_kernel<<<(unsigned)(nstd + nco), 256, 0, stream>>>(
+      E, lde, n_eff, m, mu, cov, Xs, n_pad, m_pad, st, nx, nstd, coef, nt, clist);
   VL_LAUNCH_CHECK();
   return VL_OK;
 }
@@ -208,24 +224,26 @@ static bool use_rows(int64_t items) {
 // Stages 4-5 with FP32 (plain sums) or FP64 (compensated sums) partials.
 template <class TP>
 static int launch_moments(const PairwisePlan& p, const PairwiseWs& w, const float* E,
-                          int64_t lde, const double* cov, const double* Hx, double* Hr,
+                          int64_t lde, const double* cov, double* Hx, double* Hr,
                           double* S, double* mom, TP* partU, TP* partB, hipStream_t stream) {
   const int64_t m = p.m, n_eff = p.n_eff;
+  bool rows = false;
   {
     ProfileScope ps("pairwise_moments", stream);
-    bool rows = false;
     if constexpr (std::is_same<TP, float>::value) {
       rows = use_rows(p.items);
       if (rows)
-        pairwise_rows_kernel<<<(unsigned)p.items, 256, 0, stream>>>(
-            w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB);
+        pairwise_rows_kernel<<<(unsigned)(m + p.items), 256, 0, stream>>>(
+            w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB,
+            n_eff, Hx, w.momx, E, lde, w.mu, cov, w.clist);
     }
     if (!rows)
-      pairwise_moments_kernel<TP><<<(unsigned)p.blocks, 256, 0, stream>>>(
-          w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB);
+      pairwise_moments_kernel<TP><<<(unsigned)(hx_blocks(m) + p.blocks), 256, 0, stream>>>(
+          w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB,
+          n_eff, Hx, w.momx);
     VL_LAUNCH_CHECK();
   }
-  {
+  if (!rows) {
     ProfileScope ps("pairwise_collinear", stream);
     const int64_t blocks = std::min<int64_t>(ceil_div(p.items, 4), 256);
     pairwise_collinear_kernel<TP><<<(unsigned)blocks, 256, 0, stream>>>(
@@ -279,12 +297,8 @@ int run_pairwise(const PairwisePlan& p, const PairwiseWs& w, const float* E, int
   {
     ProfileScope ps("pairwise_prep", stream);
     int rc = standardize_to(E, lde, n_eff, m, w.mu, cov, w.Xs, p.n_pad, p.m_pad, st, stream,
-                            w.clist, p.tiles + 1);
+                            w.coef, p.nt, w.clist);
     if (rc) return rc;
-    prep_kernel<<<(unsigned)(m + ceil_div(p.m_pad * p.m_pad, (int64_t)kHxThreads)), kHxThreads,
-                  0, stream>>>(w.Xs, p.n_pad, n_eff, Hx, w.momx, cov, m, p.m_pad, w.coef, p.nt,
-                               p.tiles, w.clist, st);
-    VL_LAUNCH_CHECK();
   }
   if (p.comp)
     return launch_moments(p, w, E, lde, cov, Hx, Hr, S, mom, w.partU64, w.partB64, stream);

@@ -29,7 +29,7 @@ struct PairwiseWs {
   double* partU64 = nullptr;  // nc x m x m (compensated sums; in place of partU, partB)
   double* partB64 = nullptr;
   double* momx = nullptr;     // 2 m: E[log cosh x_i], E[x_i exp(-x_i^2/2)]
-  int32_t* clist = nullptr;   // 2 tiles + 1: near-collinear tile flags, count, list
+  int32_t* clist = nullptr;   // near-collinear tile flags
   int8_t* slices = nullptr;   // sliced covariance: slice planes of E's columns (stage 1)
   int32_t* ex = nullptr;      // m exponents
 };
@@ -41,10 +41,10 @@ size_t scratch_doubles(const PairwisePlan& p);
 size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out);
 // Standardise E with the given means and covariance diagonal into the variable-major Xs
 // (m_pad x n_pad, zero padded).  n_pad >= n_eff, m_pad >= m.
-// The launch also clears zero[0 .. nzero) (nullptr: nothing).
+// With coef: the same launch forms the pair coefficients (nt micro-tiles a side) and their flags.
 int standardize_to(const float* E, int64_t lde, int64_t n_eff, int64_t m, const double* mu,
                    const double* cov, float* Xs, int64_t n_pad, int64_t m_pad, int32_t* st,
-                   hipStream_t stream, int32_t* zero = nullptr, int64_t nzero = 0);
+                   hipStream_t stream, float2* coef = nullptr, int nt = 0, int32_t* clist = nullptr);
 // kFirst: the call's first kernels (the status word is set to VL_OK); kContinue: a step of a call
 // under way, with the splits' column sums of E already in the workspace's scratch.
 enum class PairwiseStart { kFirst, kContinue };

@@ -10,17 +10,12 @@ namespace vl {
 // ------------------------------------------------------------------------------------------
 // Stage 2a: standardise + transpose.  Block = 64 x 64 tile of E (t x i), staged through LDS.
 // ------------------------------------------------------------------------------------------
-// The blocks also clear zero[0 .. nzero) (the collinear-tile flags and list count of the
-// pairwise precompute; nullptr for none), block `blk` of `nblk` taking a grid-stride share.
 __device__ inline void standardize_tile(
     const float* __restrict__ E, int64_t lde, int64_t n_eff, int64_t m,
     const double* __restrict__ mu, const double* __restrict__ cov, float* __restrict__ Xs,
-    int64_t n_pad, int64_t m_pad, int32_t* st, int64_t t0, int64_t i0,
-    int32_t* __restrict__ zero = nullptr, int64_t nzero = 0, int64_t blk = 0, int64_t nblk = 1) {
+    int64_t n_pad, int64_t m_pad, int32_t* st, int64_t t0, int64_t i0) {
   __shared__ float tile[64][65];
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  if (zero)
-    for (int64_t e = blk * blockDim.x + threadIdx.x; e < nzero; e += nblk * blockDim.x) zero[e] = 0;
   const int64_t i = i0 + tx;
   double mui = 0.0, inv = 0.0;
   if (i < m) {
@@ -29,15 +24,14 @@ __device__ inline void standardize_tile(
     mui = mu[i];
     inv = var > 0.0 ? 1.0 / sqrt(var) : 0.0;
   }
-  // every load of the tile in flight at once (clamped addresses; a load under the bounds test
-  // would be waited for in turn)
+  // every load of the tile in flight at once (a load under the bounds test would be waited for in
+  // turn), by a stepped pointer clamped to the last row
   float ev[16];
   const float* Ei = E + (i < m ? i : m - 1);
+  const float* last = Ei + (n_eff - 1) * lde;
+  const float* pe = Ei + (t0 + ty) * lde;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int64_t t = t0 + ty + 4 * q;
-    ev[q] = Ei[(t < n_eff ? t : n_eff - 1) * lde];
-  }
+  for (int q = 0; q < 16; ++q, pe += 4 * lde) ev[q] = *(pe < last ? pe : last);
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
     const int r = ty + 4 * q;
@@ -56,7 +50,7 @@ __device__ inline void standardize_tile(
 // library exp/log (O(mn) work, not on the critical path).
 // ------------------------------------------------------------------------------------------
 template <int NT>
-__device__ inline void hx_block(const float* __restrict__ Xs, int64_t n_pad, int64_t n_eff,
+__device__ __forceinline__ void hx_block(const float* __restrict__ Xs, int64_t n_pad, int64_t n_eff,
                                 double* __restrict__ Hx, double* __restrict__ momx, int64_t i) {
   constexpr int kW = NT / 64;
   __shared__ double ra[kW], rb[kW];
@@ -132,38 +126,33 @@ __device__ inline void tile_coords(int64_t k, int nt, int& bi, int& bj) {
 // A pair with sqrt(1 - rho^2) below kCollinearS is near-collinear: its Eq. 1 residual
 // x_i - rho x_j cancels to a small fraction of the data, and forming it from the FP32 rounded
 // standardised columns would amplify their rounding by 1 / sqrt(1 - rho^2).  The coefficient
-// stage lists the micro-tiles that hold such a pair; after the FP32 moment kernel (which runs
-// every tile) the collinear kernel recomputes their items, standardising and forming the
-// residual in FP64 from E itself, and overwrites their partials.
-// List layout (int32): flag[tiles] (1 = listed), then count, then the listed tile indices; the
-// flags and the count are cleared by the standardisation stage.
+// stage flags the micro-tiles that hold such a pair; their items are recomputed after the FP32
+// moment kernel (which runs every tile), or taken instead of it where the items run as rows:
+// standardised and with the residual formed in FP64 from E itself.
 constexpr double kCollinearS = 0.25;
 
-__device__ inline void list_collinear_tile(int32_t* __restrict__ clist, int nt, int64_t tiles,
-                                           int64_t i, int64_t j) {
-  const int64_t a = (i < j ? i : j) / kT, b = (i < j ? j : i) / kT;
-  const int64_t tile = a * nt - a * (a - 1) / 2 + (b - a);
-  if (atomicExch(&clist[tile], 1) == 0) {
-    const int k = atomicAdd(&clist[tiles], 1);
-    clist[tiles + 1 + k] = (int32_t)tile;
-  }
-}
+// ------------------------------------------------------------------------------------------
+// Stage 3: scaled pair coefficients (a, b) of the micro-tiles {I, J}, bi <= bj (the others are
+// read by nothing); zero on the diagonal / padding.  clist[tile] is 1 for a tile with a
+// near-collinear pair, else 0.  One thread an entry, 16 consecutive threads a micro-tile: entry e
+// of nt nt kT kT, so a tile's flag is one ballot and nothing has to be cleared first.
+// ------------------------------------------------------------------------------------------
+inline __host__ __device__ int64_t coef_threads(int64_t nt) { return nt * nt * kT * kT; }
 
-// ------------------------------------------------------------------------------------------
-// Stage 3: scaled pair coefficients (a, b) for i, j < m_pad; zero on the diagonal / padding.
-// A near-collinear pair lists its micro-tile in clist.
-// ------------------------------------------------------------------------------------------
 __device__ inline void pair_coef_elem(const double* __restrict__ cov, int64_t m, int64_t m_pad,
-                                      float2* __restrict__ coef, int nt, int64_t tiles,
+                                      float2* __restrict__ coef, int nt,
                                       int32_t* __restrict__ clist, int32_t* st, int64_t e) {
-  if (e >= m_pad * m_pad) return;
-  const int64_t i = e / m_pad, j = e % m_pad;
+  static_assert(kT * kT == 16, "a micro-tile is 16 lanes of a wave");
+  const int64_t bi = (e >> 4) / nt, bj = (e >> 4) - bi * nt;
+  const int64_t i = bi * kT + ((e >> 2) & 3), j = bj * kT + (e & 3);
+  const bool own = bi <= bj && bi < nt;
   float2 c = make_float2(0.f, 0.f);
-  if (i < m && j < m && i != j) {
+  bool near = false;
+  if (own && i < m && j < m && i != j) {
     const double vi = cov[i * m + i], vj = cov[j * m + j];
     const double rho = cov[i * m + j] / sqrt(vi * vj);
     const double omr = 1.0 - rho * rho;
-    if (!(omr >= kCollinearS * kCollinearS)) list_collinear_tile(clist, nt, tiles, i, j);
+    near = !(omr >= kCollinearS * kCollinearS);
     if (!(omr >= kMinOneMinusRho2)) {
       raise_status(st, VL_ERR_DEGENERATE);
     } else {
@@ -171,7 +160,11 @@ __device__ inline void pair_coef_elem(const double* __restrict__ cov, int64_t m,
       c = make_float2((float)(kWScale / s), (float)(kWScale * rho / s));
     }
   }
-  coef[e] = c;
+  const uint64_t any = __ballot(near);
+  if (!own) return;
+  coef[i * m_pad + j] = c;
+  if ((e & 15) == 0)
+    clist[bi * nt - bi * (bi - 1) / 2 + (bj - bi)] = (any >> (threadIdx.x & 48)) & 0xffff ? 1 : 0;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -609,13 +602,13 @@ __device__ __attribute__((always_inline)) inline void pairwise_moments_item_comp
   write_moment_partials(acc, i0, j0, m, chunk, partU, partB);
 }
 
-// The same item, (tile, chunk), for a listed micro-tile.  Lanes run over samples, one per step.  Each sample of the tile's 2 kT variables
-// is standardised in FP64 from E (x = (e - mu) / sd, population moments), the residuals of
+// The same item, (tile, chunk), for a flagged micro-tile.  Lanes run over samples, one per step.
+// Each sample of the tile's 2 kT variables is standardised in FP64 from E (x = (e - mu) / sd, population moments), the residuals of
 // both directions are formed in FP64, d = x_i - rho x_j, and only the scaled residual
 // w = d c / sqrt(1 - rho^2) is rounded to FP32: its relative error is then that of one
 // rounding, as for a well-conditioned pair.  The moment terms are the fast item's.
 template <class TP>
-__device__ inline void pairwise_collinear_item(
+__device__ __forceinline__ void pairwise_collinear_item(
     const float* __restrict__ E, int64_t lde, int64_t n_eff, const double* __restrict__ mu,
     const double* __restrict__ cov, int64_t m, int nt, int chunk_len, int64_t tile,
     int64_t chunk, TP* __restrict__ partU, TP* __restrict__ partB) {
@@ -709,26 +702,6 @@ __device__ inline double combine_finish(double su, double sb, int64_t n_eff, dou
   return kHGauss - kK1 * (A - kGamma) * (A - kGamma) - kK2 * B * B;
 }
 
-template <class TP>
-__device__ inline void combine_hr_elem(const TP* __restrict__ partU,
-                                       const TP* __restrict__ partB, int nc, int64_t m,
-                                       int64_t n_eff, double* __restrict__ Hr,
-                                       double* __restrict__ mom, int64_t e) {
-  if (e >= m * m) return;
-  const int64_t i = e / m, j = e % m;
-  if (i == j) {
-    Hr[e] = 0.0;
-    if (mom) mom[2 * e] = mom[2 * e + 1] = 0.0;
-    return;
-  }
-  double su = 0.0, sb = 0.0;
-  for (int c = 0; c < nc; ++c) {
-    su += (double)partU[(int64_t)c * m * m + e];
-    sb += (double)partB[(int64_t)c * m * m + e];
-  }
-  Hr[e] = combine_finish(su, sb, n_eff, mom ? mom + 2 * e : nullptr);
-}
-
 // Block bi <= bj of kCS x kCS entries and its mirror image, one entry of each a thread: Hr of both
 // (partials read along rows, four chunks of both in flight, added in chunk order), then S of
 // both, the mirrored Hr passing through LDS: the same two sums in both orders -> S[j][i] ==
@@ -736,7 +709,7 @@ __device__ inline void combine_hr_elem(const TP* __restrict__ partU,
 constexpr int kCS = 16;
 
 template <class TP>
-__device__ inline void combine_score_block(const TP* __restrict__ partU,
+__device__ __forceinline__ void combine_score_block(const TP* __restrict__ partU,
                                            const TP* __restrict__ partB, int nc, int64_t m,
                                            int64_t n_eff, const double* __restrict__ Hx,
                                            double* __restrict__ Hr, double* __restrict__ mom,

@@ -241,3 +241,35 @@ def test_batch_full_workload_sampled(api):
     for k in sorted({int(np.argmin(ms)), int(np.argmax(ms)), 17, 200}):
         print(f"  oracle check of problem {k} (m={ms[k]})", flush=True)
         _check_problem(results[k], insts[k], 1)
+
+
+@pytest.mark.parametrize("fill", [False, True], ids=["quarter tiles", "whole tiles"])
+@pytest.mark.parametrize("p", [1, 3])
+def test_batch_residuals_at_the_edges(api, p, fill):
+    """E = Y - c - Z M' of the batch's own coefficients, at the edges of the residual's tiles (16
+    and 64 variables, 64 and 256 samples), below both (m < 16, n_eff < 64) and with lag blocks that
+    are no multiple of 16; with enough large problems beside them (or not) for one wave per tile.
+    E is one FP32 rounding (2^-24) of an FP64 sum of dz + 2 terms; the bound allows 2^-23 |E| and
+    1e-12 of the terms' size."""
+    n_effs = {3: 37, 5: 63, 15: 64, 16: 63, 17: 129, 31: 200, 33: 255, 48: 256, 63: 257, 64: 320,
+              65: 511, 80: 513}
+    rng = np.random.default_rng(11 + p)
+    # (m p + m + 20 samples at least: with fewer than m p + m + 1 the residuals have no full rank)
+    Xs = [(rng.laplace(size=(max(ne, m * p + m + 20) + p, m)) + rng.uniform(-3, 3, m)).astype(np.float32)
+          for m, ne in n_effs.items() if m * p <= 256]
+    count = len(Xs)
+    if fill:                                              # 14 x 2 x 63 tiles
+        Xs += [rng.laplace(size=(4000, 70)).astype(np.float32) for _ in range(14)]
+    results, status = api.fit_batched(Xs, p, "mixed")
+    assert all(s == 0 for s in status)
+    for X, r in zip(Xs[:count + 1], results):
+        Y = X.astype(np.float64)
+        M, c = r.M.cpu().numpy(), r.intercept.cpu().numpy()
+        want, size = Y[p:] - c, np.abs(Y[p:]) + np.abs(c)
+        for tau in range(1, p + 1):
+            lag = Y[p - tau:len(Y) - tau]
+            want = want - lag @ M[tau - 1].T
+            size = size + np.abs(lag) @ np.abs(M[tau - 1]).T
+        E = r.E.cpu().numpy()
+        assert E.shape == want.shape
+        assert np.all(np.abs(E - want) <= 2.0 ** -23 * np.abs(want) + 1e-12 * size), X.shape

@@ -488,3 +488,19 @@ def test_pairwise_near_collinear_pairs(api, dev, n):
     print(f"pairwise near-collinear n={n}", flush=True)
     E32 = synth.near_collinear(n, 17 + n, [0.99, 0.999, 0.9999, 0.99999, 0.999999])
     _check_pairwise(api, dev, E32)
+
+
+@pytest.mark.parametrize("m,n", [(12, 640), (12, 1300), (33, 1300), (64, 5000), (66, 20000),
+                                 (100, 5000), (130, 1281)])
+def test_pairwise_near_collinear_among_others(api, dev, m, n):
+    """A few near-collinear pairs among independent columns, from plans that run one-row items to
+    plans that run whole micro-tiles: flagged tiles at both ends of the tile order and off the
+    diagonal, element-wise at the bounds of the well-conditioned tests."""
+    print(f"pairwise near-collinear among others m={m} n={n}", flush=True)
+    rng = np.random.default_rng(7 * m + n)
+    N = synth.near_collinear(n, 31 + n, [0.99, 0.9999, 0.999999]).astype(np.float64)
+    E = rng.laplace(size=(n, m))
+    E[:, 0], E[:, 1] = N[:, 0], N[:, 1]                  # in the first tile
+    E[:, 4], E[:, m - 1] = N[:, 2], N[:, 3]              # off the diagonal
+    E[:, m - 3], E[:, m - 2] = N[:, 4], N[:, 5]
+    _check_pairwise(api, dev, E.astype(np.float32))
