@@ -218,10 +218,10 @@ __device__ __forceinline__ void bat_gram_tile(const float* A, int64_t lda, const
                                      const double* muA, int64_t M, const float* B, int64_t ldb,
                                      const int64_t* mapB, const double* muB, int64_t N,
                                      int64_t i0, int64_t j0, int64_t K, double* C, int64_t ldc,
-                                     double scale, bool mirror) {
+                                     double scale, bool mirror, bool diag) {
   if (kFp64)
     gram_tile_f64(A, lda, mapA, muA, M, B, ldb, mapB, muB, N, i0, j0, 0, K, C, ldc, scale,
-                  mirror);
+                  mirror, diag);
   else  // FP32 partial sums over 128-sample blocks added in FP64 (the single-problem path gets
         // the same from its FP64 combination of split-K partials)
     gram_tile_f32<4>(A, lda, mapA, muA, M, B, ldb, mapB, muB, N, i0, j0, 0, K, C, ldc, scale,
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256, kFp64 ? 2 : 4) void bat_gram_kernel(BTables T,
     const int64_t i0 = (g ? ti : (lb - tri) / tm) * kGT, j0 = (g ? tj : (lb - tri) % tm) * kGT;
     bat_gram_tile<kFp64>(X, ldx, map + m, mu + m, dz, X, ldx, g ? map + m : map,
                          g ? mu + m : mu, g ? dz : m, uni(i0), uni(j0), n_eff,
-                         g ? d.G : d.Tmp, g ? dz : m, 1.0, false);
+                         g ? d.G : d.Tmp, g ? dz : m, 1.0, false, g && ti == tj);
   } else {
     int64_t ti, tj;
     lower_tile(lb, ti, tj);
@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256, kFp64 ? 2 : 4) void bat_gram_kernel(BTables T,
     const int64_t lde = d.lde;
     const double* mu = d.emu;
     bat_gram_tile<kFp64>(E, lde, nullptr, mu, m, E, lde, nullptr, mu, m, uni(ti * kGT),
-                         uni(tj * kGT), n_eff, d.cov, m, 1.0 / (double)n_eff, ti != tj);
+                         uni(tj * kGT), n_eff, d.cov, m, 1.0 / (double)n_eff, ti != tj, ti == tj);
   }
 }
 

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(256, 2) void gram_tn_f64_kernel(
   int64_t i0, j0;
   gram_tile_origin(sym, i0, j0);
   gram_tile_f64(A, lda, mapA, muA, M, B, ldb, mapB, muB, N, i0, j0, kb, ke,
-                P + (int64_t)blockIdx.z * M * N, N, 1.0);
+                P + (int64_t)blockIdx.z * M * N, N, 1.0, false, sym && i0 == j0);
 }
 
 // C[i][j] = sum_t (A(t,i) - muA[i]) B64[t][j] with an FP64 right operand (not centred): the

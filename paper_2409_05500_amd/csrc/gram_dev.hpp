@@ -203,6 +203,8 @@ __device__ inline void gram_tile_bf16(
 // use): 1000 x 1000 over 49999 samples (lower tiles) 1.43 -> 0.93 ms (60 TFLOP/s of the tiles),
 // 400 x 2000 over 9996 0.46 -> 0.35 ms, 10 x 10 over 999 22.6 -> 6.3 us; both Grams of the 256
 // uneven problems (m 20-200, n 500-8000) 2.67 -> 1.77 ms, of 181 windows of 50 x 2000 0.38 -> 0.23.
+// diag: a tile on the diagonal of a symmetric product forms its lower 16 x 16 blocks only, 10 of
+// 16, and writes both halves (the two cases again: 1.77 -> 1.60 ms, 0.23 -> 0.21).
 // ------------------------------------------------------------------------------------------
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
@@ -213,7 +215,7 @@ __device__ __forceinline__ void gram_tile_f64(
     const double* __restrict__ muA, int64_t M, const float* __restrict__ B, int64_t ldb,
     const int64_t* __restrict__ mapB, const double* __restrict__ muB, int64_t N, int64_t i0,
     int64_t j0, int64_t kb, int64_t ke, double* __restrict__ out, int64_t ldo, double scale,
-    bool mirror = false) {
+    bool mirror = false, bool diag = false) {
   __shared__ double part[4][8][4][64];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lk = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -246,9 +248,10 @@ __device__ __forceinline__ void gram_tile_f64(
 #pragma unroll
     for (int a = 0; a < 4; ++a)
       if (a < na) {
+        const int nba = diag && a + 1 < nb ? a + 1 : nb;
 #pragma unroll
         for (int b = 0; b < 4; ++b)
-          if (b < nb)
+          if (b < nba)
             acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
       }
   };
@@ -320,7 +323,7 @@ __device__ __forceinline__ void gram_tile_f64(
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int blk = 2 * wave + u, a = 2 * h + (blk >> 2), b = blk & 3;
-      if (a >= na || b >= nb) continue;
+      if (a >= na || b >= nb || (diag && b > a)) continue;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const double v = ((part[0][blk][r][lane] + part[1][blk][r][lane]) +
@@ -328,7 +331,7 @@ __device__ __forceinline__ void gram_tile_f64(
         const int64_t i = i0 + a * 16 + lk + 4 * r, j = j0 + b * 16 + li;
         if (i < M && j < N) {
           out[i * ldo + j] = scale * v;
-          if (mirror) out[j * ldo + i] = scale * v;
+          if (mirror || (diag && a != b)) out[j * ldo + i] = scale * v;
         }
       }
     }
