@@ -482,13 +482,18 @@ __global__ __launch_bounds__(kCS* kCS) void bat_combine_kernel(BTables T) {
 // covariance (B0_KK = I - L^{-1}) and B_tau = (I - B0) M_tau.
 // One workgroup per problem: the ordering, then the covariance permuted into that order
 // (with the permutation check).
+// Problems of at most 64 variables are ordered from LDS (32 KB; 128 KB for twice that would allow
+// one workgroup per CU and measured the same at m 20-200).
 __global__ __launch_bounds__(256) void bat_order_kernel(const BInst* __restrict__ I,
                                                         int32_t* st0) {
   const BInst d = block_inst(I + blockIdx.x);
   int32_t* st = st0 + blockIdx.x;
   const int64_t m = d.m;
   const int tid = threadIdx.x;
-  order_wave_block<kBatchMaxM / 64, 256>(d.S, m, d.order, d.margin, st);
+  if (m <= 64)
+    order_wave_block<1, 256, true>(d.S, m, d.order, d.margin, st);
+  else
+    order_wave_block<kBatchMaxM / 64, 256>(d.S, m, d.order, d.margin, st);
   __shared__ int seen[kBatchMaxM], Ks[kBatchMaxM];
   for (int64_t a = tid; a < m; a += 256) {
     seen[a] = 0;
@@ -496,7 +501,7 @@ __global__ __launch_bounds__(256) void bat_order_kernel(const BInst* __restrict_
   }
   __syncthreads();
   // the permuted covariance, four rows a wave at a time, every load of them in flight (an element
-  // a thread had the kernel at 258 us for 256 problems, now 157)
+  // a thread had the kernel at 258 us for 256 problems, this at 157)
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int kR = 4, kU = kBatchMaxM / 64;
   const double* cov = d.cov;

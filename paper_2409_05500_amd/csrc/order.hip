@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void order_wave_kernel(const double* __re
     if (threadIdx.x == 0) *st = VL_OK;
     __syncthreads();
   }
-  order_wave_block<R, kThreads>(S, m, order, margin, st);
+  order_wave_block<R, kThreads, (R <= 2)>(S, m, order, margin, st);
 }
 
 int run_order(const double* S, int64_t m, int32_t* order, double* margin, double* M0,

@@ -10,7 +10,7 @@ namespace vl {
 // ------------------------------------------------------------------------------------------
 // Single-wave form for m <= 64 R.  Phase 0: all waves of the block form M0 (this reads every
 // row of S once, which also brings S into this CU's L2 for the sequential phase).  Phase 1:
-// wave 0 alone runs the m steps with M in registers and wave-wide minima by DPP / permlane
+// two waves run the m steps with M in registers and wave-wide minima by DPP / permlane
 // butterflies: no barriers inside the sequential loop.  The live set shrinks by one a step, so
 // the loop runs in stages of R, R - 1, ..., 1 slots a lane (halving above 8): whenever the live
 // entries fit in the next stage's slots they are packed into them through LDS, each slot
@@ -117,47 +117,123 @@ __device__ __forceinline__ int slots_index_of(const double (&x)[R], const int (&
   return t[0];
 }
 
+// The wave's smallest key (NaN: none) and, in lane, the one lane that holds it, or -1 where several
+// may: the wave compares the high words only, as ordered integers (one operation a level, where
+// an FP64 minimum takes two moves and one); equal high words (equal or nearly equal keys, or
+// none) take the full reduction.
+__device__ __forceinline__ double wave_lowest(double key, int& lane) {
+  const int hi = __double2hiint(key);
+  const int hk = key == key ? hi ^ ((hi >> 31) & 0x7fffffff) : 0x7fffffff;
+  int v = hk;
+  v = min(v, __builtin_amdgcn_mov_dpp(v, kDppRowMirror, 0xF, 0xF, true));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, kDppHalfMirror, 0xF, 0xF, true));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, kDppQuadXor2, 0xF, 0xF, true));
+  v = min(v, __builtin_amdgcn_mov_dpp(v, kDppQuadXor1, 0xF, 0xF, true));
+  const int low = min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+                      min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+  const unsigned long long mk = __ballot(hk == low);
+  lane = -1;
+  if (__builtin_expect((mk & (mk - 1)) != 0, 0)) return wave_min_quiet(key);
+  lane = __builtin_ctzll(mk);
+  return __hiloint2double(__builtin_amdgcn_readlane(hi, lane),
+                          __builtin_amdgcn_readlane(__double2loint(key), lane));
+}
+
+// Which part of a step a wave does: all of it, or one of two waves' shares.
+enum class OrderRole { kAll, kOrder, kMargin };
+
+// What the ordering wave tells the margin wave of each step, in LDS: index is written last (-1:
+// not yet), and a wave's LDS accesses are carried out in order.
+template <int N>
+struct OrderBox {
+  double low[N];
+  int index[N];
+};
+
 constexpr int order_next_slots(int R) { return R > 8 ? R / 2 : R - 1; }
 
 // Steps k .. while more entries are live than the next stage holds, with R slots a lane
 // (Mv[r], vid[r]: the lane's entries and their variable indices; removed and empty slots hold
 // NaN).  Removed and padding entries hold NaN: the minimum passes over NaN, and NaN equals
 // nothing, so they never win a minimum nor the index search even when every live M is +inf (a
-// row of S with a non-finite entry, which raised VL_ERR_NONFINITE).  Each step: m1 = wave min
-// over the live entries; i1 = lowest index holding m1; the loads of row i1 are issued at once
-// and the second minimum (the margin) is reduced while they are in flight.  sM, sI: LDS for
-// the packing (64 R entries each).
-template <int R>
-__device__ __forceinline__ void order_stage(const double* __restrict__ S, int64_t m,
+// row of S with a non-finite entry, which raised VL_ERR_NONFINITE).  A step finds the smallest M
+// (m1) and the lowest index that holds it (i1), loads row i1 of S and updates M by it; its margin
+// is the smallest M left without i1.  It costs one wave's dependent instructions (8 cycles and
+// more each), so with few slots what the next step does not need is another wave's: the ordering
+// wave posts m1 and i1, and the margin wave, with an M of its own, takes each post, which always
+// comes, and does the rest.  Where the slots' own work is the most of it (R > 8) one wave does
+// all, the margin's reduction while the row is loaded.  The results are stored 64 steps at a
+// time: the wait for a row counts every memory operation of the wave, so a step that stores
+// waits for its stores.  In us, with one wave that stores at each step and reduces FP64 values
+// throughout, and now: m = 100 49 and 38, m = 317 183 and 152, m = 1000 (with its B0 and lag
+// matrices) 1312 and 1231.  sM, sI: LDS for the packing, the wave's own (64 RN entries each).
+template <int R, OrderRole kRole, int N>
+__device__ __forceinline__ void order_stage(const double* S, int64_t m,
                                             int32_t* __restrict__ order,
-                                            double* __restrict__ margin, double* sM, int* sI,
-                                            double (&Mv)[R], int (&vid)[R], int64_t k) {
+                                            double* __restrict__ margin, OrderBox<N>& box,
+                                            double* sM, int* sI, double (&Mv)[R], int (&vid)[R],
+                                            int k, int out_i, double out_m) {
   const int lane = threadIdx.x & 63;
   const double inf = INFINITY, gone = __builtin_nan("");
-  const int64_t last = m - 1;
+  const int last = (int)m - 1;
   constexpr int RN = order_next_slots(R);
-  const int64_t kend = RN > 0 ? m - 64 * RN : m;   // m - k entries are live at step k
+  const int kend = RN > 0 ? (int)m - 64 * RN : (int)m;   // m - k entries are live at step k
   for (; k < kend; ++k) {
-    const double m1 = wave_min_quiet(slots_min<R>(Mv));
-    const int i1 = wave_min_i32(slots_index_of<R>(Mv, vid, m1));
+    double m1;
+    int i1;
+    if constexpr (kRole == OrderRole::kMargin) {
+      volatile int* post = &box.index[k];
+      do i1 = *post;
+      while (i1 < 0);
+      i1 = __builtin_amdgcn_readfirstlane(i1);
+      m1 = *(volatile double*)&box.low[k];
+    } else {
+      const double key = slots_min<R>(Mv);
+      const int own = slots_index_of<R>(Mv, vid, key);
+      int l;
+      m1 = wave_lowest(key, l);
+      if (__builtin_expect(l >= 0, 1)) i1 = __builtin_amdgcn_readlane(own, l);
+      else i1 = __builtin_amdgcn_readfirstlane(wave_min_i32(key == m1 ? own : 0x7fffffff));
+    }
     // row i1 of S at this lane's variables (every vid is a valid column)
-    const double* rowp = S + (int64_t)(i1 < m ? i1 : last) * m;
+    const double* rowp = S + (unsigned)min(i1, last) * (unsigned)m;
     double v[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = rowp[vid[r]];
-    // remove the winner, then the margin from the remaining minimum
+    if constexpr (kRole == OrderRole::kOrder) {
+      if (lane == 0) {
+        *(volatile double*)&box.low[k] = m1;
+        *(volatile int*)&box.index[k] = i1;
+      }
+    }
+    // remove the winner (any low word with this high word is a NaN)
 #pragma unroll
     for (int r = 0; r < R; ++r)
-      if (vid[r] == i1) Mv[r] = gone;
-    const double m2 = wave_min_quiet(slots_min<R>(Mv));    // NaN when no live entry is left
-    if (lane == 0) {
-      order[k] = i1;
-      margin[k] = (m2 == inf || m2 != m2) ? inf : m2 - m1;
+      Mv[r] = __hiloint2double(vid[r] == i1 ? 0x7ff80000 : __double2hiint(Mv[r]),
+                               __double2loint(Mv[r]));
+    if constexpr (kRole != OrderRole::kOrder) {
+      int l;
+      const double m2 = wave_lowest(slots_min<R>(Mv), l);    // NaN when no live entry is left
+      const double gap = (m2 == inf || m2 != m2) ? inf : m2 - m1;
+      const bool mine = lane == (k & 63);
+      out_i = mine ? i1 : out_i;
+      out_m = mine ? gap : out_m;
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-      const double pos = v[r] > 0.0 && v[r] < inf ? v[r] : 0.0;
+      // 0 for v <= 0, NaN and infinity (a zero high word leaves a number whose square is 0)
+      const bool up = v[r] > 0.0 && v[r] < inf;
+      const double pos = __hiloint2double(up ? __double2hiint(v[r]) : 0, __double2loint(v[r]));
       Mv[r] -= pos * pos;            // +inf stays +inf, NaN stays NaN
+    }
+    if constexpr (kRole != OrderRole::kOrder) {
+      if ((k & 63) == 63 || k == last) {
+        const int ko = (k & ~63) + lane;
+        if (ko <= k) {
+          order[ko] = out_i;
+          margin[ko] = out_m;
+        }
+      }
     }
   }
   if constexpr (RN > 0) {
@@ -183,17 +259,40 @@ __device__ __forceinline__ void order_stage(const double* __restrict__ S, int64_
       Mn[r] = p < base ? sM[p] : gone;
       vn[r] = p < base ? sI[p] : 0;
     }
-    order_stage<RN>(S, m, order, margin, sM, sI, Mn, vn, k);
+    order_stage<RN, kRole>(S, m, order, margin, box, sM, sI, Mn, vn, k, out_i, out_m);
   }
 }
 
-template <int R, int kThreads>
-__device__ inline void order_wave_block(const double* __restrict__ S, int64_t m,
+// kLds: S is first copied to LDS (m <= 64 R; 64 R squared doubles), a shorter wait for each row
+template <int R, int kThreads, bool kLds = false>
+__device__ __forceinline__ void order_wave_block(const double* __restrict__ Sg, int64_t m,
                                         int32_t* __restrict__ order, double* __restrict__ margin,
                                         int32_t* st) {
-  __shared__ double M0s[64 * R];   // M0, then the packing buffer of the sequential phase
-  __shared__ int vidS[64 * R];
+  __shared__ double M0s[64 * R];   // M0
+  constexpr int kPack = 64 * (order_next_slots(R) > 0 ? order_next_slots(R) : 1);
+  __shared__ double packM[2][kPack];
+  __shared__ int packI[2][kPack];
+  __shared__ OrderBox<64 * R> box;
+  __shared__ double Sl[kLds ? 64 * R * 64 * R : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  if constexpr (kLds) {
+    constexpr int kF = 8;
+    const int total = (int)(m * m);
+    for (int e0 = threadIdx.x; e0 < total; e0 += kF * kThreads) {
+      double v[kF];
+#pragma unroll
+      for (int q = 0; q < kF; ++q) {
+        const int e = e0 + q * kThreads;
+        v[q] = Sg[e < total ? e : total - 1];
+      }
+#pragma unroll
+      for (int q = 0; q < kF; ++q)
+        if (e0 + q * kThreads < total) Sl[e0 + q * kThreads] = v[q];
+    }
+    __syncthreads();
+  }
+  const double* S = Sg;
+  if constexpr (kLds) S = Sl;
   bool bad = false;
   // several rows per wave at once, every load of them issued before the sums (clamped
   // in-bounds addresses; the padding is skipped in the sums)
@@ -225,8 +324,10 @@ __device__ inline void order_wave_block(const double* __restrict__ S, int64_t m,
     }
   }
   if (bad) raise_status(st, VL_ERR_NONFINITE);
+  for (int e = threadIdx.x; e < (int)m; e += kThreads) box.index[e] = -1;
   __syncthreads();
-  if (wave == 0) {
+  static_assert(kThreads >= 128, "an ordering and a margin wave");
+  if (wave < (R <= 8 ? 2 : 1)) {
     const double gone = __builtin_nan("");
     double Mv[R];
     int vid[R];
@@ -236,7 +337,15 @@ __device__ inline void order_wave_block(const double* __restrict__ S, int64_t m,
       Mv[r] = i < m ? M0s[i] : gone;
       vid[r] = i < m ? i : 0;
     }
-    order_stage<R>(S, m, order, margin, M0s, vidS, Mv, vid, 0);
+    if constexpr (R > 8)
+      order_stage<R, OrderRole::kAll>(S, m, order, margin, box, packM[0], packI[0], Mv, vid, 0, 0,
+                                      0.0);
+    else if (wave == 0)
+      order_stage<R, OrderRole::kOrder>(S, m, order, margin, box, packM[0], packI[0], Mv, vid, 0, 0,
+                                        0.0);
+    else
+      order_stage<R, OrderRole::kMargin>(S, m, order, margin, box, packM[1], packI[1], Mv, vid, 0,
+                                         0, 0.0);
   }
   __syncthreads();
 }

@@ -504,3 +504,24 @@ def test_pairwise_near_collinear_among_others(api, dev, m, n):
     E[:, 4], E[:, m - 1] = N[:, 2], N[:, 3]              # off the diagonal
     E[:, m - 3], E[:, m - 2] = N[:, 4], N[:, 5]
     _check_pairwise(api, dev, E.astype(np.float32))
+
+
+@pytest.mark.parametrize("m", [1, 2, 3, 63, 64, 65, 100, 128, 129, 200, 317, 512, 513, 1025])
+def test_order_ties_and_equal_high_words(api, dev, m):
+    """S of 0, +-1 and +-(1 + 2^-20): every M is a sum of few-bit squares, exact in FP64 in any
+    order, with many equal values and many that differ in their last bits only.  The order (lowest
+    index on ties) and the margins are then the plain algorithm's, exactly."""
+    rng = np.random.default_rng(m)
+    U = np.triu(rng.choice([0.0, 1.0, -1.0, 1.0 + 2.0 ** -20, -1.0 - 2.0 ** -20], size=(m, m)), 1)
+    S = U - U.T
+    order, margin = (t.cpu().numpy() for t in api.approx_order(_dev(S, dev)))
+    M = (np.minimum(S, 0.0) ** 2).sum(axis=1)
+    live = np.ones(m, bool)
+    for k in range(m):
+        Mk = np.where(live, M, np.inf)
+        c = int(np.argmin(Mk))
+        assert order[k] == c, k
+        live[c] = False
+        rest = Mk[live]
+        assert margin[k] == (rest.min() - Mk[c] if rest.size else np.inf), k
+        M = M - np.maximum(S[c], 0.0) ** 2
