@@ -285,7 +285,7 @@ __device__ inline CholArgs bat_chol_args(const BInst& d, int which, int32_t* st)
 __global__ __launch_bounds__(256) void bat_chol_prologue_kernel(const BInst* __restrict__ I,
                                                                 int which, int32_t* st0) {
   const CholArgs a = bat_chol_args(block_inst(I + blockIdx.x), which, st0 + blockIdx.x);
-  for (int64_t e = threadIdx.x; e < a.n * a.n; e += 256) chol_linv_init(a, e);
+  for (int64_t e = threadIdx.x; a.n > kNb && e < a.n * a.n; e += 256) chol_linv_init(a, e);
   chol_prologue_block(a);
 }
 
@@ -672,11 +672,11 @@ int64_t blocks_for(int map, const vl_instance& in, const InstLayout& L) {
   }
   if (map >= kMapVarChol0 && map < kMapBChol0) {
     const int64_t k = map - kMapVarChol0, nb = ceil_div(dz, (int64_t)kNb);
-    return k < nb ? step_items(nb, k, ceil_div(m, (int64_t)kNb), true).total() : 0;
+    return nb > 1 && k < nb ? step_items(nb, k, ceil_div(m, (int64_t)kNb), true).total() : 0;
   }
   if (map >= kMapBChol0 && map < kMapVarBack) {
     const int64_t k = map - kMapBChol0, nb = ceil_div(m, (int64_t)kNb);
-    return k < nb ? step_items(nb, k, 0, true).total() : 0;
+    return nb > 1 && k < nb ? step_items(nb, k, 0, true).total() : 0;
   }
   return 0;
 }

@@ -404,6 +404,7 @@ __device__ inline void crit_each(F f) {
 
 // Step 0's diagonal block: the original diagonal is saved for the pivot test, block 0 is
 // factored and inverted (one workgroup).  All global loads are issued before the first store.
+// With n <= 64 that is the whole factorisation: no step follows.
 __device__ __attribute__((always_inline)) inline void chol_prologue_block(const CholArgs& a) {
   __shared__ double S[kNb][kTL];
   __shared__ double Y[kNb][kTL];
@@ -433,13 +434,39 @@ __device__ __attribute__((always_inline)) inline void chol_prologue_block(const 
     S[r][q] = (r < kb && q < kb) ? v[u] : (r == q ? 1.0 : 0.0);
   }
   if (threadIdx.x < kNb) D0[threadIdx.x] = d0v;
-  block_factor_inv(S, Y, buf, D0, a.st);
+  block_factor_inv(S, Y, buf, D0, a.st, kb);
   store_y(Y, a, 0);
+  if (a.n > kNb) return;
+  // one block is all there is: L^{-1} is Y, and R <- Y R here instead of in a launch of its own
+  // (6 us)
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int e = threadIdx.x + 256 * u, r = e >> 6, q = e & 63;
+    const double y = q <= r ? Y[r][q] : 0.0;
+    if (q > r) Y[r][q] = 0.0;
+    if (a.Li && r < kb && q < kb) a.Li[(int64_t)r * a.ldli + q] = y;
+  }
+  if (!a.R) return;
+  for (int64_t c0 = 0; c0 < a.nrhs; c0 += kNb) {
+    const int cols = (int)(a.nrhs - c0 < kNb ? a.nrhs - c0 : kNb);
+    double pr[16];
+    tile_fetch(pr, a.R + c0, a.ldr, kb, cols);
+    tile_put(S, pr);
+    __syncthreads();
+    f64x4 acc[2][2];
+    acc_zero(acc);
+    mm64<false, false>(Y, S, acc);
+    acc_each(acc, [&](int r, int q, double v) {
+      if (r < kb && q < cols) a.R[(int64_t)r * a.ldr + c0 + q] = v;
+    });
+    __syncthreads();
+  }
 }
 
-// L^{-1} starts as the identity (the substitution works on it in place): element e of n x n.
+// L^{-1} starts as the identity (the substitution works on it in place; n > 64): element e of n x n.
 __device__ inline void chol_linv_init(const CholArgs& a, int64_t e) {
-  if (a.Li && e < a.n * a.n) {
+  if (a.Li && a.n > kNb && e < a.n * a.n) {
     const int64_t r = e / a.n, c = e % a.n;
     a.Li[r * a.ldli + c] = r == c ? 1.0 : 0.0;
   }
@@ -594,7 +621,7 @@ __device__ __attribute__((always_inline)) inline void chol_step_item(const CholA
       __syncthreads();
       if (w == 0) leaf_store_y(X, 0, y0);
       __syncthreads();
-      block_factor_rest(Z, X, buf, D0, a.st, bad_any);
+      block_factor_rest(Z, X, buf, D0, a.st, bad_any, (int)ri);
       store_y(X, a, k + 1);
       return;
     }

@@ -84,10 +84,10 @@ int chol_solve_lower(double* A, int64_t n, int64_t lda, double* R, int64_t nrhs,
   a.Yb = ws + n;
   a.st = st;
   const int64_t cr = a.R ? ceil_div(nrhs, (int64_t)kNb) : 0;
-  const unsigned init = Linv ? (unsigned)ceil_div(n * n, (int64_t)256) : 0u;
+  const unsigned init = Linv && nb > 1 ? (unsigned)ceil_div(n * n, (int64_t)256) : 0u;
   chol_prologue_kernel<<<1 + init, 256, 0, stream>>>(a);
   VL_LAUNCH_CHECK();
-  for (int64_t k = 0; k < nb; ++k) {
+  for (int64_t k = 0; nb > 1 && k < nb; ++k) {
     const int64_t items = step_items(nb, k, cr, Linv != nullptr).total();
     if (items == 0) continue;
     chol_step_kernel<<<(unsigned)items, 256, 0, stream>>>(a, k);

@@ -198,15 +198,24 @@ constexpr int kFactorBuf = 3 * kLeaf * kLeaf;
 //
 // block_factor_rest is the part after leaf 0: it starts once Y's block (0, 0) holds the leaf's
 // inverse and S holds the input (a workgroup barrier after those writes); bad_any carries the
-// pivot test of leaf 0.
+// pivot test of leaf 0.  Leaves wholly past kb are the identity with zeros below: they are written,
+// not factored (a leaf is about 2 us of one chain).  With the scaling of R and L^{-1} in the same
+// launch where n <= 64, n = 10 takes 9.9 us in one launch (20 in two), n = 100 one leaf less.
 __device__ __attribute__((always_inline)) inline void block_factor_rest(double (*S)[kLd],
                                                                          double (*Y)[kLd],
                                                                          double* buf,
                                                                          const double* D0,
                                                                          int32_t* st,
-                                                                         bool bad_any) {
+                                                                         bool bad_any, int kb) {
   const int tid = threadIdx.x, w = tid >> 6;
-  constexpr int kB = kNb / kLeaf;  // 4 block rows
+  const int kB = (kb + kLeaf - 1) / kLeaf;  // block rows that hold any of the kb
+  if (kB < kNb / kLeaf) {
+    const int n0 = kB * kLeaf, rows = kNb - n0;
+    for (int e = tid; e < rows * kNb; e += 256) {
+      const int r = n0 + e / kNb, q = e % kNb;
+      Y[r][q] = r == q ? 1.0 : 0.0;
+    }
+  }
   for (int sb = 0; sb < kB - 1; ++sb) {
     const int b = sb * kLeaf;
     // panel: wave w takes block row sb + 1 + w (reads and writes only its own block)
@@ -255,12 +264,12 @@ __device__ __attribute__((always_inline)) inline void block_factor_inv(double (*
                                                                         double (*Y)[kLd],
                                                                         double* buf,
                                                                         const double* D0,
-                                                                        int32_t* st) {
+                                                                        int32_t* st, int kb) {
   __syncthreads();
   bool bad_any = false;
   if ((threadIdx.x >> 6) == 0) leaf_factor_inv(S, Y, D0, 0, bad_any);
   __syncthreads();
-  block_factor_rest(S, Y, buf, D0, st, bad_any);
+  block_factor_rest(S, Y, buf, D0, st, bad_any, kb);
 }
 
 }  // namespace vl

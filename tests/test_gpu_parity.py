@@ -525,3 +525,32 @@ def test_order_ties_and_equal_high_words(api, dev, m):
         rest = Mk[live]
         assert margin[k] == (rest.min() - Mk[c] if rest.size else np.inf), k
         M = M - np.maximum(S[c], 0.0) ** 2
+
+
+@pytest.mark.parametrize("m", [1, 2, 15, 16, 17, 32, 33, 48, 49, 63, 64, 65, 80, 81, 97, 113, 129])
+def test_factorisation_block_edges(api, dev, m):
+    """B0, B_tau of a well-conditioned covariance and M, c of a VAR(1) fit at the edges of the
+    factorisation's blocks (16-column leaves, 64-column panels; one panel alone also scales the
+    right-hand sides) against NumPy in FP64: both are backward stable, the condition numbers are
+    below 1e3, so 1e-10 is 1e3 times their rounding."""
+    rng = np.random.default_rng(m)
+    A = rng.standard_normal((4 * m + 20, m))
+    Cov = A.T @ A / len(A) + 0.1 * np.eye(m)
+    M = 0.3 * rng.standard_normal((2, m, m))
+    order = rng.permutation(m).astype(np.int32)
+    B0, Bl = (t.cpu().numpy() for t in api.estimate_B(_dev(Cov, dev), _dev(M, dev),
+                                                       _dev(order, dev)))
+    oB0, oBl = np.zeros((m, m)), np.zeros((2, m, m))
+    for k in range(1, m):
+        pa = order[:k]
+        oB0[order[k], pa] = np.linalg.solve(Cov[np.ix_(pa, pa)], Cov[pa, order[k]])
+    for t in range(2):
+        oBl[t] = (np.eye(m) - oB0) @ M[t]
+    np.testing.assert_allclose(B0, oB0, rtol=0, atol=1e-10)
+    np.testing.assert_allclose(Bl, oBl, rtol=0, atol=1e-10)
+    X = rng.standard_normal((6 * m + 40, m)).astype(np.float32)
+    fM, fc = (t.cpu().numpy() for t in api.fit_var(_dev(X, dev), 1)[:2])
+    D = np.hstack([X[:-1].astype(np.float64), np.ones((len(X) - 1, 1))])
+    W = np.linalg.lstsq(D, X[1:].astype(np.float64), rcond=None)[0]
+    np.testing.assert_allclose(fM.reshape(m, m), W[:m].T, rtol=0, atol=1e-10)
+    np.testing.assert_allclose(fc, W[m], rtol=0, atol=1e-10)
