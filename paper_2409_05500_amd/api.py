@@ -44,6 +44,29 @@ class DeviceStatus:
         check(code, where)
 
 
+class _OwnStatus(DeviceStatus):
+    """A call's own status words.  Every library call sets its word itself before a kernel can
+    raise, so they start uninitialised (a fill is a launch of its own)."""
+
+    def __init__(self, device, count: int = 1):
+        self.t = torch.empty(count, dtype=torch.int32, device=device)
+
+    def word(self, i: int) -> "_StatusWord":
+        return _StatusWord(self.t.data_ptr() + 4 * i)
+
+    def read_all(self, names) -> None:
+        """Reads every word in one copy (one synchronisation) and raises the first error."""
+        for code, name in zip(self.t.tolist(), names):
+            check(int(code), name)
+
+
+class _StatusWord:
+    """One word of an _OwnStatus, as the `status` of a stage."""
+
+    def __init__(self, ptr: int):
+        self.ptr = ptr
+
+
 def _require(t: torch.Tensor, dtype, name: str) -> None:
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
@@ -64,7 +87,7 @@ def fit_var(X: torch.Tensor, p: int, prec="mixed", status: "DeviceStatus | None"
     E = torch.empty((n - p, m), dtype=torch.float32, device=dev)
     nb = lib.varlingam_fit_var_workspace_bytes(n, m, p, _prec(prec))
     ws = _workspace(nb, dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.varlingam_fit_var(X.data_ptr(), n, m, X.stride(0), p, _prec(prec), M.data_ptr(),
                                 c.data_ptr(), E.data_ptr(), E.stride(0), ws.data_ptr(),
                                 ws.numel(), st.ptr, _stream_ptr(dev)), "varlingam_fit_var")
@@ -84,7 +107,7 @@ def select_lag(X: torch.Tensor, p_max: int, status: "DeviceStatus | None" = None
     bic = torch.empty(p_max, dtype=torch.float64, device=dev)
     best = torch.empty(2, dtype=torch.int32, device=dev)
     ws = _workspace(lib.varlingam_select_lag_workspace_bytes(n, m, p_max), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.varlingam_select_lag(X.data_ptr(), n, m, X.stride(0), p_max, logdet.data_ptr(),
                                    aic.data_ptr(), bic.data_ptr(), best.data_ptr(),
                                    ws.data_ptr(), ws.numel(), st.ptr, _stream_ptr(dev)),
@@ -113,7 +136,7 @@ def pairwise_stats(E: torch.Tensor, prec="mixed", status: "DeviceStatus | None" 
     Cov = torch.empty((m, m), dtype=torch.float64, device=dev)
     nb = lib.pairwise_stats_workspace_bytes(n_eff, m, _prec(prec))
     ws = _workspace(nb, dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.pairwise_stats(E.data_ptr(), n_eff, m, E.stride(0), _prec(prec), Hx.data_ptr(),
                              Hr.data_ptr(), S.data_ptr(), Cov.data_ptr(), ws.data_ptr(),
                              ws.numel(), st.ptr, _stream_ptr(dev)), "pairwise_stats")
@@ -141,7 +164,7 @@ def pairwise_stats_noalloc(E: torch.Tensor, prec="mixed", status: "DeviceStatus 
         if t.dtype != torch.float64 or not t.is_cuda or tuple(t.shape) != shape or \
                 not t.is_contiguous():
             raise ValueError("out must be contiguous f64 device tensors (m), (m, m) x 3")
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.pairwise_stats_noalloc(E.data_ptr(), n_eff, m, E.stride(0), _prec(prec),
                                      Hx.data_ptr(), Hr.data_ptr(), S.data_ptr(), Cov.data_ptr(),
                                      st.ptr, _stream_ptr(dev)), "pairwise_stats_noalloc")
@@ -162,7 +185,7 @@ def pairwise_stats_save(E: torch.Tensor, prec="mixed", status: "DeviceStatus | N
     Cov = torch.empty((m, m), dtype=torch.float64, device=dev)
     saved = torch.empty(lib.pairwise_stats_saved_doubles(m), dtype=torch.float64, device=dev)
     ws = _workspace(lib.pairwise_stats_workspace_bytes(n_eff, m, _prec(prec)), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.pairwise_stats_save(E.data_ptr(), n_eff, m, E.stride(0), _prec(prec),
                                   Hx.data_ptr(), Hr.data_ptr(), S.data_ptr(), Cov.data_ptr(),
                                   saved.data_ptr(), ws.data_ptr(), ws.numel(), st.ptr,
@@ -189,7 +212,7 @@ def pairwise_stats_backward(E: torch.Tensor, G: torch.Tensor, prec="mixed",
     dE = torch.empty((n_eff, m), dtype=torch.float32, device=dev)
     nb = lib.pairwise_stats_backward_workspace_bytes(n_eff, m, _prec(prec))
     ws = _workspace(nb, dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.pairwise_stats_backward(E.data_ptr(), n_eff, m, E.stride(0), _prec(prec),
                                       saved.data_ptr() if saved is not None else None,
                                       G.data_ptr(), dE.data_ptr(), dE.stride(0), ws.data_ptr(),
@@ -243,7 +266,7 @@ def approx_order(S: torch.Tensor, status: "DeviceStatus | None" = None):
     order = torch.empty(m, dtype=torch.int32, device=dev)
     margin = torch.empty(m, dtype=torch.float64, device=dev)
     ws = _workspace(lib.approx_order_workspace_bytes(m), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.approx_order(S.contiguous().data_ptr(), m, order.data_ptr(), margin.data_ptr(),
                            ws.data_ptr(), ws.numel(), st.ptr, _stream_ptr(dev)), "approx_order")
     if status is None:
@@ -272,7 +295,7 @@ def approx_order_certified(E: torch.Tensor, S: torch.Tensor, eps_S: float = CERT
     margin = torch.empty(m, dtype=torch.float64, device=dev)
     refined = torch.empty(m, dtype=torch.int32, device=dev)
     ws = _workspace(lib.approx_order_certified_workspace_bytes(n_eff, m), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     nref = C.c_int64(0)
     check(lib.approx_order_certified(E.data_ptr(), n_eff, m, E.stride(0), S.data_ptr(),
                                      float(eps_S), order.data_ptr(), margin.data_ptr(),
@@ -293,7 +316,7 @@ def order_iterative(E: torch.Tensor, prec="mixed", status: "DeviceStatus | None"
     order = torch.empty(m, dtype=torch.int32, device=dev)
     margin = torch.empty(m, dtype=torch.float64, device=dev)
     ws = _workspace(lib.varlingam_order_iterative_workspace_bytes(n_eff, m, _prec(prec)), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.varlingam_order_iterative(E.data_ptr(), n_eff, m, E.stride(0), _prec(prec),
                                         order.data_ptr(), margin.data_ptr(), ws.data_ptr(),
                                         ws.numel(), st.ptr, _stream_ptr(dev)),
@@ -313,7 +336,7 @@ def order_hybrid(E: torch.Tensor, k_exact: int, prec="mixed",
     order = torch.empty(m, dtype=torch.int32, device=dev)
     margin = torch.empty(m, dtype=torch.float64, device=dev)
     ws = _workspace(lib.varlingam_order_hybrid_workspace_bytes(n_eff, m, _prec(prec)), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.varlingam_order_hybrid(E.data_ptr(), n_eff, m, E.stride(0), _prec(prec), k_exact,
                                      order.data_ptr(), margin.data_ptr(), ws.data_ptr(),
                                      ws.numel(), st.ptr, _stream_ptr(dev)),
@@ -333,7 +356,7 @@ def estimate_B(Cov: torch.Tensor, M: torch.Tensor, order: torch.Tensor,
     B0 = torch.zeros((m, m), dtype=torch.float64, device=dev)
     Bl = torch.empty((max(p, 1), m, m), dtype=torch.float64, device=dev)
     ws = _workspace(lib.estimate_B_workspace_bytes(m, p), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     Mp = M.contiguous().data_ptr() if p > 0 else None
     check(lib.estimate_B(Cov.contiguous().data_ptr(), Mp, order.contiguous().data_ptr(), m, p,
                          B0.data_ptr(), Bl.data_ptr() if p > 0 else None, ws.data_ptr(),
@@ -355,7 +378,7 @@ def prune(X: torch.Tensor, p: int, order: torch.Tensor, B0: torch.Tensor, B_lags
     Blo = torch.empty((p, m, m), dtype=torch.float64, device=dev)
     info = torch.empty((m, 3), dtype=torch.int32, device=dev)
     ws = _workspace(lib.varlingam_prune_workspace_bytes(n, m, p, max_steps), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     K = order.to(torch.int32).contiguous()
     B0c = B0.to(torch.float64).contiguous()
     Blc = B_lags.to(torch.float64).contiguous()
@@ -400,15 +423,13 @@ def fit(X: torch.Tensor, p: int, prec="mixed", verify: bool = True) -> FitResult
     ordering -> B0 and B_tau, enqueued back to back on the current stream.  With `verify`, the
     four status words are read (one synchronisation) at the end."""
     dev = X.device
-    st = [DeviceStatus(dev) for _ in range(4)]
-    M, c, E = fit_var(X, p, prec, status=st[0])
-    Hx, Hr, S, Cov = pairwise_stats(E, prec, status=st[1])
-    order, margin = approx_order(S, status=st[2])
-    B0, Bl = estimate_B(Cov, M, order, status=st[3])
+    st = _OwnStatus(dev, 4)
+    M, c, E = fit_var(X, p, prec, status=st.word(0))
+    Hx, Hr, S, Cov = pairwise_stats(E, prec, status=st.word(1))
+    order, margin = approx_order(S, status=st.word(2))
+    B0, Bl = estimate_B(Cov, M, order, status=st.word(3))
     if verify:
-        for s, name in zip(st, ("varlingam_fit_var", "pairwise_stats", "approx_order",
-                                "estimate_B")):
-            s.read(name)
+        st.read_all(("varlingam_fit_var", "pairwise_stats", "approx_order", "estimate_B"))
     return FitResult(M, c, E, Hx, Hr, S, Cov, order, margin, B0, Bl)
 
 
@@ -577,7 +598,7 @@ def var_simulate(M: torch.Tensor, intercept: torch.Tensor, X0: torch.Tensor, E: 
     _require(X0, torch.float32, "X0")
     _require(E, torch.float32, "E")
     ws = _workspace(lib.varlingam_var_simulate_workspace_bytes(m, p), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.varlingam_var_simulate(Mc.data_ptr(), cc.data_ptr(), m, p, X0.data_ptr(),
                                      X0.stride(0), E.data_ptr(), E.shape[0], E.stride(0),
                                      Ic.data_ptr(), R, T, out.data_ptr(), m, out.stride(0),
@@ -605,7 +626,7 @@ def edge_frequency(orders: torch.Tensor, B0s: torch.Tensor, B_lags: torch.Tensor
     Lc = B_lags.contiguous() if p > 0 else None
     Sc = problem_status.to(torch.int32).contiguous() if problem_status is not None else None
     ws = _workspace(lib.varlingam_edge_frequency_workspace_bytes(K, m), dev)
-    st = status if status is not None else DeviceStatus(dev)
+    st = status if status is not None else _OwnStatus(dev)
     check(lib.varlingam_edge_frequency(Oc.data_ptr(), Bc.data_ptr(),
                                        Lc.data_ptr() if p > 0 else None, K, m, p,
                                        float(threshold),
