@@ -150,6 +150,7 @@ int colmeans(const float* A, int64_t lda, const int64_t* colmap, int64_t ncol, i
                                                              scratch, reset);
     VL_LAUNCH_CHECK();
   }
+  if (o.sums_only) return VL_OK;
   colmean_final_kernel<<<(unsigned)ceil_div(ncol, 64), 64, 0, stream>>>(
       scratch, ncol, splits, K, mean, o.rep, o.rep_m, o.rep_blocks, o.range_exp,
       o.centre_m > 0 ? o.centre_m : ncol, o.range_exp_own, st);
@@ -213,6 +214,29 @@ __global__ __launch_bounds__(256, 2) void gram_tn_f64_kernel(
   gram_tile_origin(sym, i0, j0);
   gram_tile_f64(A, lda, mapA, muA, M, B, ldb, mapB, muB, N, i0, j0, kb, ke,
                 P + (int64_t)blockIdx.z * M * N, N, 1.0, false, sym && i0 == j0);
+}
+
+// The same for A^T A (lower tiles) with the means still in the splits' sums: each workgroup adds up
+// its own 128 columns' (the means are left in mean, by every workgroup that has them: the same
+// values), instead of a launch between the sums and the products.
+__global__ __launch_bounds__(256, 2) void gram_tn_f64_sums_kernel(
+    const float* __restrict__ A, int64_t lda, int64_t M, int64_t K, int64_t kchunk,
+    const double* __restrict__ sums, int nsums, double* mean, double* __restrict__ P, int32_t* st) {
+  const int64_t kb = (int64_t)blockIdx.z * kchunk;
+  const int64_t ke = kb + kchunk < K ? kb + kchunk : K;
+  int64_t i0, j0;
+  gram_tile_origin(1, i0, j0);
+  if (threadIdx.x < 2 * kGT) {
+    const int64_t c = threadIdx.x < kGT ? i0 + threadIdx.x : j0 + threadIdx.x - kGT;
+    if (c < M) {
+      const double v = sum_splits_at(sums, nsums, M, c) / (double)K;
+      if (!isfinite(v)) raise_status(st, VL_ERR_NONFINITE);
+      mean[c] = v;
+    }
+  }
+  __syncthreads();
+  gram_tile_f64(A, lda, nullptr, mean, M, A, lda, nullptr, mean, M, i0, j0, kb, ke,
+                P + (int64_t)blockIdx.z * M * M, M, 1.0, false, i0 == j0);
 }
 
 // C[i][j] = sum_t (A(t,i) - muA[i]) B64[t][j] with an FP64 right operand (not centred): the
@@ -331,6 +355,25 @@ int sum_splits(const double* P, int splits, int64_t M, int64_t N, double scale, 
                                                                        C, ldc);
   VL_LAUNCH_CHECK();
   return VL_OK;
+}
+
+bool cov_sums_fused(int64_t M, int64_t K) {
+  return colmean_splits(K) <= 64 &&
+         ceil_div(M, (int64_t)kGT) * (ceil_div(M, (int64_t)kGT) + 1) / 2 * gram_splits_f64(M, M, K) <=
+             512;
+}
+
+int cov_from_sums(const float* A, int64_t lda, int64_t M, int64_t K, const double* sums,
+                  double* mean, double scale, double* C, double* scratch, int32_t* st,
+                  hipStream_t stream) {
+  const int64_t kchunk = round_up(ceil_div(K, (int64_t)gram_splits_f64(M, M, K)), kGK);
+  const int splits = (int)ceil_div(K, kchunk);
+  const int64_t tm = ceil_div(M, (int64_t)kGT);
+  gram_tn_f64_sums_kernel<<<dim3((unsigned)(tm * (tm + 1) / 2), 1, (unsigned)splits), 256, 0,
+                            stream>>>(A, lda, M, K, kchunk, sums, colmean_splits(K), mean, scratch,
+                                      st);
+  VL_LAUNCH_CHECK();
+  return sum_splits(scratch, splits, M, M, scale, C, M, true, stream);
 }
 
 int gram_tn(const float* A, int64_t lda, const int64_t* mapA, const double* muA, int64_t M,

@@ -13,6 +13,7 @@ inline int colmean_splits(int64_t K) {
 // Options of colmeans():
 //   reset        the call's first kernel: the status word is set to VL_OK before anything raises;
 //   have_sums    scratch already holds the splits' sums (of this K and ncol);
+//   sums_only    the splits' sums are left in scratch, no means are formed;
 //   rep          rep[h * rep_m + c] = mean[c] for c < rep_m and h < rep_blocks as well;
 //   range_exp    range_exp[c] = e with |A(t, c) - mean[c mod centre_m]| < 2^e for every t < K
 //                (from the column's range; centre_m = 0: ncol); scratch: 3 splits ncol doubles;
@@ -20,6 +21,7 @@ inline int colmean_splits(int64_t K) {
 struct ColmeanOptions {
   bool reset = false;
   bool have_sums = false;
+  bool sums_only = false;
   double* rep = nullptr;
   int64_t rep_m = 0, rep_blocks = 0;
   int32_t* range_exp = nullptr;
@@ -63,6 +65,18 @@ inline int gram_splits_f64(int64_t M, int64_t N, int64_t K) {
   if (s > old) s = few > old ? (s < few ? s : few) : old;
   return (int)(s < 1 ? 1 : s);
 }
+
+// Whether a covariance forms its means inside the FP64 Gram, from the column sums' splits
+// (cov_from_sums): where one round of workgroups takes it and a column has at most 64 sums, four
+// groups of loads (2 us; the launch it saves takes 3.5 at m = 50, n = 5000 and 14 with 256 sums,
+// which each of several rounds would pay again).
+bool cov_sums_fused(int64_t M, int64_t K);
+
+// C = scale (A - mean)^T (A - mean), M x M, with mean (written) from the colmean_splits(K) sums of
+// each column; scratch as for gram_tn() and apart from sums.  Raises VL_ERR_NONFINITE.
+int cov_from_sums(const float* A, int64_t lda, int64_t M, int64_t K, const double* sums,
+                  double* mean, double scale, double* C, double* scratch, int32_t* st,
+                  hipStream_t stream);
 
 // Arithmetic of gram_tn():
 //   kFp32        FP32 MFMA, FP32 accumulation over the whole split;

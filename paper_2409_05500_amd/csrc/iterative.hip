@@ -228,14 +228,14 @@ int run_order_iterative(const float* E, int64_t n_eff, int64_t m, int64_t lde, i
     if (u >= 2) {
       float* next = w.D[k & 1];
       // the sums go where the next step's plan keeps them (past this step's means, read here: the
-      // scratch follows the means, the covariance and the moments)
+      // sums follow the means, the covariance and the moments)
       PairwiseWs nw;
       pairwise_ws_bytes(plan_pairwise(n_eff, std::max<int64_t>(u - 1, 2)), w.pw, &nw);
       const int splits = colmean_splits(n_eff);
       iter_refine_kernel<<<dim3((unsigned)ceil_div(u - 1, (int64_t)64), (unsigned)splits), 256, 0,
                            stream>>>(cur, ldc, n_eff, u, pw.mu, w.Cov, w.pick, idx_in,
                                      w.idx[(k + 1) & 1], next, m,
-                                     ceil_div(n_eff, (int64_t)splits), nw.scratch);
+                                     ceil_div(n_eff, (int64_t)splits), nw.sums);
       VL_LAUNCH_CHECK();
       cur = next;
       ldc = m;

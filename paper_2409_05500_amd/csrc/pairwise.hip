@@ -155,6 +155,7 @@ PairwisePlan plan_pairwise(int64_t n_eff, int64_t m, bool compensated, bool slic
   p.n_pad = (int64_t)p.nc * p.chunk_len;
   p.items = p.tiles * p.nc;
   p.blocks = round_up(ceil_div(p.items, 4), 8);
+  p.fused = !sliced && cov_sums_fused(m, n_eff);
   return p;
 }
 
@@ -169,6 +170,7 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out) {
   char* region = base ? static_cast<char*>(base) + c.used : nullptr;
   Carver a(region);                              // stage 1
   w.scratch = a.take<double>(scratch_doubles(p));
+  w.sums = p.fused ? a.take<double>((size_t)colmean_splits(p.n_eff) * p.m) : w.scratch;
   if (p.sliced) {
     w.slices = a.take<int8_t>(slice_bytes(p.m, p.n_eff));
     w.ex = a.take<int32_t>(p.m);
@@ -272,9 +274,16 @@ int run_pairwise(const PairwisePlan& p, const PairwiseWs& w, const float* E, int
     o.reset = start != PairwiseStart::kContinue;
     o.have_sums = start == PairwiseStart::kContinue;
     if (p.sliced) o.range_exp = w.ex;
-    int rc = colmeans(E, lde, nullptr, m, n_eff, w.mu, w.scratch, st, stream, o);
+    const bool fp32 = (prec & ~VL_PAIRWISE_COMPENSATED) == VL_PREC_FP32;
+    const bool fused = p.fused && !fp32;
+    o.sums_only = fused;
+    int rc = colmeans(E, lde, nullptr, m, n_eff, w.mu, w.sums, st, stream, o);
     if (rc) return rc;
-    if (p.sliced) {
+    if (fused) {
+      rc = cov_from_sums(E, lde, m, n_eff, w.sums, w.mu, 1.0 / (double)n_eff, cov, w.scratch, st,
+                         stream);
+      if (rc) return rc;
+    } else if (p.sliced) {
       // the covariance from int8 slices of E's centred columns
       rc = slice_columns(E, lde, m, 1, 0, n_eff, w.mu, w.ex, w.slices, stream);
       if (rc) return rc;
@@ -287,7 +296,6 @@ int run_pairwise(const PairwisePlan& p, const PairwiseWs& w, const float* E, int
       if (rc) return rc;
     } else {
       // covariance: exact products and FP64 sums (plain FP32 mode: FP32 MFMA throughout)
-      const bool fp32 = (prec & ~VL_PAIRWISE_COMPENSATED) == VL_PREC_FP32;
       rc = gram_tn(E, lde, nullptr, w.mu, m, E, lde, nullptr, w.mu, m, n_eff,
                    fp32 ? GramMode::kFp32 : GramMode::kFp64, 1.0 / (double)n_eff, cov, m,
                    w.scratch, stream, true);

@@ -7,6 +7,7 @@ namespace vl {
 struct PairwisePlan {
   bool comp = false;      // compensated moment sums, FP64 partials
   bool sliced = false;    // covariance from int8 slices (VL_PREC_SLICED)
+  bool fused = false;     // means formed inside the FP64 covariance (cov_sums_fused)
   int64_t m = 0, n_eff = 0;
   int nt = 0;             // micro-tiles per side (4 variables each)
   int64_t m_pad = 0;      // nt * 4
@@ -21,7 +22,8 @@ struct PairwisePlan {
 struct PairwiseWs {
   double* mu = nullptr;       // m column means
   double* cov = nullptr;      // m x m covariance when the caller passes none
-  double* scratch = nullptr;  // split partials of the column sums / Gram
+  double* sums = nullptr;     // split partials of the column sums (fused: apart from scratch)
+  double* scratch = nullptr;  // split partials of the Gram
   float* Xs = nullptr;        // m_pad x n_pad standardised, variable-major
   float2* coef = nullptr;     // m_pad x m_pad pair coefficients
   float* partU = nullptr;     // nc x m x m (plain sums)
@@ -46,7 +48,7 @@ int standardize_to(const float* E, int64_t lde, int64_t n_eff, int64_t m, const 
                    const double* cov, float* Xs, int64_t n_pad, int64_t m_pad, int32_t* st,
                    hipStream_t stream, float2* coef = nullptr, int nt = 0, int32_t* clist = nullptr);
 // kFirst: the call's first kernels (the status word is set to VL_OK); kContinue: a step of a call
-// under way, with the splits' column sums of E already in the workspace's scratch.
+// under way, with the splits' column sums of E already in the workspace's sums.
 enum class PairwiseStart { kFirst, kContinue };
 
 // mom (nullable): 2 m^2 doubles, (A, B) per ordered pair, for tests and the backward pass.

@@ -58,3 +58,17 @@ def test_batched_and_single_var_edges(api, shape):
     assert st == [0, 0]
     assert np.abs(single - M).max() <= 1e-9 * np.abs(M).max()
     assert np.abs(res[0].M.cpu().numpy() - M).max() <= 1e-9 * np.abs(M).max()
+
+
+@pytest.mark.parametrize("m,n", [(3, 8319), (3, 8320), (64, 8319), (64, 8320), (200, 8192),
+                                 (400, 8319), (600, 1100)])
+def test_covariance_means_inside_and_before(api, m, n):
+    """At the line between means formed inside the Gram (at most 64 column sums, one round of
+    workgroups) and before it, and at its largest; with a NaN in the last column's last row."""
+    test_covariance_edges(api, m, n)
+    from paper_2409_05500_amd._lib import VarLiNGAMError, VL_ERR_NONFINITE
+    E = _data(n, m, 5)
+    E[n - 1, m - 1] = np.nan
+    with pytest.raises(VarLiNGAMError) as ei:
+        api.pairwise_stats(torch.from_numpy(E).cuda(), "mixed")
+    assert ei.value.code == VL_ERR_NONFINITE
