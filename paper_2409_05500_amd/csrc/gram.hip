@@ -108,28 +108,44 @@ __device__ inline double sum_splits_at(const double* __restrict__ P, int splits,
   return s;
 }
 
-__global__ void colmean_final_kernel(const double* __restrict__ part, int64_t ncol, int splits,
-                                     int64_t K, double* __restrict__ mean,
-                                     double* __restrict__ rep, int64_t rep_m,
-                                     int64_t rep_blocks, int32_t* __restrict__ range_exp,
-                                     int64_t centre_m, int32_t* __restrict__ range_exp_own,
-                                     int32_t* st) {
-  int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// kRange: 64 columns by four waves, each over one of a column's four lists (its sums, those of its
+// centre column c mod centre_m, minima, maxima): one after another they took 16 us at 1200 columns
+// of 78 splits, side by side 6.7.
+template <bool kRange>
+__global__ __launch_bounds__(kRange ? 256 : 64) void colmean_final_kernel(
+    const double* __restrict__ part, int64_t ncol, int splits, int64_t K,
+    double* __restrict__ mean, double* __restrict__ rep, int64_t rep_m, int64_t rep_blocks,
+    int32_t* __restrict__ range_exp, int64_t centre_m, int32_t* __restrict__ range_exp_own,
+    int32_t* st) {
+  const int lane = threadIdx.x & 63;
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t cc = c < ncol ? c : ncol - 1, sn = (int64_t)splits * ncol;
+  double v;
+  __shared__ double list[kRange ? 4 : 1][64];
+  if constexpr (kRange) {
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double s = w < 2 ? 0.0 : (w == 2 ? INFINITY : -INFINITY);
+    if (w == 0) s = sum_splits_at(part, splits, ncol, cc);
+    else if (w == 1) s = sum_splits_at(part, splits, ncol, cc % centre_m);
+    else if (w == 2) each_split(part + sn, splits, ncol, cc, [&](double x) { s = fmin(s, x); });
+    else each_split(part + 2 * sn, splits, ncol, cc, [&](double x) { s = fmax(s, x); });
+    list[w][lane] = s;
+    __syncthreads();
+    if (w > 0) return;
+    v = s / (double)K;
+  } else {
+    v = sum_splits_at(part, splits, ncol, cc) / (double)K;
+  }
   if (c >= ncol) return;
-  const double v = sum_splits_at(part, splits, ncol, c) / (double)K;
   // a NaN or infinity in the column makes its sum one (finite FP32 values cannot overflow FP64)
   if (!isfinite(v)) raise_status(st, VL_ERR_NONFINITE);
   mean[c] = v;
   if (rep && c < rep_m)
     for (int64_t h = 0; h < rep_blocks; ++h) rep[h * rep_m + c] = v;
-  if (range_exp) {
+  if constexpr (kRange) {
     // |x - mu0| <= max(max - mu0, mu0 - min) over the column, mu0 the mean of column
     // c mod centre_m (the same sum, so the same value)
-    const int64_t sn = (int64_t)splits * ncol, c0 = c % centre_m;
-    const double mu0 = c0 == c ? v : sum_splits_at(part, splits, ncol, c0) / (double)K;
-    double mn = INFINITY, mx = -INFINITY;
-    each_split(part + sn, splits, ncol, c, [&](double v) { mn = fmin(mn, v); });
-    each_split(part + 2 * sn, splits, ncol, c, [&](double v) { mx = fmax(mx, v); });
+    const double mu0 = list[1][lane] / (double)K, mn = list[2][lane], mx = list[3][lane];
     range_exp[c] = exponent_of(fmax(mx - mu0, mu0 - mn));
     if (range_exp_own) range_exp_own[c] = exponent_of(fmax(mx - v, v - mn));
   }
@@ -151,9 +167,15 @@ int colmeans(const float* A, int64_t lda, const int64_t* colmap, int64_t ncol, i
     VL_LAUNCH_CHECK();
   }
   if (o.sums_only) return VL_OK;
-  colmean_final_kernel<<<(unsigned)ceil_div(ncol, 64), 64, 0, stream>>>(
-      scratch, ncol, splits, K, mean, o.rep, o.rep_m, o.rep_blocks, o.range_exp,
-      o.centre_m > 0 ? o.centre_m : ncol, o.range_exp_own, st);
+  const unsigned g = (unsigned)ceil_div(ncol, 64);
+  const int64_t cm = o.centre_m > 0 ? o.centre_m : ncol;
+  if (o.range_exp)
+    colmean_final_kernel<true><<<g, 256, 0, stream>>>(scratch, ncol, splits, K, mean, o.rep, o.rep_m,
+                                                      o.rep_blocks, o.range_exp, cm,
+                                                      o.range_exp_own, st);
+  else
+    colmean_final_kernel<false><<<g, 64, 0, stream>>>(scratch, ncol, splits, K, mean, o.rep, o.rep_m,
+                                                      o.rep_blocks, nullptr, cm, nullptr, st);
   VL_LAUNCH_CHECK();
   return VL_OK;
 }

@@ -280,32 +280,106 @@ static int var_residual(const VarPlan& v, const VarWs& w, const float* X, int64_
 // h = tau1 - tau2, the window sum sum_t xt_j(t - tau2) xt_i(t - tau1) is F_h[j][i] with the
 // tau2 rows that the window gains at its start added and the tau2 rows it loses at its end taken
 // away, and G = that sum - n_eff d_tau1[i] d_tau2[j].  R's block tau is F_tau^T (d_0 = 0).
-__global__ void var_assemble_kernel(const float* __restrict__ X, int64_t ldx,
-                                    const double* __restrict__ F, const double* __restrict__ mu,
-                                    int64_t m, int p, int64_t n, double* __restrict__ G,
-                                    double* __restrict__ R) {
-  const int64_t dz = m * p, nc = m * (p + 1);
-  int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < dz * dz) {
-    const int64_t r = e / dz, c = e % dz;
-    if (c > r) return;
-    const int64_t t1 = r / m + 1, i = r % m, t2 = c / m + 1, j = c % m, h = t1 - t2;
-    const double ci = mu[i], cj = mu[j];
-    double wv = F[j * nc + h * m + i];
-    for (int64_t s = p - t2; s < p; ++s)
-      wv += ((double)X[s * ldx + j] - cj) * ((double)X[(s - h) * ldx + i] - ci);
-    for (int64_t s = n - t2; s < n; ++s)
-      wv -= ((double)X[s * ldx + j] - cj) * ((double)X[(s - h) * ldx + i] - ci);
-    const double di = mu[t1 * m + i] - ci, dj = mu[t2 * m + j] - cj;
-    const double g = wv - (double)(n - p) * di * dj;
-    G[r * dz + c] = g;
-    G[c * dz + r] = g;
+// 64 x 64 tiles (lower ones of G, then R's), lanes along r = (tau1, i), so that F, the window's rows
+// and the mirrored half are read and written along memory; the other half passes through LDS.
+// Each thread forms four entries side by side: their loads are the only latency there is to
+// hide.  An entry a thread in row order took 35 us at m = 400, p = 4 and 11 at p = 2, this 17 and
+// 8.
+constexpr int kAT = 64;
+
+__global__ __launch_bounds__(1024) void var_assemble_kernel(
+    const float* __restrict__ X, int64_t ldx, const double* __restrict__ F,
+    const double* __restrict__ mu, int m, int p, int64_t n, int nt, double* __restrict__ G,
+    double* __restrict__ R) {
+  __shared__ double T[kAT][kAT + 1];
+  const int dz = m * p, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t nc = (int64_t)m * (p + 1);
+  constexpr int kQ = 4;
+  const int tri = nt * (nt + 1) / 2;
+  if ((int)blockIdx.x >= tri) {
+    // R[r][j] = F[j][m + r]
+    const int tm = (m + kAT - 1) / kAT, t = (int)blockIdx.x - tri;
+    const int r0 = (t / tm) * kAT, j0 = (t % tm) * kAT;
+    const int r = r0 + lane < dz ? r0 + lane : dz - 1;
+    double v[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const int j = j0 + wave + 16 * q;
+      v[q] = F[(j < m ? j : m - 1) * nc + m + r];
+    }
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) T[wave + 16 * q][lane] = v[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      const int rr = r0 + wave + 16 * q;
+      if (rr < dz && j0 + lane < m) R[(int64_t)rr * m + j0 + lane] = T[lane][wave + 16 * q];
+    }
     return;
   }
-  e -= dz * dz;
-  if (e >= dz * m) return;
-  const int64_t r = e / m, j = e % m;
-  R[r * m + j] = F[j * nc + m + r];
+  int ti = (int)((sqrt(8.0 * (double)blockIdx.x + 1.0) - 1.0) * 0.5);
+  while (ti * (ti + 1) / 2 > (int)blockIdx.x) --ti;
+  while ((ti + 1) * (ti + 2) / 2 <= (int)blockIdx.x) ++ti;
+  const int r0 = ti * kAT, c0 = ((int)blockIdx.x - ti * (ti + 1) / 2) * kAT;
+  const int r = r0 + lane < dz ? r0 + lane : dz - 1;
+  const int t1 = r / m + 1, i = r - (t1 - 1) * m;
+  const double ci = mu[i], di = mu[(int64_t)t1 * m + i] - ci;
+  int t2[kQ], j[kQ], h[kQ];
+  double cj[kQ], dj[kQ], wv[kQ];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    const int c = c0 + wave + 16 * q < dz ? c0 + wave + 16 * q : dz - 1;
+    t2[q] = c / m + 1;
+    j[q] = c - (t2[q] - 1) * m;
+    // (a diagonal tile's entries above the diagonal are not stored; their lag stays in range)
+    h[q] = t1 >= t2[q] ? t1 - t2[q] : 0;
+    cj[q] = mu[j[q]];
+    dj[q] = mu[(int64_t)t2[q] * m + j[q]] - cj[q];
+    wv[q] = F[j[q] * nc + (int64_t)h[q] * m + i];
+  }
+  // the window's gained, then lost, rows s = p - t2 .. p - 1 of its start and end; earlier ones
+  // count as zero
+  for (int side = 0; side < 2; ++side) {
+    const int64_t base = side ? n - p : 0;
+    for (int s = 0; s < p; ++s) {
+      float xj[kQ], xi[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        const int64_t t = base + s, u = t - h[q] > 0 ? t - h[q] : 0;
+        xj[q] = X[t * ldx + j[q]];
+        xi[q] = X[u * ldx + i];
+      }
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        const double x = mask_f64(((double)xj[q] - cj[q]), s >= p - t2[q]);
+        const double y = (double)xi[q] - ci;
+        wv[q] = side ? fma(-x, y, wv[q]) : fma(x, y, wv[q]);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    const int c = c0 + wave + 16 * q;
+    const double g = wv[q] - (double)(n - p) * di * dj[q];
+    T[wave + 16 * q][lane] = g;
+    if (c <= r0 + lane && r0 + lane < dz) G[(int64_t)c * dz + r0 + lane] = g;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) {
+    const int rr = r0 + wave + 16 * q, c = c0 + lane;
+    if (rr < dz && c < rr) G[(int64_t)rr * dz + c] = T[lane][wave + 16 * q];
+  }
+}
+
+static int launch_assemble(const VarPlan& v, const VarWs& w, const float* X, int64_t ldx,
+                           hipStream_t stream) {
+  const int nt = (int)ceil_div(v.dz, (int64_t)kAT), tm = (int)ceil_div(v.m, (int64_t)kAT);
+  var_assemble_kernel<<<(unsigned)(nt * (nt + 1) / 2 + nt * tm), 1024, 0, stream>>>(
+      X, ldx, w.F, w.mu, (int)v.m, v.p, v.n, nt, w.G, w.Tmp);
+  VL_LAUNCH_CHECK();
+  return VL_OK;
 }
 
 // Column map, means, G = Zc^T Zc and R = Zc^T Yc (R into Tmp, where the forward substitution
@@ -359,19 +433,13 @@ static int var_normal_equations(const VarPlan& v, const VarWs& w, const float* X
       D.e = w.ex;
       rc = slice_gram(D, m, D, nc, n_eff, 1.0, w.F, nc, w.scratch, stream);
       if (rc) return rc;
-      var_assemble_kernel<<<(unsigned)ceil_div(dz * dz + dz * m, 256), 256, 0, stream>>>(
-          X, ldx, w.F, w.mu, m, v.p, v.n, w.G, w.Tmp);
-      VL_LAUNCH_CHECK();
-      return VL_OK;
+      return launch_assemble(v, w, X, ldx, stream);
     }
     if (fp64) {
       rc = gram_tn(X, ldx, w.colmap, w.mu, m, X, ldx, w.colmap, w.mu0, nc, n_eff, gmode, 1.0,
                    w.F, nc, w.scratch, stream);
       if (rc) return rc;
-      var_assemble_kernel<<<(unsigned)ceil_div(dz * dz + dz * m, 256), 256, 0, stream>>>(
-          X, ldx, w.F, w.mu, m, v.p, v.n, w.G, w.Tmp);
-      VL_LAUNCH_CHECK();
-      return VL_OK;
+      return launch_assemble(v, w, X, ldx, stream);
     }
     const int64_t* mapZ = w.colmap + m;
     const double* muZ = w.mu + m;

@@ -72,3 +72,16 @@ def test_covariance_means_inside_and_before(api, m, n):
     with pytest.raises(VarLiNGAMError) as ei:
         api.pairwise_stats(torch.from_numpy(E).cuda(), "mixed")
     assert ei.value.code == VL_ERR_NONFINITE
+
+
+@pytest.mark.parametrize("m,p", [(1, 4), (13, 5), (16, 4), (21, 3), (33, 2), (43, 3), (64, 1),
+                                 (65, 2), (128, 2)])
+@pytest.mark.parametrize("prec", ["mixed", "sliced"])
+def test_normal_equations_from_lag_products(api, m, p, prec):
+    """The normal equations assembled from lag products, in tiles of 64 columns that end inside,
+    at and past the lag blocks, against least squares on the data (1e-9 of max|M|, as above)."""
+    n = 3 * m * p + 200 + m % 7
+    X = _data(n, m, 13 * m + p)
+    M = O.fit_var(X.astype(np.float64), p)[0]
+    got = api.fit_var(torch.from_numpy(X).cuda(), p, prec)[0].cpu().numpy()
+    assert np.abs(got - M).max() <= 1e-9 * np.abs(M).max()
