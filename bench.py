@@ -35,8 +35,8 @@ TRANS_PER_EVAL = 3
 # exactly: x1).  Keyed by the SHA-256 of the kernel sources the counters were taken with
 # (kernel_source_digest); any other source reports null.
 MEASURED_TRAFFIC = {
-    # FETCH_SIZE 35619.3 KiB x 2, WRITE_SIZE 8534.9 KiB x 1 per dispatch (24 dispatches)
-    "9c3f5650953d15594460fd06170797ec504d0b1f40359f4630bfa99cb262d0e9": 81688064,
+    # FETCH_SIZE 36326.6 KiB x 2, WRITE_SIZE 8879.7 KiB x 1 per dispatch (24 dispatches)
+    "1bf5cdc3da10022c3fc71f38d1bb98532e1c2e9ef92b50f1d6873a308f42642f": 83489759,
 }
 HEADLINE_PREC = "sliced"
 STAGES = ("var_gram", "var_solve", "var_residual", "var_refine", "pairwise_cov",
@@ -332,10 +332,11 @@ def bench_prune(api, torch, X, fit, steps):
     order = K.cpu().numpy()
     byts = 0
     for pos in range(m):
-        # model: the active set grows by one column per step (exact when no column leaves)
+        # model: the active set grows by one column per step (exact when no column leaves); a step
+        # reads the lower triangle of the inverse factor once and the active rows' inactive columns
         d = pos + m * p
         a = np.minimum(np.arange(1, int(inf[order[pos]][0]) + 1, dtype=np.float64), d)
-        byts += int(8 * (1.25 * a * a + a * (d - a)).sum())
+        byts += int(8 * (0.5 * a * a + a * (d - a)).sum())
     nnz0 = int((B0o != 0).sum().item())
     return {"m": m, "n": n, "p": p, "ms": ms, "workspace_bytes": nb,
             "path_steps_total": int(inf[:, 0].sum()), "df_mean": float(inf[:, 2].mean()),

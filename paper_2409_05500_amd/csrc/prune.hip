@@ -25,12 +25,12 @@
 // step limit (8 d by default).  Ties go to the lowest design column.
 //
 // What bounds it: memory.  A step with |A| of d columns active reads Li once (|A|^2 / 2
-// doubles, private to the variable: 3.3 GB of active matrices at m = 400, p = 2, far over the
+// doubles, private to the variable: 1.9 GB of them at m = 400, p = 2, far over the
 // caches) and min(|A|, d - |A|) rows of C (shared, 11.5 MB: served by L2 and the Infinity Cache).
-// Measured at m = 400, p = 2, n = 10^4, complete paths: 174 ms a call, 1.4 TB read; 601 ms with the
+// Measured at m = 400, p = 2, n = 10^4, complete paths: 174 ms a call, 1.1 TB of both; 601 ms with the
 // inverse of the active Gram itself kept and updated (1.25 |A|^2 doubles a step, written too).
-// Clocks of the longest path (1199 columns): 71 ms in the products with C, 89 ms in those with
-// Li, 23 ms in the rest; together the workgroups move ~9 TB/s through the caches.
+// Clocks of the longest path (1199 columns): 74 ms in the products with C, 76 ms in those with
+// Li, 9 ms in the rest; together the workgroups move ~9 TB/s through the caches.
 #include "prune.hpp"
 #include "gram.hpp"
 #include "order_dev.hpp"
