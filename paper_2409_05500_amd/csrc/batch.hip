@@ -631,7 +631,7 @@ size_t carve_inst(const vl_instance& in, const InstLayout& L, char* base, BInst*
   t.coef = c.take<float2>(L.m_pad * L.m_pad);
   t.partU = c.take<float>((size_t)L.nchunk * m * m);
   t.partB = c.take<float>((size_t)L.nchunk * m * m);
-  t.clist = c.take<int32_t>(L.tiles);
+  t.clist = c.take<int32_t>(2 * L.tiles + 1);   // (tiles flags; workspaces keep their size)
   t.P = c.take<double>(m * m);
   t.Linv = c.take<double>(m * m);
   t.bchol = c.take<double>(chol_ws_doubles_dev(m));
