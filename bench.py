@@ -35,8 +35,8 @@ TRANS_PER_EVAL = 3
 # exactly: x1).  Keyed by the SHA-256 of the kernel sources the counters were taken with
 # (kernel_source_digest); any other source reports null.
 MEASURED_TRAFFIC = {
-    # FETCH_SIZE 36326.6 KiB x 2, WRITE_SIZE 8879.7 KiB x 1 per dispatch (24 dispatches)
-    "1bf5cdc3da10022c3fc71f38d1bb98532e1c2e9ef92b50f1d6873a308f42642f": 83489759,
+    # FETCH_SIZE 36368.4 KiB x 2, WRITE_SIZE 8873.9 KiB x 1 per dispatch (24 dispatches)
+    "425989bbf3880fd3b9d6af856842e4cadcf01e6409fb3f0c3fa3e785d34f7dc7": 83569308,
 }
 HEADLINE_PREC = "sliced"
 STAGES = ("var_gram", "var_solve", "var_residual", "var_refine", "pairwise_cov",

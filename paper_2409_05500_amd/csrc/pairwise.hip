@@ -170,7 +170,7 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out) {
   char* region = base ? static_cast<char*>(base) + c.used : nullptr;
   Carver a(region);                              // stage 1
   w.scratch = a.take<double>(scratch_doubles(p));
-  w.sums = p.fused ? a.take<double>((size_t)colmean_splits(p.n_eff) * p.m) : w.scratch;
+  w.sums = w.scratch + (p.fused ? gram_splits_f64(p.m, p.m, p.n_eff) * p.m * p.m : 0);
   if (p.sliced) {
     w.slices = a.take<int8_t>(slice_bytes(p.m, p.n_eff));
     w.ex = a.take<int32_t>(p.m);
@@ -187,7 +187,7 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out) {
     w.partU = b.take<float>(np);
     w.partB = b.take<float>(np);
   }
-  w.clist = b.take<int32_t>(2 * p.tiles + 1);   // (tiles flags; the size is the limits')
+  w.clist = b.take<int32_t>(2 * p.tiles + 1);   // (tiles flags; workspaces keep their size)
   if (out) *out = w;
   return c.used + std::max(a.used, b.used);
 }
@@ -200,6 +200,8 @@ size_t scratch_doubles(const PairwisePlan& p) {
     a *= 3;     // column ranges for the slice exponents
     b = std::max(b, (size_t)slice_gram_splits(p.m, p.m, p.n_eff, true) * p.m * p.m);
   }
+  // fused: the sums lie past the Gram's own partials, within the scratch where it is larger
+  if (p.fused) b = std::max(b, (size_t)gram_splits_f64(p.m, p.m, p.n_eff) * p.m * p.m + a);
   return a > b ? a : b;
 }
 
