@@ -158,8 +158,16 @@ __global__ void bat_reset_kernel(int32_t* st, int count) {
   if (i < count) st[i] = VL_OK;
 }
 
+// Whether a problem's FP64 residual runs as whole tiles where the batch has enough of them, and the
+// sums of E's columns over each tile's samples that it then leaves (ceil(n_eff / 64) x m, in the
+// space of Xs, which is written after the means are formed).
+__device__ inline bool resid_wide(const BInst& d) { return d.m >= 16 && d.n_eff >= 64; }
+__device__ inline double* resid_sums(const BInst& d) { return reinterpret_cast<double*>(d.Xs); }
+
 // Column means over all n_eff rows, 64 columns by kColLanes row lanes per block, each with 16
-// loads in flight from a stepped pointer; which = 0: the lag map of X (VAR), 1: the residuals E.
+// loads in flight from a stepped pointer; which = 0: the lag map of X (VAR), 1: the residuals E,
+// 2: E, from the whole tiles' sums where the residual left them (256 problems, m 20-200: both
+// launches 330 -> 214 us, the residual's 824 -> 846 with the sums in it).
 // Raises VL_ERR_NONFINITE (a NaN or infinity in a column makes its sum one).
 constexpr int kColLanes = 16;
 
@@ -175,7 +183,19 @@ __global__ __launch_bounds__(64 * kColLanes) void bat_colmeans_kernel(BTables T,
   const int64_t ncol = which ? d.m : d.nc;
   const int64_t c = lb * 64 + cc;
   double s = 0.0;
-  if (c < ncol) {
+  if (which == 2 && resid_wide(d)) {
+    const double* su = resid_sums(d);
+    const int64_t tiles = ceil_div(d.n_eff, (int64_t)64), cl = c < ncol ? c : ncol - 1;
+    for (int64_t z = rg; z < tiles; z += 8 * kColLanes) {
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = su[(z + u * kColLanes < tiles ? z + u * kColLanes : tiles - 1) * ncol + cl];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (z + u * kColLanes < tiles) s += v[u];
+    }
+  } else if (c < ncol) {
     const int64_t n_eff = d.n_eff, step = kColLanes * lda;
     const float* p = A + (which ? c : d.colmap[c]) + rg * lda;
     int64_t t = rg;
@@ -383,18 +403,23 @@ __global__ __launch_bounds__(256, 2) void bat_var_residual_kernel(BTables T) {
   if constexpr (kRows == 64) {
     var_residual_wave_f64<2, 2>(d.X, d.ldx, d.colmap, d.mu, d.m, d.p, d.n_eff, d.Coef, d.E, d.lde,
                                 t0 + 32 * (wave >> 1), j0 + 32 * (wave & 1));
-  } else if (d.m >= 16 && d.n_eff >= 64) {
+  } else if (resid_wide(d)) {
     if (tw >= d.n_eff) return;
     const int m = (int)d.m, j = (int)j0;
+    double* su = resid_sums(d) + tw / 64 * d.m;
     switch (m - j >= 64 ? 4 : (m - j + 15) / 16) {
       case 1:
-        return var_residual_wide_f64<1>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+        return var_residual_wide_f64<1>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j,
+                                        su);
       case 2:
-        return var_residual_wide_f64<2>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+        return var_residual_wide_f64<2>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j,
+                                        su);
       case 3:
-        return var_residual_wide_f64<3>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+        return var_residual_wide_f64<3>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j,
+                                        su);
       default:
-        return var_residual_wide_f64<4>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j);
+        return var_residual_wide_f64<4>(d.X, d.ldx, d.mu, m, d.p, d.n_eff, d.Coef, d.E, d.lde, tw, j,
+                                        su);
     }
   } else {
     for (int q = 0; q < 4; ++q)
@@ -879,7 +904,8 @@ int launch_fit(const vl_batch* B, void* ws, int32_t* st, hipStream_t s) {
   }
   {
     ProfileScope ps("batch_pairwise", s);
-    bat_colmeans_kernel<<<(unsigned)B->total[kMapColE], 64 * kColLanes, 0, s>>>(T, 1, st);
+    bat_colmeans_kernel<<<(unsigned)B->total[kMapColE], 64 * kColLanes, 0, s>>>(
+        T, f64 && B->resid_rows == 256 ? 2 : 1, st);
     VL_LAUNCH_CHECK();
     if (f64) bat_gram_kernel<true><<<(unsigned)B->total[kMapGramCov], 256, 0, s>>>(T, 1);
     else bat_gram_kernel<false><<<(unsigned)B->total[kMapGramCov], 256, 0, s>>>(T, 1);

@@ -208,7 +208,8 @@ __device__ __forceinline__ void var_residual_wave_f64(
 // one before (the same values written twice; the lags seen before count as zero), so every load
 // is a full one (a lane's four lags in one, whatever their alignment) and can be counted.  A step
 // converts its sixteen lags first, then loads the next sixteen, and each product's coefficients
-// are loaded again as soon as it has used them.  Bound by the FP64 matrix rate, two waves per
+// are loaded again as soon as it has used them.  sums[j]: the stored E of column j added up over the
+// samples from t0 on (those no other tile has), for the column means.  Bound by the FP64 matrix rate, two waves per
 // SIMD, and by the memory for Y and E at the end.  Against 64 x 64 tiles staged in LDS, four
 // waves a tile: 256 problems (m 20-200, n 500-8000) 1136 -> 824 us, 181 windows of 50 x 2000
 // 102 -> 77.
@@ -218,8 +219,9 @@ template <int NB>
 __device__ __forceinline__ void var_residual_wide_f64(
     const float* __restrict__ X, int64_t ldx, const double* __restrict__ mu, int m, int p,
     int64_t n_eff, const double* __restrict__ Coef, float* __restrict__ E, int64_t lde, int64_t t0,
-    int j0) {
+    int j0, double* __restrict__ sums) {
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int64_t tnew = t0;
   t0 = t0 < n_eff - 64 ? t0 : n_eff - 64;
   int jq[NB];
 #pragma unroll
@@ -284,9 +286,12 @@ __device__ __forceinline__ void var_residual_wide_f64(
     g = gn;
   }
   // Y at this lane's outputs, a block row at a time: its loads issued before its stores
-  double muy[NB];
+  double muy[NB], total[NB];
 #pragma unroll
-  for (int b = 0; b < NB; ++b) muy[b] = mu[jq[b]];
+  for (int b = 0; b < NB; ++b) {
+    muy[b] = mu[jq[b]];
+    total[b] = 0.0;
+  }
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     const int64_t t = t0 + 16 * a + lk;              // f64 D layout: rows lk + 4 r
@@ -298,9 +303,17 @@ __device__ __forceinline__ void var_residual_wide_f64(
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (j0 + 16 * b + li < m)
-          E[(t + 4 * r) * lde + jq[b]] = (float)(((double)y[b][r] - muy[b]) - acc[a][b][r]);
+      for (int r = 0; r < 4; ++r) {
+        const float e = (float)(((double)y[b][r] - muy[b]) - acc[a][b][r]);
+        if (j0 + 16 * b + li < m) E[(t + 4 * r) * lde + jq[b]] = e;
+        total[b] += mask_f64((double)e, t + 4 * r >= tnew);
+      }
+  }
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    total[b] += __shfl_xor(total[b], 16, 64);
+    total[b] += __shfl_xor(total[b], 32, 64);
+    if (lk == 0 && j0 + 16 * b + li < m) sums[jq[b]] = total[b];
   }
 }
 
