@@ -751,8 +751,11 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
       best_bic = bic;
       best_knot = steps;
       best_df = df;
+      // every column's entry: an excluded column is on neither list and may have been active at the
+      // best knot before
+      for (int j = t; j < d; j += kPT) best[j] = 0.0;
+      __syncthreads();
       for (int r = t; r < nA; r += kPT) best[des[r]] = bc[r];
-      for (int x = ib + t; x < d; x += kPT) best[des[x]] = 0.0;
     }
     __syncthreads();
     if (event == 0 || Cc <= kStopRel * C0) break;
