@@ -761,20 +761,24 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
     if (event == 0 || Cc <= kStopRel * C0) break;
   }
 
-  // outputs: row i of B0 (predecessors only) and of every B_tau
-  double* rowB0 = a.B0o + (int64_t)i * m;
-  for (int64_t v = t; v < m; v += kPT) rowB0[v] = 0.0;
-  __syncthreads();
+  // outputs: row i of B0 (predecessors only) and of every B_tau.  They may be the inputs' own rows
+  // (B0o = B0, Blo = Bl): every weight is read before the first output is written.
   for (int j = t; j < d; j += kPT) {
     int cj;
     double s;
     design(j, cj, s);
-    const double v = best[j] * s;
+    best[j] *= s;
+  }
+  __syncthreads();
+  double* rowB0 = a.B0o + (int64_t)i * m;
+  for (int64_t v = t; v < m; v += kPT) rowB0[v] = 0.0;
+  __syncthreads();
+  for (int j = t; j < d; j += kPT) {
     if (j < pos) {
-      rowB0[min(max(a.order[j], 0), (int)m - 1)] = v;
+      rowB0[min(max(a.order[j], 0), (int)m - 1)] = best[j];
     } else {
       const int64_t jj = j - pos;
-      a.Blo[jj / m * m * m + (int64_t)i * m + jj % m] = v;
+      a.Blo[jj / m * m * m + (int64_t)i * m + jj % m] = best[j];
     }
   }
   if (a.info && t == 0) {
