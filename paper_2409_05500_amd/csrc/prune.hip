@@ -43,7 +43,9 @@ namespace {
 
 constexpr int kPT = 512;            // threads per variable
 constexpr int kPW = kPT / kWave;
-constexpr int kPanel = 1024;        // inactive columns per pass when the state is in memory
+constexpr int kPanel = 1024;        // columns per pass when the state is in memory
+constexpr int kMemNC = 20;          // pieces of an active set whose rows fit in registers there
+constexpr int kMemMaxD = 4096;      // designs (m (p + 1) <= 4096)
 constexpr double kGammaRel = 1e-12;
 constexpr double kCollinearRel = 1e-12;
 constexpr double kStopRel = 1e-12;
@@ -227,57 +229,132 @@ __device__ __forceinline__ void li_blocks(const double* __restrict__ Li, int n, 
   }
 }
 
-// out = G_A^{-1} x = Li^T (Li x) over n active slots; returns |Li x|^2 (every thread alike).
-// NC > 0: rows in registers, one read of Li (n <= 64 NC; x in LDS, zeros up to
-// the next multiple of 64).  NC = 0: any n, Li read twice (the
-// row sums through y, a scratch vector of n).  Ends with a barrier; x, out may not alias.
+// The rest of apply_inverse's register form: g from the wave's rows, |Li x|^2, the waves' sums.
 template <int NC>
-__device__ __forceinline__ double apply_inverse(const double* __restrict__ Li, int n, const double* x,
-                                       double* out, double* y, double* part, double* red) {
+__device__ __forceinline__ double apply_rows(const double* __restrict__ Li, int n, const double* x,
+                                             double* out, double* part, double* red) {
   const int t = threadIdx.x, lane = fresh_lane(), w = uni(t / kWave);
   double ysq = 0.0, z = 0.0;
-  if constexpr (NC > 0) {
-    double xr[NC], g[NC];
+  double xr[NC], g[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      xr[c] = 64 * c < n ? x[64 * c + lane] : 0.0;
-      g[c] = 0.0;
-    }
-    static_assert(NC % 2 == 0, "two piece counts an instance");
-    li_blocks<2, NC>(Li, n, w, xr, g, ysq);
+  for (int c = 0; c < NC; ++c) {
+    xr[c] = 64 * c < n ? x[64 * c + lane] : 0.0;
+    g[c] = 0.0;
+  }
+  static_assert(NC % 2 == 0, "two piece counts an instance");
+  li_blocks<2, NC>(Li, n, w, xr, g, ysq);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int e = 64 * c + lane;
-      if (e < n) part[w * n + e] = g[c];
-    }
-    ysq = lane == 0 ? ysq : 0.0;
-    wg_sum2(ysq, z, red);
-    for (int r = t; r < n; r += kPT) {
-      double s = part[r];
+  for (int c = 0; c < NC; ++c) {
+    const int e = 64 * c + lane;
+    if (e < n) part[w * n + e] = g[c];
+  }
+  ysq = lane == 0 ? ysq : 0.0;
+  wg_sum2(ysq, z, red);
+  for (int r = t; r < n; r += kPT) {
+    double s = part[r];
 #pragma unroll
-      for (int q = 1; q < kPW; ++q) s += part[q * n + r];
-      out[r] = s;
+    for (int q = 1; q < kPW; ++q) s += part[q * n + r];
+    out[r] = s;
+  }
+  __syncthreads();
+  return ysq;
+}
+
+// The same for any n <= kMemMaxD, Li read twice: y = Li x by rows, then Li^T y by panels of kPanel
+// columns, a panel's sums in registers.  Both with two rows of 16 pieces in flight a wave; pieces
+// past a row's end read its last one with weight 0.  part: kPW kPanel doubles (x in the first pass),
+// y: kMemMaxD doubles, both LDS.
+__device__ __forceinline__ double apply_passes(const double* __restrict__ Li, int n,
+                                               const double* x, double* out, double* part,
+                                               double* y, double* red) {
+  constexpr int U = kPanel / kWave;
+  const int t = threadIdx.x, lane = fresh_lane(), w = uni(t / kWave);
+  double ysq = 0.0, z = 0.0;
+  for (int e = t; e < 64 * ((n + 63) / 64); e += kPT) part[e] = x[e];
+  __syncthreads();
+#pragma unroll 1
+  for (int r = w; r < n; r += 2 * kPW) {
+    const bool two = r + kPW < n;
+    const int r1 = two ? r + kPW : r, k0 = r >> 6, k1 = r1 >> 6;
+    const double *p0 = Li + li_row(r) + lane, *p1 = Li + li_row(r1) + lane;
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 1
+    for (int c0 = 0; c0 <= k1; c0 += U) {
+      double a0[U], a1[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) a0[u] = p0[64 * min(c0 + u, k0)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) a1[u] = p1[64 * min(c0 + u, k1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const double xv = part[64 * min(c0 + u, k1) + lane];
+        s0 = fma(a0[u], c0 + u <= k0 ? xv : 0.0, s0);
+        s1 = fma(a1[u], c0 + u <= k1 ? xv : 0.0, s1);
+      }
     }
+    s0 = wave_allsum_d(s0);
+    s1 = two ? wave_allsum_d(s1) : 0.0;
+    ysq = fma(s0, s0, ysq);
+    ysq = fma(s1, s1, ysq);
+    if (lane == 0) {
+      y[r] = s0;
+      if (two) y[r1] = s1;
+    }
+  }
+  ysq = lane == 0 ? ysq : 0.0;
+  wg_sum2(ysq, z, red);                              // (its barriers: y is whole, x is done with)
+#pragma unroll 1
+  for (int e0 = 0; e0 < n; e0 += kPanel) {
+    const int c0 = e0 >> 6;
+    double g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) g[u] = 0.0;
+#pragma unroll 1
+    for (int r = e0 + w; r < n; r += 2 * kPW) {
+      const bool two = r + kPW < n;
+      const int r1 = two ? r + kPW : r, k0 = r >> 6, k1 = r1 >> 6;
+      const double *p0 = Li + li_row(r) + lane, *p1 = Li + li_row(r1) + lane;
+      double a0[U], a1[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) a0[u] = p0[64 * min(c0 + u, k0)];
+#pragma unroll
+      for (int u = 0; u < U; ++u) a1[u] = p1[64 * min(c0 + u, k1)];
+      const double y0 = y[r], y1 = two ? y[r1] : 0.0;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        g[u] = fma(a0[u], c0 + u <= k0 ? y0 : 0.0, g[u]);
+        g[u] = fma(a1[u], c0 + u <= k1 ? y1 : 0.0, g[u]);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) part[w * kPanel + 64 * u + lane] = g[u];
     __syncthreads();
-  } else {
-    for (int r = w; r < n; r += kPW) {
-      const double* p = Li + li_row(r);
-      double s = 0.0;
-      for (int e = lane; e <= r; e += kWave) s = fma(p[e], x[e], s);
-      s = wave_allsum_d(s);
-      ysq = fma(s, s, ysq);
-      if (lane == 0) y[r] = s;
-    }
-    ysq = lane == 0 ? ysq : 0.0;
-    wg_sum2(ysq, z, red);
-    for (int e0 = 64 * w; e0 < n; e0 += kPT) {
-      double s = 0.0;
-      for (int r = e0; r < n; ++r) s = fma(Li[li_row(r) + e0 + lane], y[r], s);
-      if (e0 + lane < n) out[e0 + lane] = s;
+    for (int e = t; e < min(kPanel, n - e0); e += kPT) {
+      double s = part[e];
+#pragma unroll
+      for (int q = 1; q < kPW; ++q) s += part[q * kPanel + e];
+      out[e0 + e] = s;
     }
     __syncthreads();
   }
   return ysq;
+}
+
+// out = G_A^{-1} x = Li^T (Li x) over n active slots; returns |Li x|^2 (every thread alike).  x
+// holds zeros up to the next multiple of 64; x and out may not alias.  NC > 0: rows in registers,
+// one read of Li (n <= 64 NC, x in LDS).  NC = 0: x in memory, the same while kMemNC pieces hold the
+// active set, else two reads.  With this and the products by rows of C the complete paths at
+// m = 400, p = 3 take 635 ms and at m = 660, p = 1 334 (16 pieces: 783 and 388; two reads with one
+// load at a time: 2302 and 1416).  Ends with a barrier.
+template <int NC>
+__device__ __forceinline__ double apply_inverse(const double* __restrict__ Li, int n, const double* x,
+                                                double* out, double* part, double* red) {
+  if constexpr (NC > 0) {
+    return apply_rows<NC>(Li, n, x, out, part, red);
+  } else {
+    if (n <= 64 * kMemNC) return apply_rows<kMemNC>(Li, n, x, out, part, red);
+    return apply_passes(Li, n, x, out, part, part + 64 * kMemNC * kPW, red);
+  }
 }
 
 // Removes active slot r0 of n from Li.  G_A^{-1} = sum of the rows' outer products; rotating row
@@ -378,24 +455,25 @@ __device__ __forceinline__ void inactive_dots(const double* __restrict__ C, int6
   }
 }
 
-// y[e] = sum_j C[ic_e][col_j] x_j over all d design columns (x in LDS: zero outside the active ones and
-// up to the next multiple of 64) for
-// np inactive columns ic; col_j = j, plus gap from pos on.  The other form of the same products, for more active columns than
-// inactive ones.  A step then reads min(|A|, d - |A|) rows of C whole; by active rows alone the
-// late steps read whole cache lines for a few scattered columns each (the longest path at
-// m = 400, p = 2: 152 ms in these products by active rows alone, 71 ms with both forms).
-template <int K>  // d <= 64 K
+// y[e] = sum_j C[ic_e][col_j] x_j over all d design columns (x: zero outside the active ones and up
+// to the next multiple of 64) for np inactive columns ic; col_j = j, plus gap from pos on.  The
+// other form of the same products, for more active columns than inactive ones.  A step then reads
+// min(|A|, d - |A|) rows of C whole; by active rows alone the late steps read whole cache lines for
+// a few scattered columns each (the longest path at m = 400, p = 2: 152 ms in these products by
+// active rows alone, 71 ms with both forms).
+// The columns 64 c0 .. 64 (c0 + K) - 1 of the design; kAdd: added to y (each entry by one lane).
+template <int K, bool kAdd>
 __device__ __forceinline__ void inactive_rows_k(const double* __restrict__ C, int64_t ldc, int d,
                                                 int pos, int gap, const double* x, int np,
-                                                const int* ic, double* y) {
+                                                const int* ic, double* y, int c0) {
   const int lane = fresh_lane(), w = uni(threadIdx.x / kWave);
   double xr[K];
   uint32_t k[K];
 #pragma unroll
   for (int c = 0; c < K; ++c) {
-    const int j = min(64 * c + lane, d - 1);
+    const int j = min(64 * (c0 + c) + lane, d - 1);
     k[c] = (uint32_t)(j + (j >= pos ? gap : 0));
-    xr[c] = 64 * c < d ? x[64 * c + lane] : 0.0;
+    xr[c] = 64 * (c0 + c) < d ? x[64 * (c0 + c) + lane] : 0.0;
   }
 #pragma unroll 1
   for (int e = w; e < np; e += 2 * kPW) {
@@ -416,10 +494,20 @@ __device__ __forceinline__ void inactive_rows_k(const double* __restrict__ C, in
     s0 = wave_allsum_d(s0);
     s1 = wave_allsum_d(s1);
     if (lane == 0) {
-      y[e] = s0;
-      if (two) y[e + kPW] = s1;
+      y[e] = kAdd ? y[e] + s0 : s0;
+      if (two) y[e + kPW] = kAdd ? y[e + kPW] + s1 : s1;
     }
   }
+}
+
+// Any d: kMemNC pieces of the design at a time.
+__device__ __forceinline__ void inactive_rows_any(const double* __restrict__ C, int64_t ldc, int d,
+                                                  int pos, int gap, const double* x, int np,
+                                                  const int* ic, double* y) {
+  inactive_rows_k<kMemNC, false>(C, ldc, d, pos, gap, x, np, ic, y, 0);
+#pragma unroll 1
+  for (int c0 = kMemNC; 64 * c0 < d; c0 += kMemNC)
+    inactive_rows_k<kMemNC, true>(C, ldc, d, pos, gap, x, np, ic, y, c0);
 }
 
 template <int K, int NC>
@@ -427,7 +515,7 @@ __device__ __forceinline__ void inactive_rows(const double* __restrict__ C, int6
                                               int pos, int gap, const double* x, int np,
                                               const int* ic, double* y) {
   if (d <= 64 * K)
-    inactive_rows_k<K>(C, ldc, d, pos, gap, x, np, ic, y);
+    inactive_rows_k<K, false>(C, ldc, d, pos, gap, x, np, ic, y, 0);
   else if constexpr (K < NC)
     inactive_rows<K + 2, NC>(C, ldc, d, pos, gap, x, np, ic, y);
 }
@@ -455,7 +543,7 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
   double* best = Li + prune_li_doubles(prune_active_cap(d, a.cap));
   // state vectors: scale; beta | correlation; q | Z~^T u; sign; two scratch vectors; column of C;
   // design column
-  const int D = NC > 0 ? (int)round_up(a.dmax, 64) : d;
+  const int D = (int)round_up(NC > 0 ? a.dmax : d, 64);
   double* vec;
   if constexpr (NC > 0) vec = dyn;
   else vec = best + d;
@@ -465,7 +553,7 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
   double* sv = qa + D;
   double* bv = sv + D;
   double* gn = bv + D;
-  double *part, *more;                 // wave partials; scratch vectors of li_remove and NC = 0
+  double *part, *more;                 // wave partials; scratch vectors of li_remove
   int* col;
   if constexpr (NC > 0) {
     part = gn + D;
@@ -474,7 +562,7 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
   } else {
     part = dyn;
     more = gn + D;
-    col = reinterpret_cast<int*>(more + 5 * D);
+    col = reinterpret_cast<int*>(more + 4 * D);
   }
   int* des = col + D;
   const int panel = NC > 0 ? D : kPanel;
@@ -540,25 +628,36 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
   int best_knot = 0, best_df = 0, steps = 0;
   const int64_t cap = a.cap > 0 ? a.cap : 8 * (int64_t)uni((int)nkeep);
 
-  // inactive slot e leaves the list: the ones before it move up by one.  Every thread must be
-  // done with slot e before the call; ends with a barrier.
+  // inactive slot e leaves the list: the ones before it move up by one, kG groups of kPT at a time
+  // (state in memory: their loads in flight together).  Every thread must be done with slot e before
+  // the call; ends with a barrier.
+  constexpr int kG = NC > 0 ? 1 : kMemMaxD / kPT;
   auto drop_inactive = [&](int e) {
-    for (int hi = e - 1; hi >= ib; hi -= kPT) {
-      const int x = hi - t;
-      double v0 = 0.0, v1 = 0.0;
-      int w0 = 0, w1 = 0;
-      if (x >= ib) {
-        v0 = sc[x];
-        v1 = bc[x];
-        w0 = col[x];
-        w1 = des[x];
+    for (int hi = e - 1; hi >= ib; hi -= kG * kPT) {
+      double v0[kG], v1[kG];
+      int w0[kG], w1[kG];
+#pragma unroll
+      for (int q = 0; q < kG; ++q) {
+        const int x = hi - t - q * kPT;
+        v0[q] = v1[q] = 0.0;
+        w0[q] = w1[q] = 0;
+        if (x >= ib) {
+          v0[q] = sc[x];
+          v1[q] = bc[x];
+          w0[q] = col[x];
+          w1[q] = des[x];
+        }
       }
       __syncthreads();
-      if (x >= ib) {
-        sc[x + 1] = v0;
-        bc[x + 1] = v1;
-        col[x + 1] = w0;
-        des[x + 1] = w1;
+#pragma unroll
+      for (int q = 0; q < kG; ++q) {
+        const int x = hi - t - q * kPT;
+        if (x >= ib) {
+          sc[x + 1] = v0[q];
+          bc[x + 1] = v1[q];
+          col[x + 1] = w0[q];
+          des[x + 1] = w1[q];
+        }
       }
     }
     ++ib;
@@ -599,20 +698,26 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
     for (int p0 = 0; p0 < nI; p0 += panel) {
       const int np = min(panel, nI - p0);
       if (p0 > 0) __syncthreads();
-      bool rows = false;
-      if constexpr (NC > 0) {
-        rows = nA > nI;
-        if (rows) {
+      const bool rows = nA > nI;
+      if (rows) {
+        if (p0 == 0) {
           for (int j = t; j < 64 * ((d + 63) / 64); j += kPT) gn[j] = 0.0;
           __syncthreads();
           for (int r = t; r < nA; r += kPT) gn[des[r]] = bv[r];
           __syncthreads();
-          inactive_rows<2, NC>(a.C, ldc, d, (int)pos, (int)(m - pos), gn, np, col + ib, part);
         }
+        if constexpr (NC > 0)
+          inactive_rows<2, NC>(a.C, ldc, d, (int)pos, (int)(m - pos), gn, np, col + ib, part);
+        else
+          inactive_rows_any(a.C, ldc, d, (int)pos, (int)(m - pos), gn, np, col + ib + p0, part);
+      } else {
+        // up to four slots a wave: loads for four (m = 2040, p = 1, 25 steps: with drop_inactive's
+        // loads in flight 19.0 -> 14.5 ms)
+        if (NC == 0 && nA <= 4 * kPW)
+          inactive_dots<4>(a.C, ldc, nA, col, bv, np, col + ib + p0, part);
+        else
+          inactive_dots<16>(a.C, ldc, nA, col, bv, np, col + ib + p0, part);
       }
-      if (!rows)
-        inactive_dots<16>(a.C, ldc, nA, col, bv, np, col + ib + p0,
-                                                     part);
       __syncthreads();
       for (int e = t; e < np; e += kPT) {
         double s = part[e];
@@ -704,21 +809,19 @@ __global__ __launch_bounds__(kPT) void prune_lars_kernel(PruneArgs a) {
         col[ib] = c0;
         des[ib] = j0;
       }
-      for (int r = t; r < (NC > 0 ? 64 * ((nA + 63) / 64) : nA); r += kPT)
-        bv[r] = r < nA ? sv[r] : 0.0;
+      for (int r = t; r < 64 * ((nA + 63) / 64); r += kPT) bv[r] = r < nA ? sv[r] : 0.0;
       __syncthreads();
-      apply_inverse<NC>(Li, nA, bv, qa, more + 4 * (NC > 0 ? 0 : D), part, red);
+      apply_inverse<NC>(Li, nA, bv, qa, part, red);
     } else if (event > 0) {
       // border the factor with the joining column (or exclude it when collinear)
       const int e = uni(hat.slot), ck = col[e], jk = des[e];
       const double sk = sc[e], sgn = bc[e] >= 0.0 ? 1.0 : -1.0;
       const double* Ck = a.C + (int64_t)ck * ldc;     // C is symmetric
       const double gkk = sk * sk * Ck[ck];
-      for (int r = t; r < (NC > 0 ? 64 * ((nA + 63) / 64) : nA); r += kPT)
+      for (int r = t; r < 64 * ((nA + 63) / 64); r += kPT)
         bv[r] = r < nA ? sc[r] * sk * Ck[col[r]] : 0.0;
       __syncthreads();
-      const double delta =
-          gkk - apply_inverse<NC>(Li, nA, bv, gn, more + 4 * (NC > 0 ? 0 : D), part, red);
+      const double delta = gkk - apply_inverse<NC>(Li, nA, bv, gn, part, red);
       if (delta <= kCollinearRel * gkk) {
         drop_inactive(e);
       } else {
@@ -798,7 +901,9 @@ size_t prune_lds_bytes(int64_t d) {
 
 template <int NC>
 int launch_prune(const PruneArgs& a, hipStream_t stream) {
-  const size_t lds = NC > 0 ? prune_lds_bytes(a.dmax) : (size_t)kPW * kPanel * sizeof(double);
+  const size_t lds = NC > 0 ? prune_lds_bytes(a.dmax)
+                            : (size_t)(kPW * 64 * kMemNC + kMemMaxD) * sizeof(double);
+  static_assert(kPanel <= 64 * kMemNC, "the panels' partials fit in the rows'");
   if (hipFuncSetAttribute(reinterpret_cast<const void*>(&prune_lars_kernel<NC>),
                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
     return VL_ERR_HIP;

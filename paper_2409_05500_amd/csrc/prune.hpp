@@ -24,9 +24,10 @@ __host__ __device__ inline int64_t prune_li_doubles(int64_t n) {
 }
 
 // Doubles of the region of a variable with d design columns: the inverse factor, the best knot's
-// coefficients, and (designs too long for LDS) eleven FP64 vectors and two int32 vectors of d.
+// coefficients, and (designs too long for LDS) ten FP64 vectors and two int32 vectors of d rounded up
+// to 64.
 __host__ __device__ inline int64_t prune_region_doubles(int64_t d, int64_t cap) {
-  return round_up(prune_li_doubles(prune_active_cap(d, cap)) + 13 * d, 32);
+  return round_up(prune_li_doubles(prune_active_cap(d, cap)) + d + 11 * round_up(d, 64), 32);
 }
 
 size_t prune_ws_bytes(int64_t n, int64_t m, int p, int64_t cap, void* base, PruneWs* out);
