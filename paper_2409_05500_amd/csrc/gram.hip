@@ -354,14 +354,23 @@ __global__ void sum_splits_kernel(const double* __restrict__ P, int splits, int6
 }
 
 // Symmetric form: entries (i, j) with i >= j of the lower tiles are summed and written to both
-// (i, j) and (j, i), so C is exactly symmetric.
+// (i, j) and (j, i), so C is exactly symmetric.  kOrder: row and column a < norder of C are those of
+// column order[a] (clamped: a caller's check reports bad entries).
+template <bool kOrder>
 __global__ void sum_splits_sym_kernel(const double* __restrict__ P, int splits, int64_t M,
-                                      double scale, double* __restrict__ C, int64_t ldc) {
+                                      double scale, double* __restrict__ C, int64_t ldc,
+                                      const int32_t* __restrict__ order, int norder) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= M * M) return;
   const int64_t i = e / M, j = e % M;
   if (j > i) return;
-  const double s = sum_splits_at(P, splits, M * M, e);
+  int64_t from = e;
+  if constexpr (kOrder) {
+    const int64_t a = i < norder ? min(max(order[i], 0), norder - 1) : i;
+    const int64_t b = j < norder ? min(max(order[j], 0), norder - 1) : j;
+    from = a > b ? a * M + b : b * M + a;
+  }
+  const double s = sum_splits_at(P, splits, M * M, from);
   C[i * ldc + j] = s * scale;
   C[j * ldc + i] = s * scale;
 }
@@ -370,8 +379,8 @@ int sum_splits(const double* P, int splits, int64_t M, int64_t N, double scale, 
                int64_t ldc, bool sym, hipStream_t stream) {
   const int64_t tot = M * N;
   if (sym)
-    sum_splits_sym_kernel<<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(P, splits, M, scale,
-                                                                            C, ldc);
+    sum_splits_sym_kernel<false><<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(
+        P, splits, M, scale, C, ldc, nullptr, 0);
   else
     sum_splits_kernel<<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(P, splits, M, N, scale,
                                                                        C, ldc);
@@ -401,7 +410,7 @@ int cov_from_sums(const float* A, int64_t lda, int64_t M, int64_t K, const doubl
 int gram_tn(const float* A, int64_t lda, const int64_t* mapA, const double* muA, int64_t M,
             const float* B, int64_t ldb, const int64_t* mapB, const double* muB, int64_t N,
             int64_t K, GramMode mode, double scale, double* C, int64_t ldc, double* scratch,
-            hipStream_t stream, bool sym) {
+            hipStream_t stream, bool sym, const int32_t* order, int norder) {
   int splits = mode == GramMode::kFp64 ? gram_splits_f64(M, N, K) : gram_splits(M, N, K);
   const int64_t kchunk = round_up(ceil_div(K, splits), kGK);
   if (mode == GramMode::kFp64) splits = (int)ceil_div(K, kchunk);   // no empty splits
@@ -423,9 +432,12 @@ int gram_tn(const float* A, int64_t lda, const int64_t* mapA, const double* muA,
                                                 kchunk, scratch, sy);
   VL_LAUNCH_CHECK();
   const int64_t tot = M * N;
-  if (sym)
-    sum_splits_sym_kernel<<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(scratch, splits, M,
-                                                                            scale, C, ldc);
+  if (sym && order)
+    sum_splits_sym_kernel<true><<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(
+        scratch, splits, M, scale, C, ldc, order, norder);
+  else if (sym)
+    sum_splits_sym_kernel<false><<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(
+        scratch, splits, M, scale, C, ldc, nullptr, 0);
   else
     sum_splits_kernel<<<(unsigned)ceil_div(tot, 256), 256, 0, stream>>>(scratch, splits, M, N,
                                                                        scale, C, ldc);
