@@ -166,6 +166,11 @@ __device__ __forceinline__ void fmac_row16(double& acc, double x, const double (
 #undef VL_FMAC
 }
 
+// Doubles between two variables' partials: an odd number of 16-byte pairs, so that the reads of a
+// pair a lane spread over all banks (at 8 groups, an even one: m = 64, p = 8, 48 resamples
+// of 400 steps 0.65 ms, 0.41 so; the register kernel 0.50).
+__host__ __device__ inline int sim_stride(int groups) { return (groups + 1) / 2 * 2 | 2; }
+
 template <int TPW>  // tasks (blocks of 16 variables) a wave
 __global__ __launch_bounds__(64 * kSimWaves) void var_simulate_row_kernel(
     const double* __restrict__ M, const double* __restrict__ c, int m, int p, int wpg,
@@ -179,11 +184,11 @@ __global__ __launch_bounds__(64 * kSimWaves) void var_simulate_row_kernel(
   const int g = wave / wpg, blk0 = (wave % wpg) * TPW;
   const int tau = g / parts + 1, k0 = (g % parts) * kSC;
   const int ch = lane >> 4, li = lane & 15;
-  // 2 x m x gs partials (gs: groups rounded up to even, the odd one out stays 0: adding it
-  // changes nothing and the sums read pairs), then p x threads of x (p > 1)
-  const int gs = (groups + 1) & ~1;
+  // 2 x m x ld partials (gs of each ld used: groups rounded up to even, the odd one out stays 0:
+  // adding it changes nothing and the sums read pairs), then p x threads of x (p > 1)
+  const int gs = (groups + 1) & ~1, ld = sim_stride(groups);
   double* partial = sim_lds;
-  float* ring = reinterpret_cast<float*>(sim_lds + 2 * gs * m);
+  float* ring = reinterpret_cast<float*>(sim_lds + 2 * ld * m);
   const int64_t b = blockIdx.x;
   float* Xb = Xout + b * sstride;
   const int32_t* ib = idx + b * T;
@@ -212,7 +217,7 @@ __global__ __launch_bounds__(64 * kSimWaves) void var_simulate_row_kernel(
   double x = vx ? (double)X0[(int64_t)(p - tau) * ldx0 + kc] : 0.0;
 
   if (gs > groups)
-    for (int i = tid; i < 2 * m; i += blockDim.x) partial[i * gs + groups] = 0.0;
+    for (int i = tid; i < 2 * m; i += blockDim.x) partial[i * ld + groups] = 0.0;
 
   // Lane u of every eight holds the draw of step base + u (a vector load: a scalar one would make
   // the LDS waits of a step wait for it too); its residual row, clamped, and whether it was valid.
@@ -246,7 +251,7 @@ __global__ __launch_bounds__(64 * kSimWaves) void var_simulate_row_kernel(
 #pragma unroll
     for (int u = 0; u < kSimAhead; ++u) {
       if (u >= nu) break;
-      double* P = partial + (u & 1) * gs * m;
+      double* P = partial + (u & 1) * ld * m;
 #pragma unroll
       for (int q = 0; q < TPW; ++q) {
         double a = 0.0;
@@ -254,11 +259,11 @@ __global__ __launch_bounds__(64 * kSimWaves) void var_simulate_row_kernel(
         a = swap_level_d<false>(a, a);               // rows 0 + 1, 2 + 3
         a = swap_level_d<true>(a, a);                // their sums
         const int i = 16 * (blk0 + q) + li;
-        if (ch == 0 && i < m) P[i * gs + g] = a;
+        if (ch == 0 && i < m) P[i * ld + g] = a;
       }
       __syncthreads();
       double acc = cx + (double)e[u];
-      const double* Pk = P + kc * gs;
+      const double* Pk = P + kc * ld;
       for (int q = 0; q < gs; q += 2) {
         const double2 two = *reinterpret_cast<const double2*>(Pk + q);
         acc += two.x;
@@ -358,7 +363,7 @@ int run_var_simulate(const double* M, const double* intercept, int64_t m, int p,
   const int64_t tpw = fit > 0 ? ceil_div(ib, fit) : 3;
   const int64_t wpg = ceil_div(ib, tpw), nt = 64 * groups * wpg;
   const size_t row_lds =
-      (size_t)(2 * round_up(groups, 2) * m) * sizeof(double) + (p > 1 ? (size_t)p * nt * 4 : 0);
+      (size_t)(2 * sim_stride((int)groups) * m) * sizeof(double) + (p > 1 ? (size_t)p * nt * 4 : 0);
   if (groups * m <= kSimThreads && tpw <= 2 && row_lds <= 64 * 1024) {
     if (tpw == 1)
       var_simulate_row_kernel<1><<<(unsigned)R, (unsigned)nt, row_lds, stream>>>(

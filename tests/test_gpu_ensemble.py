@@ -208,3 +208,12 @@ def test_failed_window_is_left_out(api):
     P0, Pl, Po, cnt = api.edge_frequency(ef.order[1:], ef.B0[1:], ef.B_lags[1:], 0.0)
     assert cnt == ef.count
     assert torch.equal(P0, ef.P0) and torch.equal(Po, ef.P_order)
+
+
+# Group counts whose partials are padded to an odd number of pairs (3, 4, 7, 8, 12 groups), with one
+# and two tasks a wave.
+@pytest.mark.parametrize("case", [(80, 2, 20), (64, 3, 9), (64, 4, 17), (48, 7, 24), (64, 8, 25),
+                                  (33, 8, 10), (42, 12, 16)],
+                         ids=lambda c: f"m{c[0]}_p{c[1]}_T{c[2]}")
+def test_var_simulate_padded_partials(api, case):
+    test_var_simulate_tile_edges(api, case)
