@@ -46,8 +46,9 @@ __global__ __launch_bounds__(256) void standardize_transpose_kernel(
 // Hx runs in the moments' launch, as its first blocks (one a variable; both read Xs only).  It
 // had a launch of its own with the pair coefficients: the exact search at m = 100, n = 5000 6.00
 // -> 5.55 ms, the precompute at m = 10, n = 20000 97 -> 91 us, 256 problems 10.97 -> 10.64 ms (a
-// launch of m workgroups leaves most of the chip idle for its whole length).
-static inline __host__ __device__ int64_t hx_blocks(int64_t m) { return (m + 7) / 8 * 8; }
+// launch of m workgroups leaves most of the chip idle for its whole length).  The block after them
+// lists the flagged tiles for the collinear kernel.
+static inline __host__ __device__ int64_t hx_blocks(int64_t m) { return m / 8 * 8 + 8; }
 
 // Blocks are remapped so that XCD x (block id mod 8) processes a contiguous range of items in
 // chunk-major order, i.e. mostly one sample chunk per XCD and its L2.
@@ -57,11 +58,12 @@ __global__ __launch_bounds__(256) void pairwise_moments_kernel(
     const float* __restrict__ Xs, int64_t n_pad, const float2* __restrict__ coef, int64_t m_pad,
     int64_t m, int nt, int64_t tiles, int chunk_len, int64_t items,
     TP* __restrict__ partU, TP* __restrict__ partB, int64_t n_eff, double* __restrict__ Hx,
-    double* __restrict__ momx) {
+    double* __restrict__ momx, int32_t* __restrict__ clist) {
   const int64_t nb = gridDim.x - hx_blocks(m);      // a multiple of 8
   const int64_t b = (int64_t)blockIdx.x - hx_blocks(m);
   if (b < 0) {
     if (blockIdx.x < m) hx_block<256>(Xs, n_pad, n_eff, Hx, momx, blockIdx.x);
+    else if (blockIdx.x == m && threadIdx.x < 64) list_collinear_tiles(clist, tiles);
     return;
   }
   const int64_t lb = (b & 7) * (nb >> 3) + (b >> 3);
@@ -75,24 +77,20 @@ __global__ __launch_bounds__(256) void pairwise_moments_kernel(
     pairwise_moments_item(Xs, n_pad, coef, m_pad, m, nt, tiles, chunk_len, item, partU, partB);
 }
 
-// The (tile, chunk) items of the flagged micro-tiles: each wave looks through its share of all
-// items, 64 flags a time; with no flagged tile it returns after a load or two.
+// The (listed tile, chunk) items of the flagged micro-tiles, dealt to the waves one after another
+// (flags alone, each wave with a fixed share of all items, gave some waves several and others none:
+// m = 400, n = 9998 with 399 near copies 877 us, 750 so); with no flagged tile every wave returns
+// after one load.
 template <class TP>
 __global__ __launch_bounds__(256) void pairwise_collinear_kernel(
     const float* __restrict__ E, int64_t lde, int64_t n_eff, const double* __restrict__ mu,
     const double* __restrict__ cov, int64_t m, int nt, int64_t tiles, int nc, int chunk_len,
     const int32_t* __restrict__ clist, TP* __restrict__ partU, TP* __restrict__ partB) {
-  const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t total = tiles * nc, waves = (int64_t)gridDim.x * 4;
-  for (int64_t w0 = (int64_t)blockIdx.x * 4 + wave; w0 < total; w0 += 64 * waves) {
-    const int64_t wl = w0 + lane * waves;
-    uint64_t hit = __ballot(wl < total && clist[(wl < total ? wl : 0) / nc] != 0);
-    for (; hit; hit &= hit - 1) {
-      const int64_t w = w0 + (int64_t)(__ffsll((unsigned long long)hit) - 1) * waves;
-      pairwise_collinear_item(E, lde, n_eff, mu, cov, m, nt, chunk_len, w / nc, w % nc, partU,
-                              partB);
-    }
+  const int64_t total = (int64_t)clist[tiles] * nc, waves = (int64_t)gridDim.x * 4;
+  for (int64_t w = (int64_t)blockIdx.x * 4 + wave; w < total; w += waves) {
+    const int64_t tile = clist[tiles + 1 + w / nc];
+    pairwise_collinear_item(E, lde, n_eff, mu, cov, m, nt, chunk_len, tile, w % nc, partU, partB);
   }
 }
 
@@ -187,7 +185,7 @@ size_t pairwise_ws_bytes(const PairwisePlan& p, void* base, PairwiseWs* out) {
     w.partU = b.take<float>(np);
     w.partB = b.take<float>(np);
   }
-  w.clist = b.take<int32_t>(2 * p.tiles + 1);   // (tiles flags; workspaces keep their size)
+  w.clist = b.take<int32_t>(2 * p.tiles + 1);
   if (out) *out = w;
   return c.used + std::max(a.used, b.used);
 }
@@ -244,7 +242,7 @@ static int launch_moments(const PairwisePlan& p, const PairwiseWs& w, const floa
     if (!rows)
       pairwise_moments_kernel<TP><<<(unsigned)(hx_blocks(m) + p.blocks), 256, 0, stream>>>(
           w.Xs, p.n_pad, w.coef, p.m_pad, m, p.nt, p.tiles, p.chunk_len, p.items, partU, partB,
-          n_eff, Hx, w.momx);
+          n_eff, Hx, w.momx, w.clist);
     VL_LAUNCH_CHECK();
   }
   if (!rows) {

@@ -31,7 +31,7 @@ struct PairwiseWs {
   double* partU64 = nullptr;  // nc x m x m (compensated sums; in place of partU, partB)
   double* partB64 = nullptr;
   double* momx = nullptr;     // 2 m: E[log cosh x_i], E[x_i exp(-x_i^2/2)]
-  int32_t* clist = nullptr;   // near-collinear tile flags
+  int32_t* clist = nullptr;   // near-collinear tiles: a flag each, their number, their list
   int8_t* slices = nullptr;   // sliced covariance: slice planes of E's columns (stage 1)
   int32_t* ex = nullptr;      // m exponents
 };

@@ -131,6 +131,31 @@ __device__ inline void tile_coords(int64_t k, int nt, int& bi, int& bj) {
 // standardised and with the residual formed in FP64 from E itself.
 constexpr double kCollinearS = 0.25;
 
+// One wave: from the flags clist[0 .. tiles) the number of flagged tiles, clist[tiles], and their
+// list in tile order after it.
+__device__ inline void list_collinear_tiles(int32_t* __restrict__ clist, int64_t tiles) {
+  const int lane = threadIdx.x & 63;
+  constexpr int kF = 16;                              // groups of 64 flags in flight
+  int count = 0;
+  for (int64_t t0 = 0; t0 < tiles; t0 += 64 * kF) {
+    int32_t f[kF];
+#pragma unroll
+    for (int q = 0; q < kF; ++q) {
+      const int64_t t = t0 + 64 * q + lane;
+      f[q] = clist[t < tiles ? t : tiles - 1];
+    }
+#pragma unroll
+    for (int q = 0; q < kF; ++q) {
+      const int64_t t = t0 + 64 * q + lane;
+      const bool on = t < tiles && f[q] != 0;
+      const uint64_t hit = __ballot(on);
+      if (on) clist[tiles + 1 + count + __builtin_popcountll(hit & ((1ull << lane) - 1ull))] = (int32_t)t;
+      count += __builtin_popcountll(hit);
+    }
+  }
+  if (lane == 0) clist[tiles] = count;
+}
+
 // ------------------------------------------------------------------------------------------
 // Stage 3: scaled pair coefficients (a, b) of the micro-tiles {I, J}, bi <= bj (the others are
 // read by nothing); zero on the diagonal / padding.  clist[tile] is 1 for a tile with a

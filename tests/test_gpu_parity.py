@@ -554,3 +554,9 @@ def test_factorisation_block_edges(api, dev, m):
     W = np.linalg.lstsq(D, X[1:].astype(np.float64), rcond=None)[0]
     np.testing.assert_allclose(fM.reshape(m, m), W[:m].T, rtol=0, atol=1e-10)
     np.testing.assert_allclose(fc, W[m], rtol=0, atol=1e-10)
+
+
+# More tiles than one group of flags of the list (1024): the last ones are listed in the second.
+@pytest.mark.parametrize("m,n", [(184, 1100), (200, 2600)])
+def test_pairwise_near_collinear_list_groups(api, dev, m, n):
+    test_pairwise_near_collinear_among_others(api, dev, m, n)
