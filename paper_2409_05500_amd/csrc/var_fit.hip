@@ -612,9 +612,11 @@ size_t lag_ws_bytes(const VarPlan& v, void* base, LagWs* out) {
   const size_t vb = var_ws_bytes(v, nullptr, nullptr);
   char* vbase = c.take<char>(vb);
   if (base) var_ws_bytes(v, vbase, &w.var);
-  const int64_t m = v.m;
-  w.A = c.take<double>(v.p * m * m);
-  w.chol = c.take<double>(v.p * chol_ws_doubles(m));
+  // the p_max matrices and their scratch lie in the VAR workspace's buffers that the selection does
+  // not use (L) or is done with (G); small variables' scratch, a 64-wide panel each, may need its own
+  const size_t nchol = v.p * chol_ws_doubles(v.m);
+  w.A = w.var.L;
+  w.chol = nchol <= (size_t)(v.dz * v.dz) ? w.var.G : c.take<double>(nchol);
   if (out) *out = w;
   return c.used;
 }

@@ -33,7 +33,8 @@ struct VarWs {
   int32_t* ec = nullptr;      // m: exponent per coefficient column
 };
 
-// Lag-order selection workspace: the VAR workspace of the p_max plan, then m x m buffers.
+// Lag-order selection workspace: the VAR workspace of the p_max plan, two of whose buffers hold the
+// m x m matrices.
 struct LagWs {
   VarWs var;
   double* A = nullptr;      // T Sigma_p for every p (p_max m x m), factored in place
