@@ -270,9 +270,10 @@ __device__ __forceinline__ void order_wave_block(const double* __restrict__ Sg, 
                                         int32_t* st) {
   __shared__ double M0s[64 * R];   // M0
   constexpr int kPack = 64 * (order_next_slots(R) > 0 ? order_next_slots(R) : 1);
-  __shared__ double packM[2][kPack];
-  __shared__ int packI[2][kPack];
-  __shared__ OrderBox<64 * R> box;
+  constexpr bool kTwo = R <= 8;    // an ordering and a margin wave, else one wave without a mailbox
+  __shared__ double packM[kTwo ? 2 : 1][kPack];
+  __shared__ int packI[kTwo ? 2 : 1][kPack];
+  __shared__ OrderBox<kTwo ? 64 * R : 1> box;
   __shared__ double Sl[kLds ? 64 * R * 64 * R : 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if constexpr (kLds) {
@@ -324,10 +325,11 @@ __device__ __forceinline__ void order_wave_block(const double* __restrict__ Sg, 
     }
   }
   if (bad) raise_status(st, VL_ERR_NONFINITE);
-  for (int e = threadIdx.x; e < (int)m; e += kThreads) box.index[e] = -1;
+  if constexpr (kTwo)
+    for (int e = threadIdx.x; e < (int)m; e += kThreads) box.index[e] = -1;
   __syncthreads();
   static_assert(kThreads >= 128, "an ordering and a margin wave");
-  if (wave < (R <= 8 ? 2 : 1)) {
+  if (wave < (kTwo ? 2 : 1)) {
     const double gone = __builtin_nan("");
     double Mv[R];
     int vid[R];
@@ -337,7 +339,7 @@ __device__ __forceinline__ void order_wave_block(const double* __restrict__ Sg, 
       Mv[r] = i < m ? M0s[i] : gone;
       vid[r] = i < m ? i : 0;
     }
-    if constexpr (R > 8)
+    if constexpr (!kTwo)
       order_stage<R, OrderRole::kAll>(S, m, order, margin, box, packM[0], packI[0], Mv, vid, 0, 0,
                                       0.0);
     else if (wave == 0)
