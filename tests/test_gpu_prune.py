@@ -4,12 +4,17 @@
 
 Per variable the GPU must take the oracle's path: the same number of steps, the same BIC knot
 and the same number of nonzeros, hence exactly the same zeros.  Both sides decide in FP64.
-The GPU works on the covariance of the lag-embedded series with an inverse of the active Gram
-updated in place, the oracle on the data with a fresh solve per step, so a decision whose two
-candidates differ by less than 1e-9 (relative step length, or BIC) may go either way; such a
-variable is reported and its exact checks skipped (none occur in these cases).  Coefficients:
-|GPU - oracle| <= 1e-9 max|B|.  The CPU emulation of the GPU's arithmetic agrees with the
-oracle to ~5e-14; a wrong step, sign or dropped term moves a coefficient by >= 1e-3 max|B|.
+The GPU works on the covariance of the lag-embedded series with the inverse Cholesky factor of the
+active Gram, a row appended per join and the rows below rotated when a column leaves, and with a
+residual sum of squares that each step lowers by gamma (2 C / A_A - gamma); the oracle on the data
+with a fresh solve per step.  So a decision whose two candidates differ by less than 1e-9 (relative
+step length, or BIC) may go either way; such a variable is reported and its exact checks skipped
+(none occur in these cases).  Coefficients: |GPU - oracle| <= 1e-9 max|B|.  A CPU emulation of that
+arithmetic on series of these tests takes the oracle's events throughout; its coefficients at the
+chosen knots differ by 1e-15 to 1e-14 of max|B|, on the short series with leaving columns by up to
+2e-11; its running residual sum stays within 5e-12 (relative) of the data's over complete paths
+(y^T y minus the correlations' sum, formed anew at each knot: 1e-11).  A wrong step, sign or dropped
+term moves a coefficient by >= 1e-3 max|B|.
 """
 import numpy as np
 import pytest
