@@ -313,10 +313,12 @@ int estimate_B(const double* Cov, const double* M, const int32_t* order, int64_t
 /* X          in, n x m float32 (leading dimension ldx >= m), the series of the fit.         */
 /* order      in, m int32, a permutation (causal order, most exogenous first).                */
 /* B0, Blag   in, m x m and p x m x m float64, the unpruned estimates (estimate_B's layout). */
-/* B0_out, Blag_out  out, same layouts: the pruned matrices (exact zeros where pruned).      */
+/* B0_out, Blag_out  out, same layouts: the pruned matrices (exact zeros where pruned); they  */
+/*            may be B0 and Blag themselves.                                                 */
 /* info       out, nullable, 3 m int32: per variable (path steps, chosen knot, nonzeros).    */
-/* Workspace: the m (p+1) square covariance plus, per variable, the inverse of its active    */
-/* Gram (up to min(d, max_steps + 1) squared doubles) and 14 d doubles of path state.        */
+/* Workspace: the m (p+1) square covariance and its split sums plus, per variable, the       */
+/* triangular inverse factor of its active Gram (about a^2 / 2 doubles of a = min(d,         */
+/* max_steps + 1), in blocks of 64) and 12 d doubles of path state.                          */
 /* Host errors: m < 1, p < 1, max_steps < 0, m (p+1) > 4096 or n - p <= m (p+1) + 1 ->       */
 /* VL_ERR_SHAPE.  Status: VL_ERR_NONFINITE (the series), VL_ERR_INVALID_ARG (order not a     */
 /* permutation).  B0 and Blag must be finite.                                                */
